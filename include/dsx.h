@@ -344,8 +344,9 @@ dsx_status dsx_tune_query(dsx_model m, int32_t choice[3], int32_t* tuned);
  * Stockham passes and the number of columns per block of the axis-1 transform in LDS.
  * The autotuner times every order of every grouping of the edge's factor 2^a into 4s
  * and 2s with its odd factors (at most 12 sequences per axis, the default first) on the
- * axes the LDS kernels transform -- edges 8, 16 and 32 take register kernels of a
- * fixed order -- and the tiles 16, 32 and 64; the choices join the tune cache line.
+ * axes that take Stockham passes -- edges that are a product of two factors <= 16 take
+ * register kernels of a fixed order, which a sequence leaves as they are -- and the tiles
+ * 16, 32 and 64; the choices join the tune cache line.
  *   radices   [3][16] int32, per axis the radices in pass order, 0-terminated; each
  *             2, 4 or odd (>= 3), product the edge n of the axis; NULL keeps the plans
  *   col_tile  0 (by edge: 64 up to n1 = 64, else 32), 16, 32 or 64

@@ -966,6 +966,45 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
     return DSX_OK;
 }
 
+// Block shape of the register plane transforms: fields and planes per block and its threads.
+void plan_plane_regs(dsx_model m, long long planes, PlaneParams& pp)
+{
+    const int n2 = m->n[1], n3 = m->n[2], npairs = (n2 + 1) / 2;
+    pp.lp = n3 | 1;
+    pp.buf_elems = std::max(npairs * pp.lp, n2 * m->nh);
+    pp.fchunk = 1;
+    // a plane too large for the LDS: rows along axis 3 in blocks of a few row pairs, then axis 2
+    // in place like axis 1
+    if (planes_lds_bytes(pp) > 150 * 1024) {
+        pp.row_pairs = std::max(1, std::min(npairs, 4096 / (n3 + 2)));
+        pp.nrchunk = (npairs + pp.row_pairs - 1) / pp.row_pairs;
+        pp.buf_elems = pp.row_pairs * pp.lp;
+        pp.nfchunk = m->F;
+        pp.threads = 256;
+        return;
+    }
+    const long long cells = (long long)n2 * n3;
+    // fields per block: they share one read of the block's cells and make longer runs of the
+    // spectra; about 8192 cells x fields a block (64^3: 114 us with one field a block, 106 with
+    // two; 4096 and 8192 are equal on the smaller planes), fewer where that leaves under 1024
+    // blocks
+    int fb = (int)std::max<long long>(1, std::min<long long>(kPlaneMaxFields, 8192 / cells));
+    fb = std::min(fb, m->F);
+    while (fb > 1 && planes * ((m->F + fb - 1) / fb) < 1024) --fb;
+    if (m->tune_fchunk > 0) fb = std::min(m->tune_fchunk, m->F);
+    for (pp.fchunk = fb; pp.fchunk > 1 && planes_lds_bytes(pp) > 80 * 1024; --pp.fchunk) {}
+    pp.nfchunk = (m->F + pp.fchunk - 1) / pp.fchunk;
+    // small planes: several lattice planes per block (about 1024 cells), in <= 32 KB of LDS
+    int npl = (int)std::max<long long>(1, std::min<long long>(1024 / (cells * pp.fchunk), m->n[0]));
+    for (pp.npl = npl; pp.npl > 1 && planes_lds_bytes(pp) > 32 * 1024; --pp.npl) {}
+    const long long lines = (long long)pp.npl * pp.fchunk * std::max(npairs * std::max(pp.b3, 1), m->nh * pp.b2);
+    // even rounds over the transforms of a pass, of at most five waves: 18 x 20 x 27 ran at 45 us
+    // with one round of 448 threads and 37 with two of 256; 64^3 at 131 us in rounds of 192
+    // threads and 106 in rounds of 320
+    const long long rounds = (lines + 319) / 320;
+    pp.threads = (int)std::max<long long>(64, ((lines + rounds - 1) / rounds + 63) / 64 * 64);
+}
+
 dsx_status ensure_spectra(dsx_model m, hipStream_t st, bool force = false)
 {
     if (!m->dirty && !force) return DSX_OK;
@@ -995,31 +1034,38 @@ dsx_status ensure_spectra(dsx_model m, hipStream_t st, bool force = false)
     pp.S = m->S; pp.F = m->F; pp.T = m->T; pp.M = m->M; pp.kind = m->kind; pp.first_mono = m->first_mono;
     pp.npl = 1;
     const int npairs = (m->n[1] + 1) / 2;
-    pp.buf_elems = std::max(npairs * m->n[2], m->n[1] * m->nh);
-    // fields batched per block: more butterflies per pass, LDS <= 24 KB, and
-    // at least ~2048 blocks when the problem allows it
     const long long planes = (long long)m->M * m->S * m->n[0];
-    int fb = (int)std::max<size_t>(1, (24 * 1024 / sizeof(float2) - m->n[1] - m->n[2]) / (2 * (size_t)pp.buf_elems));
-    fb = std::min(fb, 4);
-    while (fb > 1 && planes * ((m->F + fb - 1) / fb) < 2048) --fb;
-    if (m->tune_fchunk > 0) fb = m->tune_fchunk;
-    pp.fchunk = std::min(fb, m->F);
-    pp.nfchunk = (m->F + pp.fchunk - 1) / pp.fchunk;
-    // a plane too large for the LDS (edges up to 256): rows along axis 3 in blocks of a
-    // few row pairs, then axis 2 in place like axis 1
-    const bool by_rows = planes_lds_bytes(pp) > 150 * 1024;
-    if (by_rows) {
-        pp.row_pairs = std::max(1, std::min(npairs, 4096 / (m->n[2] + 2)));
-        pp.nrchunk = (npairs + pp.row_pairs - 1) / pp.row_pairs;
-        pp.buf_elems = std::max(pp.row_pairs * m->n[2], 2 * pp.row_pairs * m->nh);
-        pp.fchunk = 1;
-        pp.nfchunk = m->F;
-    }
-    if (!by_rows) {
-        // small planes: several lattice planes per block (about 1024 cells), in <= 32 KB of LDS
-        int npl = std::max(1, 1024 / (m->n[1] * m->n[2] * pp.fchunk));
-        npl = std::min(npl, m->n[0]);
-        for (pp.npl = npl; pp.npl > 1 && planes_lds_bytes(pp) > 32 * 1024; --pp.npl) {}
+    bool by_rows = false;
+    const bool fixed = fft_reg_supported(m->n[1]) && fft_reg_supported(m->n[2]);
+    if (!fixed && split_length(m->n[2], &pp.a3, &pp.b3) && split_length(m->n[1], &pp.a2, &pp.b2)) {
+        plan_plane_regs(m, planes, pp);
+        by_rows = pp.row_pairs > 0;
+    } else {
+        pp.a3 = pp.b3 = pp.a2 = pp.b2 = 0;
+        pp.buf_elems = std::max(npairs * m->n[2], m->n[1] * m->nh);
+        // fields batched per block: more butterflies per pass, LDS <= 24 KB, and
+        // at least ~2048 blocks when the problem allows it
+        int fb = (int)std::max<size_t>(1, (24 * 1024 / sizeof(float2) - m->n[1] - m->n[2]) / (2 * (size_t)pp.buf_elems));
+        fb = std::min(fb, 4);
+        while (fb > 1 && planes * ((m->F + fb - 1) / fb) < 2048) --fb;
+        if (m->tune_fchunk > 0) fb = m->tune_fchunk;
+        pp.fchunk = std::min(fb, m->F);
+        pp.nfchunk = (m->F + pp.fchunk - 1) / pp.fchunk;
+        // a plane too large for the LDS (edges up to 256): rows along axis 3 in blocks of a
+        // few row pairs, then axis 2 in place like axis 1
+        by_rows = planes_lds_bytes(pp) > 150 * 1024;
+        if (by_rows) {
+            pp.row_pairs = std::max(1, std::min(npairs, 4096 / (m->n[2] + 2)));
+            pp.nrchunk = (npairs + pp.row_pairs - 1) / pp.row_pairs;
+            pp.buf_elems = std::max(pp.row_pairs * m->n[2], 2 * pp.row_pairs * m->nh);
+            pp.fchunk = 1;
+            pp.nfchunk = m->F;
+        } else {
+            // small planes: several lattice planes per block (about 1024 cells), in <= 32 KB of LDS
+            int npl = std::max(1, 1024 / (m->n[1] * m->n[2] * pp.fchunk));
+            npl = std::min(npl, m->n[0]);
+            for (pp.npl = npl; pp.npl > 1 && planes_lds_bytes(pp) > 32 * 1024; --pp.npl) {}
+        }
     }
     if (m->kind == DSX_NUCLEAR) {
         // spectra order: pairs (q, r) by e = q + r, q descending; p ascending within
@@ -1039,6 +1085,7 @@ dsx_status ensure_spectra(dsx_model m, hipStream_t st, bool force = false)
         a2.X = m->d_X; a2.tw1 = m->d_tw[1]; a2.p1 = m->plan[1];
         a2.n1 = m->n[1]; a2.n2 = 1; a2.cols = m->SF * m->nh; a2.M = m->M * m->n[0];
         a2.tc = m->n[1] <= 64 ? 64 : 32;
+        if (!split_length(a2.n1, &a2.a, &a2.b)) a2.a = 0;
         a2.ncolblk = (a2.cols + a2.tc - 1) / a2.tc;
         HIPCHK(m, timed("fft_axis2", st, [&] { return launch_fft_axis1(a2, st); }));
     }
@@ -1049,7 +1096,10 @@ dsx_status ensure_spectra(dsx_model m, hipStream_t st, bool force = false)
     ap.X = m->d_X; ap.tw1 = m->d_tw[0]; ap.p1 = m->plan[0];
     ap.n1 = m->n[0]; ap.n2 = m->n[1]; ap.cols = m->SF * m->nh; ap.M = m->M;
     if ((long long)ap.n2 * ap.cols <= (1LL << 30)) { ap.cols *= ap.n2; ap.n2 = 1; }
-    ap.tc = m->tune_tc > 0 ? m->tune_tc : (m->n[0] <= 64 ? 64 : 32);
+    if (!split_length(ap.n1, &ap.a, &ap.b)) ap.a = 0;
+    // columns per block: with one pass each thread keeps a whole column in registers; with two
+    // (or more, Stockham), the tile is exchanged through LDS
+    ap.tc = m->tune_tc > 0 ? m->tune_tc : (ap.a > 0 && ap.b == 1) ? 256 : (m->n[0] <= 64 ? 64 : 32);
     ap.ncolblk = (ap.cols + ap.tc - 1) / ap.tc;
     HIPCHK(m, timed("fft_axis1", st, [&] { return launch_fft_axis1(ap, st); }));
     m->dirty = false;
@@ -2078,7 +2128,8 @@ dsx_status dsx_autotune(dsx_model m, int32_t lanczos_m, void* hip_stream)
         m->tune_fchunk = best_fc;
         // FFT radix orders of the axes the LDS kernels transform (the register kernels of
         // edges 8, 16, 32 have a fixed order), one axis at a time
-        const auto reg = [](int n) { return n == 8 || n == 16 || n == 32; };
+        // (the register transforms have one order: only the Stockham passes are tuned)
+        const auto reg = [](int n) { int a, b; return split_length(n, &a, &b); };
         for (int a : {2, 1, 0}) {
             const bool used = a == 0 ? !reg(m->n[0]) : !(reg(m->n[1]) && reg(m->n[2]));
             if (!used) continue;
@@ -2094,7 +2145,7 @@ dsx_status dsx_autotune(dsx_model m, int32_t lanczos_m, void* hip_stream)
             m->plan[a] = bestp;
         }
         // columns per block of the LDS axis-1 FFT
-        if (!reg(m->n[0])) {
+        if (!fft_reg_supported(m->n[0])) {
             best = -1.f;
             int best_tc = 0;
             for (int cand : {16, 32, 64}) {

@@ -25,6 +25,19 @@ struct AxisPlan {
     int32_t rad[kMaxRadices];
 };
 
+// Lengths the register transforms take: n = A B with A, B <= kMaxRegRadix, one pass of
+// length-A transforms and one of length-B ones (B = 1: a single pass).  The most even split is
+// taken (least work and fewest registers per thread).  False where a prime factor, or what is
+// left over, exceeds kMaxRegRadix.
+constexpr int kMaxRegRadix = 16;
+inline bool split_length(int n, int* A, int* B)
+{
+    if (n <= kMaxRegRadix) { *A = n; *B = 1; return true; }
+    for (int b = 1; b * b <= n; ++b)
+        if (n % b == 0) { *A = n / b; *B = b; }
+    return *A <= kMaxRegRadix;
+}
+
 // Number of monomials u1^p u2^q u3^r with p + q + r <= N.
 __host__ __device__ constexpr int n_monomials(int N) { return (N + 1) * (N + 2) * (N + 3) / 6; }
 // Number of (q, r) pairs with q + r <= N.
@@ -72,6 +85,9 @@ struct PlaneParams {
     int32_t row_pairs;    // > 0: the plane does not fit the LDS; blocks take this many row pairs
                           // and transform along axis 3 only (axis 2 follows in place)
     int32_t nrchunk;      // row-pair chunks per plane
+    int32_t a2, b2, a3, b3;   // register transforms: n2 = a2 b2, n3 = a3 b3 (a3 = 0: Stockham passes)
+    int32_t lp;           // register transforms: complex elements between packed row pairs in LDS
+    int32_t threads;      // register transforms: threads per block
     int8_t mono[3 * kMaxMono];   // exponents (p, q, r) of field f (spectra order)
 };
 
@@ -80,6 +96,7 @@ struct Axis1Params {
     const float2* tw1;
     AxisPlan p1;
     int32_t n1, n2, cols, M, tc, ncolblk;
+    int32_t a, b;         // register transforms: n1 = a b (a = 0: Stockham passes)
 };
 
 // ---------------------------------------------------------------------------- recombination
@@ -333,6 +350,8 @@ hipError_t launch_lanczos_stencil(const LanczosParams& p, hipStream_t st);
 // Block sizes / LDS limits the host planner must respect.
 int recombine_max_threads(int hc, int magnetic);
 size_t planes_lds_bytes(const PlaneParams& p);
+constexpr int kPlaneMaxFields = 8;    // fields per block of the plane kernels at most
+bool fft_reg_supported(int n);        // edges of the fixed-length register kernels
 size_t axis1_lds_bytes(const Axis1Params& p);
 size_t lanczos_lds_bytes(const LanczosParams& p);
 

@@ -4,16 +4,22 @@
 //  k_sums        float64 sums S^{pqr}_{m,mu} = sum_R delta u1^p u2^q u3^r (nuclear) or
 //                sum_R delta M_c (magnetic): the k = 0 coefficient of every field,
 //                used for the Bragg points and to centre the float32 fields.
-//  k_fft_planes  generates the real fields of one lattice plane R1 (the Taylor
+//  k_plane_regs  generates the real fields of one lattice plane R1 (the Taylor
 //                monomials delta u1^p u2^q u3^r of Sec. III.C, the occupancy of Sec.
 //                III.B or the spin components of Sec. III.D), minus their mean, and
 //                transforms them along axes 3 (real-to-complex, two real rows packed
 //                in one complex line) and 2, entirely in LDS.
-//  k_fft_axis1   transforms along axis 1 in place, on LDS tiles of 64 contiguous
-//                columns.
-// The 1D transforms are Stockham auto-sort passes of radix 2, 3, 4, 5 and a direct
-// DFT, one output per thread, for any other prime (planned first, where it needs no
-// twiddles); twiddles come from a float64-generated table.
+//  k_axis1_regs  transforms along axis 1 in place.
+// Both take edges n = A B with A, B <= 16: A (then B) points per thread in registers.
+// Edges 8, 16 and 32 have kernels with the length fixed at compile time
+// (k_fft_planes_reg, k_fft_axis1_reg).  The remaining edges (a prime factor above 16,
+// or no such split) take k_fft_planes and k_fft_axis1: Stockham auto-sort passes in LDS
+// of radix 2, 3, 4, 5 and a direct DFT, one output per thread, for any other prime
+// (planned first, where it needs no twiddles); twiddles come from a float64-generated
+// table.
+#include <algorithm>
+#include <type_traits>
+
 #include "dsx_internal.h"
 
 namespace dsx {
@@ -544,6 +550,527 @@ __global__ __launch_bounds__(256) void k_fft_rows_merged(const PlaneParams* __re
     if (slot_of(slots, d, bx)) fft_rows_body<const PlaneParams&>(tab[d], bx);
 }
 
+// ---------------------------------------------------------------------------- register lines
+// Lengths n = A B with A, B <= kMaxRegRadix (powers of two up to 256, 10, 12, 18, 20, 24, 40,
+// 96, ...): each thread transforms A (then B) points in registers, so a line takes one or two
+// passes where the Stockham form takes one per radix, and its indices, twiddles and barriers
+// are paid once per A or B points.  The transform of A points is unrolled at compile time
+// (fours first, then the smallest prime; primes above 5 through the cosine and sine sums of
+// their pairs), its twiddles are constants rounded from float64.
+// On the 64^3 supercell (140 fields) the plane pass took 266 us in Stockham passes and 106 us
+// here (151 MB written; the vector unit is busy about 70 % of it: the transforms of 8 points,
+// their twiddles and the generation), axis 1 192 and 51 us (302 MB read and written); on
+// 18 x 20 x 27 (1008 fields) 70 and 37 us, 35 and 19 us; on 40^3 (96 fields) 50 and 27 us, 32
+// and 13 us.
+//   n = A B:  y_j[k]   = sum_i x[j + B i] e^{2 pi i i k / A}          (j < B, k < A)
+//             X[k + A l] = sum_j (e^{2 pi i j k / n} y_j[k]) e^{2 pi i j l / B}   (l < B)
+template <int N>
+struct TwTable {
+    float c[N], s[N];
+};
+
+// cos and sin of 2 pi t / N in float64 (argument reduced to the first octant, then the Taylor
+// series: the terms past x^18 are below 1e-18 there)
+__host__ __device__ constexpr double octant_cos(double x)
+{
+    double v = 1.0, t = 1.0;
+    for (int k = 1; k <= 9; ++k) { t *= -x * x / ((2 * k - 1) * (2 * k)); v += t; }
+    return v;
+}
+__host__ __device__ constexpr double octant_sin(double x)
+{
+    double v = x, t = x;
+    for (int k = 1; k <= 9; ++k) { t *= -x * x / ((2 * k) * (2 * k + 1)); v += t; }
+    return v;
+}
+template <int N>
+__host__ __device__ constexpr TwTable<N> tw_table()
+{
+    TwTable<N> tb{};
+    for (int t = 0; t < N; ++t) {
+        // 2 pi t / N = q pi / 2 + r pi / (4 N) with |r| <= N (q the nearest quadrant)
+        const int q = (8 * t + N) / (2 * N);
+        const int r = 8 * t - 2 * N * q;
+        const double x = 3.14159265358979323846 * (double)r / (4.0 * N);
+        const double c = octant_cos(x), s = octant_sin(x);
+        const int m = q & 3;
+        tb.c[t] = (float)(m == 0 ? c : m == 1 ? -s : m == 2 ? -c : s);
+        tb.s[t] = (float)(m == 0 ? s : m == 1 ? c : m == 2 ? -s : -c);
+    }
+    return tb;
+}
+
+// a e^{2 pi i T / N}, T a constant after unrolling
+template <int N>
+__device__ __forceinline__ float2 rot(float2 a, int T)
+{
+    constexpr TwTable<N> tb = tw_table<N>();
+    if (T == 0) return a;
+    if (4 * T == N) return cmuli(a);
+    if (2 * T == N) return make_float2(-a.x, -a.y);
+    return make_float2(a.x * tb.c[T] - a.y * tb.s[T], a.x * tb.s[T] + a.y * tb.c[T]);
+}
+
+__host__ __device__ constexpr int first_factor(int n)
+{
+    if (n % 4 == 0) return 4;
+    for (int f = 2; f < n; ++f)
+        if (n % f == 0) return f;
+    return n;
+}
+
+// z <- its transform of length N, natural order in and out
+template <int N>
+__device__ __forceinline__ void fft_small(float2 (&z)[N])
+{
+    constexpr int P = first_factor(N);
+    if constexpr (N == 1) {
+    } else if constexpr (N == 2) {
+        const float2 a = z[0], b = z[1];
+        z[0] = cadd(a, b);
+        z[1] = csub(a, b);
+    } else if constexpr (N == 4) {
+        const float2 a0 = cadd(z[0], z[2]), a1 = csub(z[0], z[2]), a2 = cadd(z[1], z[3]), a3 = cmuli(csub(z[1], z[3]));
+        z[0] = cadd(a0, a2);
+        z[1] = cadd(a1, a3);
+        z[2] = csub(a0, a2);
+        z[3] = csub(a1, a3);
+    } else if constexpr (P == N) {
+        // odd prime: X_k = x_0 + sum_r [(x_r + x_{N-r}) cos(2 pi r k / N) + i (x_r - x_{N-r}) sin(2 pi r k / N)],
+        // and X_{N-k} the same with the sines' sign turned
+        constexpr TwTable<N> tb = tw_table<N>();
+        constexpr int H = (N - 1) / 2;
+        float2 sm[H], df[H];
+        float2 x0 = z[0];
+#pragma unroll
+        for (int r = 1; r <= H; ++r) {
+            sm[r - 1] = cadd(z[r], z[N - r]);
+            df[r - 1] = csub(z[r], z[N - r]);
+        }
+#pragma unroll
+        for (int k = 1; k <= H; ++k) {
+            float2 e = x0, o = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int r = 1; r <= H; ++r) {
+                const float c = tb.c[(r * k) % N], s = tb.s[(r * k) % N];
+                e.x = fmaf(c, sm[r - 1].x, e.x);
+                e.y = fmaf(c, sm[r - 1].y, e.y);
+                o.x = fmaf(-s, df[r - 1].y, o.x);
+                o.y = fmaf(s, df[r - 1].x, o.y);
+            }
+            z[k] = cadd(e, o);
+            z[N - k] = csub(e, o);
+        }
+#pragma unroll
+        for (int r = 0; r < H; ++r) x0 = cadd(x0, sm[r]);
+        z[0] = x0;
+    } else {
+        constexpr int Q = N / P;
+        float2 y[P][Q];
+#pragma unroll
+        for (int a = 0; a < P; ++a) {
+#pragma unroll
+            for (int b = 0; b < Q; ++b) y[a][b] = z[a + P * b];
+            fft_small<Q>(y[a]);
+        }
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+            float2 t[P];
+#pragma unroll
+            for (int a = 0; a < P; ++a) t[a] = rot<N>(y[a][k], a * k);
+            fft_small<P>(t);
+#pragma unroll
+            for (int c = 0; c < P; ++c) z[k + Q * c] = t[c];
+        }
+    }
+}
+
+// x as it is, its derivation hidden from the compiler: base + i * stride then stays one add per
+// element instead of a product rebuilt for each
+__device__ __forceinline__ int opaque(int x)
+{
+    asm("" : "+v"(x));
+    return x;
+}
+
+__device__ __forceinline__ float2* opaque(float2* p)
+{
+    asm("" : "+v"(p));
+    return p;
+}
+
+// f(std::integral_constant<int, n>) for the run-time (block-uniform) n in 1..kMaxRegRadix
+template <class F>
+__device__ __forceinline__ void with_radix(int n, F f)
+{
+    switch (n) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 3: f(std::integral_constant<int, 3>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        case 5: f(std::integral_constant<int, 5>{}); break;
+        case 6: f(std::integral_constant<int, 6>{}); break;
+        case 7: f(std::integral_constant<int, 7>{}); break;
+        case 8: f(std::integral_constant<int, 8>{}); break;
+        case 9: f(std::integral_constant<int, 9>{}); break;
+        case 10: f(std::integral_constant<int, 10>{}); break;
+        case 11: f(std::integral_constant<int, 11>{}); break;
+        case 12: f(std::integral_constant<int, 12>{}); break;
+        case 13: f(std::integral_constant<int, 13>{}); break;
+        case 14: f(std::integral_constant<int, 14>{}); break;
+        case 15: f(std::integral_constant<int, 15>{}); break;
+        default: f(std::integral_constant<int, 16>{}); break;
+    }
+}
+
+// Generates the block's fields of npl planes (or of the row pairs j0 .. j0 + nj - 1 of one
+// plane), centred by their float64 mean, packs two real rows per complex line and transforms
+// the lines along axis 3.  Line l = b nj + jj (b = pl nfb + fb) holds Z_k, k < n3, at
+// Q[l lp + k]; its two half spectra are separated by whoever reads it (unpack_row).  A is
+// the other buffer.  Lanes run over the lines (lp odd): no bank conflicts at any n3.
+__device__ __forceinline__ void plane_lines(const PlaneParams& P, float2* A, float2* Q, const float2* tw3, const float* meanf, const int* expo, int m, int mu,
+                            int R1, int npl, int j0, int nj, int fa, int nfb)
+{
+    const int n2 = P.n2, n3 = P.n3, lp = P.lp, T = P.threads;
+    const int ncell = P.n1 * n2 * n3;
+    const int nb = npl * nfb, nl = nb * nj;
+    // generation: a thread takes the cells of one column of a row pair (both parts of a packed
+    // value) and loads their variables once for all the block's fields, up to four pairs at a
+    // time so that their loads share one latency.  The loop over the fields is uniform:
+    // exponents are scalars, a field that continues the p-run of the previous one costs one
+    // product.
+    const int pairs = npl * nj * n3;
+    const size_t at0 = (size_t)(m * P.S + mu) * ncell + ((size_t)R1 * n2 + 2 * j0) * n3;
+    const auto* occ = reinterpret_cast<const __attribute__((address_space(1))) char*>(P.occ ? gptr(P.occ) + at0 : nullptr);
+    const auto* vec = reinterpret_cast<const __attribute__((address_space(1))) char*>(P.vec ? gptr(P.vec) + 3 * at0 : nullptr);
+    const float rn3 = 1.f / (float)n3, rnj = 1.f / (float)nj;
+    const int last = n2 - 2 * j0;                  // rows of the plane from 2 j0 on
+    // the thread's pairs c0, c0 + T, ...: their column R3 and row pair r (over all planes) are stepped
+    const int dr = __builtin_amdgcn_readfirstlane(qdiv(T, n3, rn3)), dR3 = T - dr * n3;
+    int r = qdiv(threadIdx.x, n3, rn3), R3 = (int)threadIdx.x - r * n3;
+    auto generate = [&](auto un) {
+        constexpr int UN = decltype(un)::value;
+#pragma unroll 1
+        for (int c0 = threadIdx.x; c0 < pairs; c0 += UN * T) {
+            float d[UN][2], v[UN][2];
+            float3 u[UN][2];
+            int at[UN];
+            bool odd[UN];                          // the pair's second row exists
+#pragma unroll
+            for (int i = 0; i < UN; ++i) {
+                const bool in = c0 + i * T < pairs;
+                const int rc = in ? r : 0, pl = npl == 1 ? 0 : qdiv(rc, nj, rnj), jj = rc - __umul24(pl, nj);
+                at[i] = __umul24(__umul24(pl, nfb * nj) + jj, lp) + R3;
+                odd[i] = 2 * jj + 1 < last;
+                const uint32_t cell = __umul24(__umul24(pl, n2) + 2 * jj, n3) + R3;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t c = cell + (h && odd[i] ? (uint32_t)n3 : 0u);
+                    d[i][h] = occ ? *reinterpret_cast<const __attribute__((address_space(1))) float*>(occ + 4u * c) : 1.f;
+                    u[i][h] = make_float3(0.f, 0.f, 0.f);
+                    if (vec) {
+                        const auto* w = reinterpret_cast<const __attribute__((address_space(1))) float*>(vec + 12u * c);
+                        u[i][h] = make_float3(w[0], w[1], w[2]);
+                    }
+                    v[i][h] = 1.f;
+                }
+                r += dr;
+                R3 += dR3;
+                if (R3 >= n3) { R3 -= n3; ++r; }
+            }
+            int pe = -1, qe = -1, re = -1;
+            for (int fb = 0; fb < nfb; ++fb) {
+                const int f = fa + fb;
+                const float mf = meanf[fb];
+                if (P.kind == 1) {
+#pragma unroll
+                    for (int i = 0; i < UN; ++i)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) v[i][h] = f == 0 ? u[i][h].x : f == 1 ? u[i][h].y : u[i][h].z;
+                } else {
+                    const int ex = __builtin_amdgcn_readfirstlane(expo[fb]);
+                    const int ep = ex & 0xff, eq = (ex >> 8) & 0xff, er = ex >> 16;
+                    const bool next = ep == pe + 1 && eq == qe && er == re;
+                    if (!next)
+#pragma unroll
+                        for (int i = 0; i < UN; ++i) v[i][0] = v[i][1] = 1.f;
+                    for (int e = next ? ep - 1 : 0; e < ep; ++e)
+#pragma unroll
+                        for (int i = 0; i < UN; ++i) { v[i][0] *= u[i][0].x; v[i][1] *= u[i][1].x; }
+                    for (int e = next ? eq : 0; e < eq; ++e)
+#pragma unroll
+                        for (int i = 0; i < UN; ++i) { v[i][0] *= u[i][0].y; v[i][1] *= u[i][1].y; }
+                    for (int e = next ? er : 0; e < er; ++e)
+#pragma unroll
+                        for (int i = 0; i < UN; ++i) { v[i][0] *= u[i][0].z; v[i][1] *= u[i][1].z; }
+                    pe = ep; qe = eq; re = er;
+                }
+                float2* const dst = A + fb * nj * lp;
+#pragma unroll
+                for (int i = 0; i < UN; ++i)
+                    if (c0 + i * T < pairs)
+                        dst[at[i]] = make_float2(0.5f * (v[i][0] * d[i][0] - mf), odd[i] ? 0.5f * (v[i][1] * d[i][1] - mf) : 0.f);
+            }
+        }
+    };
+    if (pairs <= T) generate(std::integral_constant<int, 1>{});
+    else if (pairs <= 2 * T) generate(std::integral_constant<int, 2>{});
+    else generate(std::integral_constant<int, 4>{});
+    __syncthreads();
+    const int A3 = P.a3, B3 = P.b3;
+    const float rnl = 1.f / (float)nl;
+    with_radix(A3, [&](auto len) {
+        constexpr int R = decltype(len)::value;
+#pragma unroll 1
+        for (int it = threadIdx.x; it < nl * B3; it += T) {
+            const int j = qdiv(it, nl, rnl), l = it - j * nl;
+            const int line = opaque(l * lp), a0 = line + j;
+            float2 z[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) z[i] = A[a0 + i * B3];
+            fft_small<R>(z);
+            if (B3 > 1) {
+                // (in place: y_j[k] takes the place of x[j + B k])
+#pragma unroll
+                for (int k = 1; k < R; ++k) z[k] = cmul(z[k], tw3[j * k]);
+#pragma unroll
+                for (int k = 0; k < R; ++k) A[a0 + k * B3] = z[k];
+            } else {
+#pragma unroll
+                for (int k = 0; k < R; ++k) Q[line + k] = z[k];
+            }
+        }
+    });
+    __syncthreads();
+    if (B3 > 1) {
+        with_radix(B3, [&](auto len) {
+            constexpr int R = decltype(len)::value;
+#pragma unroll 1
+            for (int it = threadIdx.x; it < nl * A3; it += T) {
+                const int k = qdiv(it, nl, rnl), l = it - k * nl;
+                const int line = l * lp, a0 = opaque(line + k * B3), q0 = opaque(line + k);
+                float2 z[R];
+#pragma unroll
+                for (int j = 0; j < R; ++j) z[j] = A[a0 + j];
+                fft_small<R>(z);
+#pragma unroll
+                for (int i = 0; i < R; ++i) Q[q0 + i * A3] = z[i];
+            }
+        });
+        __syncthreads();
+    }
+}
+
+// Row `h` (0, 1) of the pair whose packed transform is Z, at k: X_a = Z_k + conj Z_-k or
+// X_b = -i (Z_k - conj Z_-k); the packed values are halved when they are generated
+__device__ __forceinline__ float2 unpack_row(const float2* Z, int k, int n3, int h)
+{
+    const float2 zk = Z[k], zm = Z[k ? n3 - k : 0];
+    return h ? make_float2(zk.y + zm.y, zm.x - zk.x) : make_float2(zk.x + zm.x, zk.y - zm.y);
+}
+
+// Blocks of one (configuration, site, plane group) differ in their fields and read the same
+// cells: they are dealt to one XCD (blocks go round-robin to the 8 XCDs), whose L2 then holds
+// the cells and merges the runs they write.  ng groups, nc field chunks each; the groups past
+// the last multiple of 8 keep the plain order.
+__device__ __forceinline__ void group_chunk(int bx, int ng, int nc, int& g, int& c)
+{
+    const int ng8 = ng & ~7;
+    if (bx < ng8 * nc) {
+        const int q = bx >> 3;
+        g = (q / nc) * 8 + (bx & 7);
+        c = q % nc;
+    } else {
+        const int r = bx - ng8 * nc;
+        g = ng8 + r / nc;
+        c = r % nc;
+    }
+}
+
+// Plane transforms of any A B edges: generation, axis 3, axis 2, written to the spectra.
+template <class PT>
+__device__ __forceinline__ void plane_regs_body(PT P, const int bx)
+{
+    extern __shared__ float2 smem[];
+    __shared__ float meanf[kPlaneMaxFields];
+    __shared__ int expo[kPlaneMaxFields];           // the fields' exponents p | q << 8 | r << 16
+    const int n2 = P.n2, n3 = P.n3, nh = P.nh, lp = P.lp, T = P.threads;
+    const bool rows = P.row_pairs > 0;
+    const int nrb = rows ? P.n1 * P.nrchunk : (P.n1 + P.npl - 1) / P.npl;   // groups per (configuration, site)
+    int gi, ci;
+    group_chunk(bx, P.M * P.S * nrb, P.nfchunk, gi, ci);
+    // (quotients by run-time divisors come out of the vector unit: back to scalars, so that the
+    // addresses built from them are scalar too)
+    const int g = __builtin_amdgcn_readfirstlane(gi), fc = __builtin_amdgcn_readfirstlane(ci);
+    const int ms = __builtin_amdgcn_readfirstlane(g / nrb), rb = g - ms * nrb;
+    const int m = __builtin_amdgcn_readfirstlane(ms / P.S), mu = ms - m * P.S;
+    const int R1 = rows ? __builtin_amdgcn_readfirstlane(rb / P.nrchunk) : rb * P.npl;
+    const int npl = rows ? 1 : min(P.npl, P.n1 - R1);
+    const int j0 = rows ? (rb - R1 * P.nrchunk) * P.row_pairs : 0;
+    const int nj = (rows ? min((n2 + 1) / 2, j0 + P.row_pairs) : (n2 + 1) / 2) - j0;
+    const int fa = fc * P.fchunk;
+    const int nfb = min(P.F, fa + P.fchunk) - fa;
+    float2* tw3 = smem;
+    float2* tw2 = tw3 + n3;
+    float2* A = tw2 + (rows ? 0 : n2);
+    float2* Q = A + P.npl * P.fchunk * P.buf_elems;
+    for (int i = threadIdx.x; i < n3; i += T) tw3[i] = ldg2(P.tw3, i);
+    if (!rows)
+        for (int i = threadIdx.x; i < n2; i += T) tw2[i] = ldg2(P.tw2, i);
+    if ((int)threadIdx.x < nfb) {
+        const int f = fa + threadIdx.x;
+        const int ep = P.mono[3 * f], eq = P.mono[3 * f + 1], er = P.mono[3 * f + 2];
+        const int t = P.kind == 1 ? f : mono_index(ep, eq, er);
+        expo[threadIdx.x] = ep | (eq << 8) | (er << 16);
+        meanf[threadIdx.x] = (float)(gptr(P.sums)[(size_t)(m * P.S + mu) * P.T + t] / (double)(P.n1 * n2 * n3));
+    }
+    __syncthreads();
+    plane_lines(P, A, Q, tw3, meanf, expo, m, mu, R1, npl, j0, nj, fa, nfb);
+    // one (k1, k2) column of the spectra (scalar: steps between columns are scalar offsets)
+    const int col = __builtin_amdgcn_readfirstlane(P.S * P.F * nh);
+    const int run = nfb * nh;                       // contiguous in the spectra for each (k1, k2)
+    const float rrun = 1.f / (float)run, rnh = 1.f / (float)nh;
+    float2* out = P.X + ((size_t)(m * P.n1 + R1) * n2 + 2 * j0) * col + (size_t)(mu * P.F + fa) * nh;
+    if (rows) {
+        // axis 3 only: the axis-2 transform follows in place
+        const int nr = min(n2, 2 * (j0 + nj)) - 2 * j0;
+        for (int it = threadIdx.x; it < nr * run; it += T) {
+            const int r = qdiv(it, run, rrun), e = it - r * run;
+            const int fb = qdiv(e, nh, rnh), k3 = e - fb * nh;
+            stg2(out, (size_t)r * col + e, unpack_row(Q + (fb * nj + (r >> 1)) * lp, k3, n3, r & 1));
+        }
+        return;
+    }
+    const int A2 = P.a2, B2 = P.b2;
+    const int colA = __builtin_amdgcn_readfirstlane(A2 * col), B2nh = B2 * nh;
+    const float rB2 = 1.f / (float)B2, rA2 = 1.f / (float)A2;
+    with_radix(A2, [&](auto len) {
+        constexpr int R = decltype(len)::value;
+#pragma unroll 1
+        for (int it = threadIdx.x; it < npl * B2 * run; it += T) {
+            const int q = qdiv(it, run, rrun), e = it - q * run;
+            const int pl = B2 == 1 ? q : qdiv(q, B2, rB2), j = q - pl * B2;
+            const int fb = qdiv(e, nh, rnh), k3 = e - fb * nh;
+            const int bi = pl * nfb + fb;
+            const float2* const Z = Q + bi * nj * lp;
+            float2 z[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                const int row = j + B2 * i;
+                z[i] = unpack_row(Z + __umul24(row >> 1, lp), k3, n3, row & 1);
+            }
+            fft_small<R>(z);
+            if (B2 > 1) {
+                const int a0 = opaque((bi * n2 + j) * nh + k3);
+#pragma unroll
+                for (int k = 1; k < R; ++k) z[k] = cmul(z[k], tw2[j * k]);
+#pragma unroll
+                for (int k = 0; k < R; ++k) A[a0 + k * B2nh] = z[k];
+            } else {
+                float2* const o = opaque(out + (size_t)pl * n2 * col + e);
+#pragma unroll
+                for (int k = 0; k < R; ++k) stg2(o + k * (size_t)col, 0, z[k]);
+            }
+        }
+    });
+    if (B2 == 1) return;
+    __syncthreads();
+    with_radix(B2, [&](auto len) {
+        constexpr int R = decltype(len)::value;
+#pragma unroll 1
+        for (int it = threadIdx.x; it < npl * A2 * run; it += T) {
+            const int q = qdiv(it, run, rrun), e = it - q * run;
+            const int pl = qdiv(q, A2, rA2), k = q - pl * A2;
+            const int fb = qdiv(e, nh, rnh), k3 = e - fb * nh;
+            const int a0 = opaque(((pl * nfb + fb) * n2 + k * B2) * nh + k3);
+            float2 z[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) z[j] = A[a0 + j * nh];
+            fft_small<R>(z);
+            float2* const o = opaque(out + (size_t)(pl * n2 + k) * col + e);
+#pragma unroll
+            for (int l = 0; l < R; ++l) stg2(o + l * (size_t)colA, 0, z[l]);
+        }
+    });
+}
+
+// (at most 96 VGPRs: the transforms of up to 16 points fit, and two 512-thread blocks or more share a CU)
+__global__ __launch_bounds__(512, 5) void k_plane_regs(PlaneParams P) { plane_regs_body<PlaneParams>(P, blockIdx.x); }
+__global__ __launch_bounds__(512, 5) void k_plane_regs_merged(const PlaneParams* __restrict__ tab, const Slot* __restrict__ slots)
+{
+    int d, bx;
+    if (slot_of(slots, d, bx)) plane_regs_body<const PlaneParams&>(tab[d], bx);
+}
+
+// Axis 1 in place for n1 = A B: a thread loads A values of a column straight into registers
+// (the lanes' columns are contiguous), transforms them, and exchanges them through LDS for its
+// B values of the second pass: one read and one write of the spectra, one barrier.
+template <class PT>
+__device__ __forceinline__ void axis1_regs_body(PT P, const int bx)
+{
+    extern __shared__ float2 smem[];
+    const int A1 = P.a, B1 = P.b, tc = P.tc, n1 = P.n1;
+    const int b = __builtin_amdgcn_readfirstlane(bx / P.ncolblk), cb = bx - b * P.ncolblk;
+    const int m = __builtin_amdgcn_readfirstlane(b / P.n2), k2 = b - m * P.n2;
+    const int c0 = cb * tc, nc = min(tc, P.cols - c0);
+    const size_t rowstride = (size_t)P.n2 * P.cols;
+    const size_t rowB = rowstride * B1, rowA = rowstride * A1;
+    float2* const base = P.X + ((size_t)m * n1 * P.n2 + k2) * P.cols + c0;
+    float2* const tw = smem;
+    float2* const W = tw + n1;                       // [n1][tc]
+    const float rtc = 1.f / (float)tc;
+    if (B1 > 1) {
+        for (int i = threadIdx.x; i < n1; i += blockDim.x) tw[i] = ldg2(P.tw1, i);
+        __syncthreads();
+    }
+    with_radix(A1, [&](auto len) {
+        constexpr int R = decltype(len)::value;
+        for (int it = threadIdx.x; it < tc * B1; it += blockDim.x) {
+            const int j = qdiv(it, tc, rtc), c = it - j * tc;
+            if (c >= nc) continue;
+            float2* const src = opaque(base + (size_t)j * rowstride + c);
+            float2 z[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) z[i] = ldg2(src + i * rowB, 0);
+            fft_small<R>(z);
+            if (B1 > 1) {
+                const int w0 = opaque(it);              // j tc + c
+#pragma unroll
+                for (int k = 1; k < R; ++k) z[k] = cmul(z[k], tw[j * k]);
+#pragma unroll
+                for (int k = 0; k < R; ++k) W[w0 + k * B1 * tc] = z[k];
+            } else {
+#pragma unroll
+                for (int k = 0; k < R; ++k) stg2(src, (size_t)k * rowstride, z[k]);
+            }
+        }
+    });
+    if (B1 == 1) return;
+    __syncthreads();
+    with_radix(B1, [&](auto len) {
+        constexpr int R = decltype(len)::value;
+        for (int it = threadIdx.x; it < tc * A1; it += blockDim.x) {
+            const int k = qdiv(it, tc, rtc), c = it - k * tc;
+            if (c >= nc) continue;
+            const int w0 = opaque(k * B1 * tc + c);
+            float2 z[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) z[j] = W[w0 + j * tc];
+            fft_small<R>(z);
+            float2* const dst = opaque(base + (size_t)k * rowstride + c);
+#pragma unroll
+            for (int l = 0; l < R; ++l) stg2(dst + l * rowA, 0, z[l]);
+        }
+    });
+}
+
+__global__ __launch_bounds__(256) void k_axis1_regs(Axis1Params P) { axis1_regs_body<Axis1Params>(P, blockIdx.x); }
+__global__ __launch_bounds__(256) void k_axis1_regs_merged(const Axis1Params* __restrict__ tab, const Slot* __restrict__ slots)
+{
+    int d, bx;
+    if (slot_of(slots, d, bx)) axis1_regs_body<const Axis1Params&>(tab[d], bx);
+}
+
 // ---------------------------------------------------------------------------- register FFTs
 // Power-of-two lengths L <= 32 are transformed by one thread in registers
 // (radix-2 decimation in time, input in bit-reversed order), so a line needs no
@@ -778,6 +1305,9 @@ static hipError_t launch_planes_reg2(const PlaneParams& p, hipStream_t st)
 
 size_t planes_lds_bytes(const PlaneParams& p)
 {
+    if (p.a3 > 0)
+        return sizeof(float2) * (size_t)((p.row_pairs > 0 ? 0 : p.n2) + p.n3 +
+                                         p.npl * p.fchunk * (p.buf_elems + (p.row_pairs > 0 ? p.row_pairs : (p.n2 + 1) / 2) * p.lp));
     return sizeof(float2) * (size_t)((p.row_pairs > 0 ? 0 : p.n2) + p.n3 + 2 * (p.npl > 1 ? p.npl : 1) * p.fchunk * p.buf_elems);
 }
 
@@ -791,6 +1321,17 @@ hipError_t launch_fft_planes(const PlaneParams& p, hipStream_t st)
         }
     }
     const size_t lds = planes_lds_bytes(p);
+    if (p.a3 > 0) {
+        const int groups = p.row_pairs > 0 ? p.n1 * p.nrchunk : (p.n1 + p.npl - 1) / p.npl;
+        if (p.npl < 1 || p.fchunk < 1 || p.fchunk > kPlaneMaxFields || p.threads < 64 || p.threads > 512 || p.a3 * p.b3 != p.n3 ||
+            p.lp < p.n3 || (p.row_pairs <= 0 && p.a2 * p.b2 != p.n2))
+            return hipErrorInvalidValue;
+        if (lds > 65536) {
+            hipError_t e = hipFuncSetAttribute((const void*)k_plane_regs, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        return dispatch(k_plane_regs, k_plane_regs_merged, p.M * p.S * groups * p.nfchunk, p.threads, lds, st, p);
+    }
     if (p.row_pairs > 0) {
         if (lds > 65536) {
             hipError_t e = hipFuncSetAttribute((const void*)k_fft_rows,
@@ -857,6 +1398,7 @@ __global__ __launch_bounds__(256) void k_fft_axis1_merged(const Axis1Params* __r
 
 size_t axis1_lds_bytes(const Axis1Params& p)
 {
+    if (p.a > 0) return p.b > 1 ? sizeof(float2) * (size_t)(p.n1 + p.n1 * p.tc) : 0;
     return sizeof(float2) * (size_t)(p.n1 + 2 * p.n1 * p.tc);
 }
 
@@ -870,6 +1412,16 @@ hipError_t launch_fft_axis1(const Axis1Params& p, hipStream_t st)
         return dispatch(k_fft_axis1_reg<32>, k_fft_axis1_reg_merged<32>, grid, 256, 0, st, p);
     }
     const size_t lds = axis1_lds_bytes(p);
+    if (p.a > 0) {
+        if (p.a * p.b != p.n1) return hipErrorInvalidValue;
+        if (lds > 65536) {
+            hipError_t e = hipFuncSetAttribute((const void*)k_axis1_regs, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        const int items = p.tc * (p.b > 1 ? std::max(p.a, p.b) : 1);
+        const unsigned threads = std::min(256, (items + 63) / 64 * 64);
+        return dispatch(k_axis1_regs, k_axis1_regs_merged, p.M * p.n2 * p.ncolblk, threads, lds, st, p);
+    }
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute((const void*)k_fft_axis1,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
