@@ -281,6 +281,9 @@ struct DeviceTables {
     int H3min = 0, nH3span = 0;
     int nwork = 0, nwork2 = 0, nwork3 = 0, hc = 0, nchunk3 = 0, block = 0;
     int n3s = 0, block3 = 0;   // k3 per slice, threads per plane of a sliced block
+    int4* work_s = nullptr;    // nuclear models: blocks of the sites form
+    int nwork_s = 0, npl_s = 1, mg_s = 1, gthreads_s = 64, rows_s = 1, csites_s = 1, n3s_s = 1, slices_s = 1;
+    int ks3 = 0, nact3 = 0;    // the k3 with points in the box: nact3 of them, cyclically from ks3
     int4* work_mr = nullptr;   // magnetic models: blocks of the row-staged form (null: not used)
     int nwork_mr = 0, rows_mr = 0, csites_mr = 0, qmod_mr = 0, qmod2_mr = 0, qmod1_mr = 0;
 };
@@ -289,7 +292,7 @@ struct DeviceTables {
 void free_tables(DeviceTables& t)
 {
     dfree(t.tab1); dfree(t.tab2); dfree(t.tabK2); dfree(t.tabK3); dfree(t.tabH3);
-    dfree(t.work); dfree(t.work2); dfree(t.work3); dfree(t.k3tab); dfree(t.work_mr);
+    dfree(t.work_s); dfree(t.work); dfree(t.work2); dfree(t.work3); dfree(t.k3tab); dfree(t.work_mr);
     t = DeviceTables{};
 }
 
@@ -491,6 +494,46 @@ dsx_status follow(dsx_model m, hipStream_t st)
     return DSX_OK;
 }
 
+// Block shape of the sites form on a box (t.hc, t.nchunk3, t.nact3 are set): two planes per
+// block where a column has more than one, halves of the k3 range when they still are 8 or more
+// long, the sites of a chunk within 48 KB of LDS (three blocks per CU; a smaller slice where one
+// site alone exceeds 96 KB), rows for about 320 items a group, and, with the threads that
+// leaves over, several configurations at a time.
+void plan_sites_form(dsx_model m, const Box& bx, int maxH2, DeviceTables& t)
+{
+    const int S = m->S, qp = n_pairs(m->order) | 1;
+    int maxH1 = 0;
+    for (int k = 0; k < m->n[0]; ++k) maxH1 = std::max(maxH1, hcount(k, m->n[0], bx.g0[0], bx.cnt[0]));
+    t.npl_s = maxH1 > 1 ? 2 : 1;
+    t.slices_s = t.nact3 >= 16 ? 2 : 1;
+    auto per_site = [&](int npl, int n3s) { return sizeof(float2) * (size_t)npl * n3s * qp; };
+    for (;;) {
+        t.n3s_s = (t.nact3 + t.slices_s - 1) / t.slices_s;
+        const bool fits = per_site(t.npl_s, t.n3s_s) <= 96 * 1024 && t.n3s_s * t.nchunk3 <= 512 / t.npl_s;
+        if (fits || (t.slices_s == 8 && t.npl_s == 1)) break;
+        if (t.slices_s < 8) t.slices_s *= 2;
+        else t.npl_s = 1;
+    }
+    t.slices_s = (t.nact3 + t.n3s_s - 1) / t.n3s_s;
+    t.csites_s = (int)std::max<size_t>(1, std::min<size_t>(S, 48 * 1024 / per_site(t.npl_s, t.n3s_s)));
+    // even chunks
+    const int nch = (S + t.csites_s - 1) / t.csites_s;
+    t.csites_s = (S + nch - 1) / nch;
+    const int per_row = t.n3s_s * t.nchunk3;
+    int rows = std::max(1, std::min(std::max(1, 320 / per_row), std::max(1, 2048 / S)));
+    rows = std::min(rows, std::max(1, maxH2));
+    const int parts = (std::max(1, maxH2) + rows - 1) / rows;
+    t.rows_s = (std::max(1, maxH2) + parts - 1) / parts;
+    const int maxg = 512 / t.npl_s / 64 * 64;
+    t.gthreads_s = std::min(maxg, (t.rows_s * per_row + 63) / 64 * 64);
+    t.mg_s = 1;
+    if (m->M > 1) {
+        const size_t one = per_site(t.npl_s, t.n3s_s) * t.csites_s;
+        t.mg_s = std::max(1, std::min(m->M, 512 / (t.npl_s * t.gthreads_s)));
+        while (t.mg_s > 1 && t.mg_s * one > 64 * 1024) --t.mg_s;
+    }
+}
+
 dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
 {
     auto it = m->tables.find(bx);
@@ -558,7 +601,7 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
     const int h2per = std::max(1, maxT / per_h2);
     const bool friedel = symmetric_box(bx);
     if (bx.half && !friedel) return fail(DSX_ERR_STATE, "half storage needs a symmetric box");
-    std::vector<std::pair<long long, int4>> items, items2, items3, items_mr;
+    std::vector<std::pair<long long, int4>> items, items2, items3, items_mr, items_s;
     int maxrows = 1;
     // the row-staged magnetic form: one thread per G3 of the box (at most
     // kMagRowsMaxThreads), rows per block from the LDS budget (about four blocks per CU),
@@ -613,6 +656,10 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
         rows = std::min(std::min(rows, kMagRowsMaxRows), maxH2);
         if (rows >= 1) { t.rows_mr = rows; t.csites_mr = cs; }
     }
+    // the k3 with points in the box (a box shorter than the supercell has none on the others)
+    t.nact3 = std::min(n3, bx.cnt[2]);
+    t.ks3 = t.nact3 == n3 ? 0 : (int)(bx.g0[2] - (long)n3 * floordiv_l(bx.g0[2], n3));
+    if (!mag) plan_sites_form(m, bx, maxH2, t);
     // k3 slices of the two-plane blocks: halves of the k3 range when it is long enough
     // that a slice still writes 64-byte runs of an output row
     const int nsl = (n3 >= 16) ? 2 : 1;
@@ -678,6 +725,22 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
                     }
                 }
             }
+            if (!mag) {
+                const int nps = (nH2 + t.rows_s - 1) / t.rows_s;
+                const int rps = (nH2 + nps - 1) / nps;
+                for (int part = 0; part < nps; ++part) {
+                    const int h2a = part * rps, h2b = std::min(nH2, h2a + rps);
+                    if (h2a >= h2b) continue;
+                    for (size_t i = 0; i < planes.size(); i += t.npl_s) {
+                        const int j1 = planes[i].first;
+                        const int hasb = t.npl_s == 2 && i + 1 < planes.size() ? 1 : 0;
+                        const int mb = hasb ? planes[i + 1].second : 0;
+                        const int wv = h2a | (h2b << 12) | (planes[i].second << 24) | (hasb << 25) | (mb << 26);
+                        for (int sl = 0; sl < t.slices_s; ++sl)
+                            items_s.push_back({key * 4096 + j1, make_int4(k1, k2, k1 + n1 * (H1lo + j1), wv | (sl << 27))});
+                    }
+                }
+            }
             for (int part = 0; part < np; ++part) {
                 const int h2a = part * rpp, h2b = std::min(nH2, h2a + rpp);
                 if (h2a >= h2b) continue;
@@ -717,7 +780,8 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
         return wl;
     };
     const std::vector<int4> work = xcd_order(items), work2 = xcd_order(items2), work3 = xcd_order(items3);
-    const std::vector<int4> work_mr = xcd_order(items_mr);
+    const std::vector<int4> work_mr = xcd_order(items_mr), work_s = xcd_order(items_s);
+    t.nwork_s = (int)work_s.size();
     t.nwork_mr = (int)work_mr.size();
     t.nwork = (int)work.size();
     t.nwork2 = (int)work2.size();
@@ -752,6 +816,9 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
         (!work3.empty() &&
          ((e = hipMalloc(&t.work3, sizeof(int4) * work3.size())) != hipSuccess ||
           (e = hipMemcpy(t.work3, work3.data(), sizeof(int4) * work3.size(), hipMemcpyHostToDevice)) != hipSuccess)) ||
+        (!work_s.empty() &&
+         ((e = hipMalloc(&t.work_s, sizeof(int4) * work_s.size())) != hipSuccess ||
+          (e = hipMemcpy(t.work_s, work_s.data(), sizeof(int4) * work_s.size(), hipMemcpyHostToDevice)) != hipSuccess)) ||
         (!work_mr.empty() &&
          ((e = hipMalloc(&t.work_mr, sizeof(int4) * work_mr.size())) != hipSuccess ||
           (e = hipMemcpy(t.work_mr, work_mr.data(), sizeof(int4) * work_mr.size(), hipMemcpyHostToDevice)) != hipSuccess)) ||
@@ -877,6 +944,25 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         const int staged = tb->qmod2_mr > 0 ? std::min(tb->rows_mr, tb->qmod2_mr) : tb->rows_mr;
         lp.lds = sizeof(float2) * magnetic_rows_lds_elems(staged, tb->csites_mr, m->S, m->nclass, n3, tb->nH3span);
     }
+    const size_t staged_lds = lp.lds;     // (the limit on sites, order and box is this one's)
+    if (!mag) {
+        // the sites form
+        p.work = tb->work_s;
+        p.nwork = tb->nwork_s;
+        p.npl = tb->npl_s; p.mg = tb->mg_s; p.gthreads = tb->gthreads_s;
+        p.ks3 = tb->ks3; p.nact3 = tb->nact3;
+        p.rows = tb->rows_s; p.csites = tb->csites_s; p.n3s = tb->n3s_s;
+        p.k3tab = tb->k3tab;
+        p.bs_elems = tb->csites_s * tb->n3s_s * (n_pairs(m->order) | 1);
+        const bool multi = m->M > 1 || p.variant == 1;
+        if (!multi) p.mg = 1;
+        lp.block = p.npl * p.mg * p.gthreads;
+        const bool par = p.parity && p.variant != 2;
+        lp.lds = sizeof(float2) * sites_lds_elems(p.npl, p.mg, p.csites, p.n3s, m->order, m->S, p.rows,
+                                                  par ? 0 : m->nclass * tb->nH3span);
+        // the groups' sums at the end
+        if (p.mg > 1) lp.lds = std::max(lp.lds, sizeof(float) * (size_t)(p.mg - 1) * lp.hc * p.npl * p.gthreads);
+    }
     // direct form: asked for, or by default where the levelled forms would spend their
     // blocks on set-up (one or two sites x configurations)
     if (direct_form_applies(m) && (p.variant == 5 || (p.variant == 0 && m->S * m->M <= 2)) &&
@@ -885,7 +971,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         lp.lds = 0;
         p.planes = stored_planes(bx);   // a half-stored box: its planes G1 <= 0 only
     }
-    if (lp.lds > 160 * 1024) return fail(DSX_ERR_UNSUPPORTED, "recombination does not fit the LDS for this box");
+    if (!lp.direct && std::max(lp.lds, staged_lds) > 160 * 1024) return fail(DSX_ERR_UNSUPPORTED, "recombination does not fit the LDS for this box");
     // folded form: every r_mu2 a multiple of 1/2 (exactly, as given), fewer r3 classes
     // than sites, and the class buffers fit the LDS
     // (the folded kernel addresses the spectra of one configuration with 31-bit offsets)
@@ -926,6 +1012,8 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
             if (sliced) p.ostream = 0;
         }
     }
+
+    if (!mag && !lp.direct && !p.fold && tb->slices_s > 1) p.ostream = 0;   // likewise
 
     BraggParams& q = lp.bp;
     std::memset(&q, 0, sizeof(q));

@@ -133,7 +133,11 @@ struct RecombParams {
                             // level A sums the sites of each r3 class (per H2 residue)
     int32_t fold_l2;        // H2 residues of the folded form: 1 (every r_mu2 whole) or 2
     int32_t n3s;            // folded form: k3 per slice; block slice s covers k3 in [s n3s, (s + 1) n3s)
-    const int2* k3tab;      // folded form: [n3] (H3lo, count) of the H3 with k3 + n3 H3 in the box
+    // sites form: planes per block (1 or 2), configurations at a time, threads per group, the
+    // first k3 with points in the box and how many there are (cyclically), blocks of at most
+    // `rows` rows and site chunks of `csites` sites
+    int32_t npl, mg, gthreads, ks3, nact3;
+    const int2* k3tab;      // folded and sites forms: [n3] (H3lo, count) of the H3 with k3 + n3 H3 in the box
     int32_t hmin_s[8];      // folded form, per slice: the fewest H3 values any item of a full wave has
     int32_t sgn2[kMaxSites];         // per sorted position: e^{2 pi i r_mu2} = +-1
     int32_t parity;         // every r_mu3 is a multiple of 1/2 (the parity form applies)
@@ -314,6 +318,12 @@ hipError_t dispatch(void (*one)(P), void (*merged)(const P*, const Slot*), unsig
 hipError_t launch_sums(const SumsParams& p, int order, hipStream_t st);
 hipError_t launch_fft_planes(const PlaneParams& p, hipStream_t st);
 hipError_t launch_fft_axis1(const Axis1Params& p, hipStream_t st);
+// Group layout of the sites form for a plan: float2 elements of its LDS
+inline size_t sites_lds_elems(int npl, int mg, int csites, int n3s, int order, int S, int rows, int phases)
+{
+    return (size_t)mg * npl * csites * n3s * (n_pairs(order) | 1) + (size_t)npl * S + (size_t)rows * S + phases
+         + (npl * (order + 1) + 1) / 2;
+}
 hipError_t launch_recombine_nuclear(const RecombParams& p, int order, int hc, int block,
                                     size_t lds, hipStream_t st);
 hipError_t launch_recombine_magnetic(const RecombParams& p, int hc, int block, size_t lds,

@@ -11,9 +11,8 @@
 // over the three axes:
 //   level A (per block: fixed k1, k2 and H1, i.e. fixed g1)
 //       B_mu^{qr}(k3) = b_mu e^{2 pi i g1 r_mu1} sum_p (i t1)^p/p! X^{pqr}_mu(k1,k2,k3)
-//       in LDS; the spectra of one site of column (k1, k2), then of the mirrored
-//       column (-k1, -k2) that supplies k3 > n3/2 through X(k) = conj X(-k), are
-//       staged in LDS with independent coalesced loads;
+//       in LDS, from the spectra of column (k1, k2) and of the mirrored column
+//       (-k1, -k2) that supplies k3 > n3/2 through X(k) = conj X(-k);
 //   level B (per thread: fixed H2 and k3)
 //       D_c^r = sum_{mu in c} e^{2 pi i (g2 r_mu2 + k3 r_mu3/n3)} sum_q (i t2)^q/q! B_mu^{qr} / r!
 //       where the class c groups the sites that share r_mu3;
@@ -240,175 +239,226 @@ __device__ __forceinline__ float parity_eval(const float2 (&S)[N + 1], float t3)
     return acc.x * acc.x + acc.y * acc.y;
 }
 
-// MULTI: more than one configuration; a single configuration needs no separate
-// |F|^2 accumulator, and the registers it frees hold the level-A prefetch.
-// PAR: every r_mu3 is a multiple of 1/2, so e^{2 pi i H3 r_c3} = +-1 by the parity
-// of H3: level B folds the classes into two coefficient sets, one for even and one
-// for odd H3, and level C evaluates a single polynomial per voxel.
+// Sites form (any sites).  A block takes one or two planes G1 (and G1 + n1) of one spectra
+// column, the H2 rows h2a..h2b and one slice of n3s of the k3 that have points in the box, and
+// P.mg configurations at a time: its threads are P.npl x P.mg groups of bh, one (H2, H3 chunk,
+// k3) item per thread of a group.
+//   level A  items (configuration, site, pair (q, r), k3) over the whole block, the sites of a
+//            chunk at once: each reads its p-terms straight from the (L2-resident) column, for
+//            both planes, and leaves them in Bs with every phase but the g2 one, and 1/r!;
+//   level B  per thread, its own configuration and plane: q contracted per site, the sites of a
+//            class summed with their g2 phases (staged once per block);
+//   level C  F(H3) accumulated over the classes, or, in the parity form (PAR: every r_mu3 a
+//            multiple of 1/2), the classes folded into the coefficient sets of even and odd H3.
+// A pass over the configurations costs two barriers per site chunk and one latency of loads
+// for all its sites, where staging the sites one by one paid both per site: 16 occupational
+// sites on a 261^3 box (half of it computed) ran at 377 us that way and 137 us here, six sites at
+// order 5 with three configurations on 77 x 85 x 113 at 103 and 62 us, 32 occupational sites with
+// 100 configurations on 125^3 at 5.0 and 0.97 ms, five sites at order 4 with two on 389 x 389 x 5
+// at 282 and 47 us (there only the k3 with points in the box are taken).  Bound by vector issue (levels B and C) and
+// by the latency of level A, which other blocks of the CU cover (LDS of a block <= 64 KB).
+// Several configurations share a block wherever its items leave threads over: each group keeps
+// its own |F|^2 sums, added through LDS in a fixed order at the end.
+template <int N>
+constexpr int kPairPitch = n_pairs(N) | 1;   // odd: the k3 of a wave's lanes start on different banks
+
 template <int N, int HC, bool MULTI, bool PAR, class PT>
-__device__ __forceinline__ void recombine_nuclear_body(PT P, const int bx)
+__device__ __forceinline__ void recombine_sites_body(PT P, const int bx)
 {
     extern __shared__ float2 smem[];
-    constexpr int QR = n_pairs(N);
-    BlockWork w;
-    if (!decode_block(P, w, bx)) return;
-    float2* Bs = smem;                                  // [sites of the chunk][n3][QR]
-    float2* Xs = smem + P.bs_elems;                     // [F][nh] staging
-    float2* tHs = Xs + P.xs_elems;                      // [nclass][nH3span]
-    __shared__ int jtab[2][QR];                         // e = q + r and first field of pair j
-    const int n1 = P.n1, n2 = P.n2, n3 = P.n3, nh = P.nh;
+    constexpr int QR = n_pairs(N), QP = kPairPitch<N>;
+    const int4 wi = P.work[bx];
+    if (wi.x < 0) return;
+    const int k1 = wi.x, k2 = wi.y, h2a = wi.w & 0xfff, h2b = (wi.w >> 12) & 0xfff;
+    const bool hasb = (wi.w >> 25) & 1;
+    const int n1 = P.n1, n2 = P.n2, n3 = P.n3, nh = P.nh, S = P.S, n3s = P.n3s;
+    const int npl = P.npl, mg = MULTI ? P.mg : 1;
+    const int t0 = ((wi.w >> 27) & 7) * n3s;                    // first active k3 of the slice
+    const int k3n = min(n3s, P.nact3 - t0);
+    const int rows = h2b - h2a;
+    const int bh = P.gthreads;                                  // threads per group (a multiple of 64)
+    const int grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / bh);
+    const int gm = npl == 2 ? grp >> 1 : grp, sel = npl == 2 ? grp & 1 : 0;
+    const bool mirror = ((wi.w >> (sel ? 26 : 24)) & 1) != 0;
+    const int G1 = wi.z + (sel && hasb ? n1 : 0);
+    int H2lo, nH2;
+    hrange(k2, n2, P.g0[1], P.cnt[1], H2lo, nH2);
+    float2* Bs = smem;                                          // [mg][npl][csites][n3s][QP]
+    float2* wbt = Bs + (size_t)mg * npl * P.bs_elems;           // [npl][S]  b e^{2 pi i g1 r1}
+    float2* t2 = wbt + npl * S;                                 // [rows][S] e^{2 pi i g2 r2}
+    float2* tHs = t2 + P.rows * S;                              // [nclass][nH3span] (class form)
+    float* cm = reinterpret_cast<float*>(tHs + (PAR ? 0 : P.nclass * P.nH3span));   // [npl][N + 1]
+    __shared__ int jtab[2][QR];              // terms N - e + 1, field of p = 0 of pair j
+    __shared__ float jfr[QR];                // 1/r! of pair j
     const int SFnh = P.SF * nh;
-    const float tau1 = (float)(6.283185307179586 * (double)w.G1 / (double)n1);
     for (int j = threadIdx.x; j < QR; j += blockDim.x) {
         int e = 0;
         while ((e + 1) * (e + 2) / 2 <= j) ++e;
         int cum = 0;
         for (int ee = 0; ee < e; ++ee) cum += (ee + 1) * (N - ee + 1);
-        cum += (j - e * (e + 1) / 2) * (N - e + 1);
-        jtab[0][j] = e;
-        jtab[1][j] = cum - P.first_mono;
+        const int r = j - e * (e + 1) / 2;
+        jtab[0][j] = N - e + 1;
+        jtab[1][j] = cum + r * (N - e + 1) - P.first_mono;
+        jfr[j] = inv_factorial_rt(r);
+    }
+    // tau1^p / p! with the sign of i^p's nonzero part, per plane
+    for (int t = threadIdx.x; t < npl * (N + 1); t += blockDim.x) {
+        const int pl = t / (N + 1), p = t - pl * (N + 1);
+        const float tau1 = (float)((double)(wi.z + (pl && hasb ? n1 : 0)) * P.tw[0]);
+        float mag = inv_factorial_rt(p);
+        for (int v = 1; v <= p; ++v) mag *= tau1;
+        cm[t] = ((p & 3) < 2) ? mag : -mag;
+    }
+    for (int t = threadIdx.x; t < npl * S; t += blockDim.x) {
+        const int pl = t / S, sl = t - pl * S;
+        wbt[t] = P.tab1[(size_t)P.site_of[sl] * P.cnt[0] + (wi.z + (pl && hasb ? n1 : 0) - P.g0[0])];
+    }
+    const float rS = 1.f / (float)S, rk = 1.f / (float)k3n;
+    for (int t = threadIdx.x; t < rows * S; t += blockDim.x) {
+        const int r = qdiv_r(t, S, rS), sl = t - r * S;
+        t2[t] = P.tab2[(size_t)P.site_of[sl] * P.cnt[1] + (k2 + n2 * (H2lo + h2a + r) - P.g0[1])];
     }
     const float2* tH0 = PAR ? nullptr : stage_class_phases(P, tHs);
 
-    // this thread's item: (H2, H3 chunk, k3) with k3 fastest
-    const int nitems = (w.h2b - w.h2a) * n3 * P.nchunk3;
-    const int item = threadIdx.x;
-    const bool active = item < nitems;
-    int k3 = 0, ch = 0, h2 = w.h2a;
+    // this thread's item (row, H3 chunk, k3), k3 fastest
+    const int item = (int)threadIdx.x - grp * bh;
+    const bool active = item < rows * k3n * P.nchunk3 && (sel == 0 || hasb);
+    int kl = 0, ch = 0, row = 0;
     if (active) {
-        k3 = item % n3;
-        const int r = item / n3;
-        ch = r % P.nchunk3;
-        h2 = w.h2a + r / P.nchunk3;
+        const int r = qdiv_r(item, k3n, rk);
+        kl = item - r * k3n;
+        row = P.nchunk3 == 1 ? r : qdiv_r(r, P.nchunk3, 1.f / (float)P.nchunk3);
+        ch = r - row * P.nchunk3;
     }
-    const int G2 = w.k2 + n2 * (w.H2lo + h2);
+    int k3 = P.ks3 + t0 + kl;                                   // (the active k3 run cyclically from ks3)
+    k3 -= k3 >= n3 ? n3 : 0;
+    const int G2 = k2 + n2 * (H2lo + h2a + row);
     const int i2 = G2 - P.g0[1];
-    int H3lo, nH3;
-    hrange(k3, n3, P.g0[2], P.cnt[2], H3lo, nH3);
-    const int hbeg = ch * HC;
-    const int hcnt = active ? max(0, min(HC, nH3 - hbeg)) : 0;
-    const int hmin = wave_min_uniform(active ? hcnt : HC);   // iterations every lane needs
+    const int2 h3 = P.k3tab[k3];
+    const int H3lo = h3.x, hbeg = ch * HC;
+    const int hcnt = active ? max(0, min(HC, h3.y - hbeg)) : 0;
+    const int hmin = wave_min_uniform(active ? hcnt : HC);     // iterations every lane needs
     const float tau2 = (float)(6.283185307179586 * (double)G2 / (double)n2);
     const float c3 = (float)(6.283185307179586 / (double)n3);
-    const float t3base = (float)(k3 + n3 * (H3lo + hbeg)) * c3;   // tau3 of h = 0
-    const float dt3 = 6.283185307179586f;                          // tau3 step per H3
-    float a2[N + 1];   // tau2^q / q!
+    const float t3base = (float)(k3 + n3 * (H3lo + hbeg)) * c3; // tau3 of h = 0
+    const float dt3 = 6.283185307179586f;                       // tau3 step per H3
+    float a2[N + 1];                                            // tau2^q / q!
     a2[0] = 1.f;
 #pragma unroll
     for (int q = 1; q <= N; ++q) a2[q] = a2[q - 1] * tau2 / (float)q;
     // g1 a* + g2 b* of the thread's row (for |Q|-dependent scattering factors)
-    const float g1f = (float)w.G1 / (float)n1, g2f = (float)G2 / (float)n2;
+    const float g1f = (float)G1 / (float)n1, g2f = (float)G2 / (float)n2;
     const float q12x = g1f * P.recip[0] + g2f * P.recip[3];
     const float q12y = g1f * P.recip[1] + g2f * P.recip[4];
     const float q12z = g1f * P.recip[2] + g2f * P.recip[5];
-
     float I[MULTI ? HC : 1];
 #pragma unroll
     for (int h = 0; h < (MULTI ? HC : 1); ++h) I[h] = 0.f;
-
-    const size_t col = ((size_t)w.k1 * n2 + w.k2) * SFnh;
-    const size_t colm = ((size_t)((n1 - w.k1) % n1) * n2 + (n2 - w.k2) % n2) * SFnh;
-
     constexpr int NF = PAR ? 1 : HC;
-    float2 F[NF];           // class mode: F(H3) accumulated over the classes
-    float2 DE[N + 1], DO[N + 1];   // parity mode: coefficient sets of even / odd H3
-    for (int m = 0; m < P.M; ++m) {
+    float2 F[NF];
+    float2 DE[N + 1], DO[N + 1];
+
+    const size_t cstride = (size_t)n1 * n2 * SFnh;              // between configurations
+    const size_t col = ((size_t)k1 * n2 + k2) * SFnh;
+    const size_t colm = ((size_t)(k1 ? n1 - k1 : 0) * n2 + (k2 ? n2 - k2 : 0)) * SFnh;
+    const int lane = threadIdx.x & 63, nwv = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // the spectra of one configuration as a buffer (an offset past its records reads 0), where
+    // 31-bit byte offsets reach them
+    const bool far = cstride >= (1u << 28);
+    for (int m0 = 0; m0 < P.M; m0 += mg) {
+        const int mc = MULTI ? min(mg, P.M - m0) : 1;
 #pragma unroll
         for (int h = 0; h < NF; ++h) F[h] = make_float2(0.f, 0.f);
 #pragma unroll
         for (int r = 0; r <= N; ++r) { DE[r] = make_float2(0.f, 0.f); DO[r] = make_float2(0.f, 0.f); }
-        const float2* Xm = P.X + (size_t)m * n1 * n2 * SFnh;
-        for (int sc = 0; sc < P.nsc; ++sc) {
-            const int s0 = P.sc_start[sc], s1 = P.sc_start[sc + 1];
-            const int ns = s1 - s0;
-            // level A: stages (site, half); the next stage's spectra are loaded into
-            // registers while the current stage is contracted from LDS
-            const int nhalf = (n3 - nh > 0) ? 2 : 1;
-            const int nst = ns * nhalf;
-            const int stot = P.F * nh;
-            constexpr int PF = (MULTI || (PAR && N >= 6)) ? 1 : 6;
-            float2 pf[PF];
-            auto stage_src = [&](int st) {
-                const int mu = P.site_of[s0 + st / nhalf];
-                return Xm + ((st % nhalf) ? colm : col) + (size_t)mu * P.F * nh;
-            };
-            auto prefetch = [&](const float2* src) {
-#pragma unroll
-                for (int u = 0; u < PF; ++u) {
-                    const int i = threadIdx.x + u * blockDim.x;
-                    if (i < stot) pf[u] = src[i];
-                }
-            };
-            prefetch(stage_src(0));
-            for (int st = 0; st < nst; ++st) {
-                const int sl = st / nhalf, half = st % nhalf;
+        for (int s0 = 0; s0 < S; s0 += P.csites) {
+            const int ns = min(P.csites, S - s0);
+            __syncthreads();                 // Bs has been read (and, first, the tables are written)
+            // level A: waves of 64 items (site, pair, k3), k3 fastest, of one configuration
+            const int nitemA = ns * QR * k3n, wpm = (nitemA + 63) >> 6;
+            for (int c = wave; c < mc * wpm; c += nwv) {
+                const int mi = MULTI ? __builtin_amdgcn_readfirstlane(qdiv_r(c, wpm, 1.f / (float)wpm)) : 0;
+                const float2* Xm = P.X + (size_t)(m0 + mi) * cstride;
+                const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<float2*>(Xm), (short)0, (int)(uint32_t)(far ? 0 : cstride * sizeof(float2)), kBufferFlags);
+                const int g = (c - mi * wpm) * 64 + lane;
+                const bool ok = g < nitemA;
+                const int gg = ok ? g : nitemA - 1;
+                const int sj = qdiv_r(gg, k3n, rk), kk0 = gg - sj * k3n;
+                const int sl = sj / QR, j = sj - sl * QR;
+                int kk = P.ks3 + t0 + kk0;
+                kk -= kk >= n3 ? n3 : 0;
                 const int mu = P.site_of[s0 + sl];
-                const float2 wbase = P.tab1[(size_t)mu * P.cnt[0] + w.i1];
-                const int k3lo = half ? nh : 0;
-                const int nk = half ? n3 - nh : nh;
-                __syncthreads();
-#pragma unroll
-                for (int u = 0; u < PF; ++u) {
-                    const int i = threadIdx.x + u * blockDim.x;
-                    if (i < stot) Xs[i] = pf[u];
-                }
-                if (stot > PF * (int)blockDim.x)       // large spectra: the rest in batches
-                    stage_copy(Xs + PF * blockDim.x, stage_src(st) + PF * blockDim.x, stot - PF * blockDim.x);
-                if (st + 1 < nst) prefetch(stage_src(st + 1));
-                __syncthreads();
-                const float sg = half ? -1.f : 1.f;
-                for (int idx = threadIdx.x; idx < QR * nk; idx += blockDim.x) {
-                    const int j = idx / nk;
-                    const int kk = k3lo + (idx - j * nk);
-                    const int e = jtab[0][j];
-                    const int f0 = jtab[1][j];           // field of p = 0 (may be -1)
-                    const float2* xs = Xs + f0 * nh + (half ? n3 - kk : kk);
-                    // sum_p wbase (i tau1)^p / p! x_p = wbase (E + i O): E, O sum the even and odd
-                    // p-terms with the real weights tau1^p / p! times the sign of i^p's nonzero
-                    // part; the mirror sign of x's imaginary part is applied to the sums
-                    float2 E = make_float2(0.f, 0.f), O = E;
-                    float mag = 1.f;
+                const int pc = jtab[0][j], f0 = jtab[1][j];
+                const bool half = kk >= nh;                     // conj X(-k) from the mirrored column
+                const size_t o = (half ? colm : col) + (size_t)(mu * P.F) * nh + (half ? n3 - kk : kk);
+                // the p-terms every lane of the wave may need: pairs run in order of e = q + r,
+                // so a wave within one site needs those of its first lane
+                const int sl0 = __builtin_amdgcn_readfirstlane(sl);
+                const bool one = __ballot(sl == sl0) == ~0ull;
+                const int pmax = one ? __builtin_amdgcn_readfirstlane(pc) : N + 1;
+                float2 E0 = make_float2(0.f, 0.f), O0 = E0, E1 = E0, O1 = E0;
+                float2 x[N + 1];
+                if (!far) {
 #pragma unroll
                     for (int p = 0; p <= N; ++p) {
-                        if (p <= N - e) {
-                            if (f0 + p >= 0) {
-                                const float2 x = xs[p * nh];
-                                const float c = ((p & 3) < 2) ? mag : -mag;
-                                if (p & 1) { O.x = fmaf(c, x.x, O.x); O.y = fmaf(c, x.y, O.y); }
-                                else { E.x = fmaf(c, x.x, E.x); E.y = fmaf(c, x.y, E.y); }
-                            }
-                            mag *= tau1 * (1.f / (float)(p + 1));
+                        const uint32_t vo = (p < pc && f0 + p >= 0) ? 8u * (uint32_t)o + 8u * (uint32_t)((f0 + p) * nh) : kNoRecord;
+                        x[p] = make_float2(0.f, 0.f);
+                        if (p < pmax) x[p] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rx, vo, 0, 0));
+                    }
+                } else {
+#pragma unroll
+                    for (int p = 0; p <= N; ++p)
+                        x[p] = (p < pc && f0 + p >= 0) ? Xm[o + (size_t)((f0 + p) * nh)] : make_float2(0.f, 0.f);
+                }
+                const float2 kf = P.tabK3[(size_t)mu * n3 + kk];
+#pragma unroll
+                for (int p = 0; p <= N; ++p) {
+                    if (p < pmax) {
+                        const float w0 = cm[p], w1 = npl == 2 ? cm[N + 1 + p] : 0.f;
+                        if (p & 1) {
+                            O0.x = fmaf(w0, x[p].x, O0.x); O0.y = fmaf(w0, x[p].y, O0.y);
+                            O1.x = fmaf(w1, x[p].x, O1.x); O1.y = fmaf(w1, x[p].y, O1.y);
+                        } else {
+                            E0.x = fmaf(w0, x[p].x, E0.x); E0.y = fmaf(w0, x[p].y, E0.y);
+                            E1.x = fmaf(w1, x[p].x, E1.x); E1.y = fmaf(w1, x[p].y, E1.y);
                         }
                     }
-                    E.y *= sg;
-                    O.y *= sg;
-                    Bs[((size_t)sl * n3 + kk) * QR + j] = cmulf(wbase, make_float2(E.x - O.y, E.y + O.x));
+                }
+                // sum_p b e^{2 pi i g1 r1} (i tau1)^p / p! X_p = wb (E + i O), conj X on the mirrored half
+                if (ok) {
+                    const float sg = half ? -1.f : 1.f, fr = jfr[j];
+                    const float2 kr = make_float2(kf.x * fr, kf.y * fr);
+                    float2* b = Bs + (((size_t)mi * npl * P.csites + sl) * n3s + kk0) * QP + j;
+                    b[0] = cmulf(cmulf(wbt[s0 + sl], kr), make_float2(fmaf(-sg, O0.y, E0.x), fmaf(sg, E0.y, O0.x)));
+                    if (npl == 2)
+                        b[P.bs_elems] = cmulf(cmulf(wbt[S + s0 + sl], kr), make_float2(fmaf(-sg, O1.y, E1.x), fmaf(sg, E1.y, O1.x)));
                 }
             }
             __syncthreads();
-            // level B (+ level C in class mode)
-            if (active) {
+            // levels B and C of the thread's plane and configuration
+            if (active && gm < mc) {
+                const float2* const B0 = Bs + (size_t)(gm * npl + sel) * P.bs_elems + (size_t)kl * QP;
+                const float2* const t2r = t2 + row * S;
                 int sp = s0;
-                while (sp < s1) {
-                    const int c = P.class_of[sp];
-                    int se = sp + 1;
-                    while (se < s1 && P.class_of[se] == c) ++se;
+                for (int c = P.class_of[s0]; sp < s0 + ns; ++c) {
+                    const int se = min(P.class_start[c + 1], s0 + ns);
+                    const float sgn_odd = PAR ? (float)P.class_sign[c] : 1.f;
                     float2 D[PAR ? 1 : N + 1];
                     if constexpr (!PAR) {
 #pragma unroll
                         for (int r = 0; r <= N; ++r) D[r] = make_float2(0.f, 0.f);
                     }
-                    const float sgn_odd = PAR ? (float)P.class_sign[c] : 1.f;
-                    for (int sl = sp - s0; sl < se - s0; ++sl) {
-                        const int mu = P.site_of[s0 + sl];
-                        const float2 ph = cmulf(P.tab2[(size_t)mu * P.cnt[1] + i2],
-                                                P.tabK3[(size_t)mu * n3 + k3]);
-                        const float2* Bp = Bs + ((size_t)sl * n3 + k3) * QR;
+#pragma unroll (N == 0 ? 4 : 1)
+                    for (int s = sp; s < se; ++s) {
+                        const float2 ph = t2r[s];
+                        const float2* Bp = B0 + (size_t)(s - s0) * n3s * QP;
 #pragma unroll
                         for (int r = 0; r <= N; ++r) {
-                            float2 C = make_float2(0.f, 0.f);
+                            float2 C = Bp[pair_index(0, r)];          // q = 0: a2[0] = 1
 #pragma unroll
-                            for (int q = 0; q + r <= N; ++q) {
+                            for (int q = 1; q + r <= N; ++q) {
                                 const float2 v = Bp[pair_index(q, r)];
                                 const float a = a2[q];
                                 // C += i^q a v
@@ -417,18 +467,18 @@ __device__ __forceinline__ void recombine_nuclear_body(PT P, const int bx)
                                 else if ((q & 3) == 2) { C.x -= a * v.x; C.y -= a * v.y; }
                                 else { C.x += a * v.y; C.y -= a * v.x; }
                             }
-                            const float2 pc = cmulf(ph, C);
                             if constexpr (PAR) {
-                                DE[r].x += pc.x * inv_factorial(r);
-                                DE[r].y += pc.y * inv_factorial(r);
-                                DO[r].x += sgn_odd * pc.x * inv_factorial(r);
-                                DO[r].y += sgn_odd * pc.y * inv_factorial(r);
+                                const float2 pcv = cmulf(ph, C);
+                                DE[r].x += pcv.x;
+                                DE[r].y += pcv.y;
+                                DO[r].x = fmaf(sgn_odd, pcv.x, DO[r].x);
+                                DO[r].y = fmaf(sgn_odd, pcv.y, DO[r].y);
                             } else {
-                                D[r].x += pc.x * inv_factorial(r);
-                                D[r].y += pc.y * inv_factorial(r);
+                                D[r].x = fmaf(ph.x, C.x, fmaf(-ph.y, C.y, D[r].x));
+                                D[r].y = fmaf(ph.x, C.y, fmaf(ph.y, C.x, D[r].y));
                             }
                             // keep the coefficient loads of one r at a time in registers
-                            __builtin_amdgcn_sched_barrier(0);
+                            if constexpr (N > 2) __builtin_amdgcn_sched_barrier(0);
                         }
                     }
                     if constexpr (!PAR) {
@@ -459,36 +509,60 @@ __device__ __forceinline__ void recombine_nuclear_body(PT P, const int bx)
                 }
             }
         }
-        if constexpr (PAR && MULTI) {
-            parity_order<N>(DE, DO, H3lo + hbeg);
+        if constexpr (MULTI) {
+            if (gm < mc) {
+                if constexpr (PAR) {
+                    parity_order<N>(DE, DO, H3lo + hbeg);
 #pragma unroll
-            for (int h = 0; h < HC; ++h)
-                if (h < hmin || h < hcnt) I[h] += parity_eval<N>((h & 1) ? DO : DE, t3base + (float)h * dt3);
-        } else if constexpr (MULTI) {
+                    for (int h = 0; h < HC; ++h)
+                        if (h < hmin || h < hcnt) I[h] += parity_eval<N>((h & 1) ? DO : DE, t3base + (float)h * dt3);
+                } else {
 #pragma unroll
-            for (int h = 0; h < HC; ++h) I[h] += F[h].x * F[h].x + F[h].y * F[h].y;
+                    for (int h = 0; h < HC; ++h) I[h] += F[h].x * F[h].x + F[h].y * F[h].y;
+                }
+            }
         }
     }
+    if constexpr (MULTI) {
+        if (mg > 1) {
+            // the groups' sums, in order, through LDS: [mg - 1][HC][npl bh]
+            float* red = reinterpret_cast<float*>(smem);
+            const int w = npl * bh, at = sel * bh + item;
+            __syncthreads();
+            if (gm > 0) {
+#pragma unroll
+                for (int h = 0; h < HC; ++h) red[((gm - 1) * HC + h) * w + at] = I[h];
+            }
+            __syncthreads();
+            if (gm > 0) return;
+            for (int g = 0; g < mg - 1; ++g) {
+#pragma unroll
+                for (int h = 0; h < HC; ++h) I[h] += red[(g * HC + h) * w + at];
+            }
+        }
+    }
+    BlockWork w;
+    w.i1 = G1 - P.g0[0];
     const int i3b = k3 + n3 * (H3lo + hbeg) - P.g0[2];       // output index of h = 0
     const RowOut ro = row_out(P, w, i2, i3b);
-    const bool full = wave_min_uniform(active ? 1 : 0) != 0;
+    const bool full = __ballot(active) == ~0ull;
     if constexpr (PAR && !MULTI) parity_order<N>(DE, DO, H3lo + hbeg);
     auto val = [&](int h) -> float {
         if constexpr (MULTI) return I[h];
         else if constexpr (PAR) return parity_eval<N>((h & 1) ? DO : DE, t3base + (float)h * dt3);
         else return F[h].x * F[h].x + F[h].y * F[h].y;
     };
-    if (w.mirror) write_row<HC, true>(ro, full, active, hmin, hcnt, P.scale, val);
+    if (mirror) write_row<HC, true>(ro, full, active, hmin, hcnt, P.scale, val);
     else write_row<HC, false>(ro, full, active, hmin, hcnt, P.scale, val);
 }
 
 template <int N, int HC, bool MULTI, bool PAR>
-__global__ __launch_bounds__(512, 4) void k_recombine_nuclear(RecombParams P) { recombine_nuclear_body<N, HC, MULTI, PAR, RecombParams>(P, blockIdx.x); }
+__global__ __launch_bounds__(512, 4) void k_recombine_sites(RecombParams P) { recombine_sites_body<N, HC, MULTI, PAR, RecombParams>(P, blockIdx.x); }
 template <int N, int HC, bool MULTI, bool PAR>
-__global__ __launch_bounds__(512, 4) void k_recombine_nuclear_merged(const RecombParams* __restrict__ tab, const Slot* __restrict__ slots)
+__global__ __launch_bounds__(512, 4) void k_recombine_sites_merged(const RecombParams* __restrict__ tab, const Slot* __restrict__ slots)
 {
     int d, bx;
-    if (slot_of(slots, d, bx)) recombine_nuclear_body<N, HC, MULTI, PAR, const RecombParams&>(tab[d], bx);
+    if (slot_of(slots, d, bx)) recombine_sites_body<N, HC, MULTI, PAR, const RecombParams&>(tab[d], bx);
 }
 
 // Folded form (every r_mu2 a multiple of 1/2; see the top of the file).  A block
@@ -858,9 +932,10 @@ static hipError_t set_lds(K kernel, size_t lds)
 template <int N, int HC, bool MULTI, bool PAR>
 static hipError_t launch_nuc_v(const RecombParams& p, int block, size_t lds, hipStream_t st)
 {
-    hipError_t e = set_lds(k_recombine_nuclear<N, HC, MULTI, PAR>, lds);
+    if (block != p.npl * (MULTI ? p.mg : 1) * p.gthreads || block > 512 || p.gthreads % 64) return hipErrorInvalidValue;
+    hipError_t e = set_lds(k_recombine_sites<N, HC, MULTI, PAR>, lds);
     if (e != hipSuccess) return e;
-    return dispatch(k_recombine_nuclear<N, HC, MULTI, PAR>, k_recombine_nuclear_merged<N, HC, MULTI, PAR>, p.nwork,
+    return dispatch(k_recombine_sites<N, HC, MULTI, PAR>, k_recombine_sites_merged<N, HC, MULTI, PAR>, p.nwork,
                     block, lds, st, p);
 }
 

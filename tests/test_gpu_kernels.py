@@ -47,3 +47,42 @@ def test_plane_rows_route_of_two_factor_edges():
     m.g0, m.count = (-2, -9, -9), (5, 19, 19)
     say(f"row route n={m.n}")
     sampled_parity(m, 1, 1500)
+
+
+# ------------------------------------------------------------------ recombination, sites form
+def sites_model(seed, n, S, M, order, r3=None, ff=False, occ=True):
+    m = synth.random_model(seed, n=n, S=S, M=M, order=order, with_occ=occ or order == 0, with_disp=order > 0, sigma=0.03)
+    if r3 is not None:
+        m.frac[:, 2] = np.asarray(r3)[np.arange(S) % len(r3)]
+    if ff:
+        m.ff = np.tile(synth.MAG_FF, (S, 1))
+        m.ff[:, 6] = 0.2 + 0.1 * (np.arange(S) % 2)
+    return m
+
+
+@pytest.mark.parametrize("S,M,order,r3", [(1, 3, 2, None), (5, 1, 0, None), (33, 2, 0, None), (7, 40, 0, (0.1, 0.6, 0.1)),
+                                          (3, 9, 4, (0.0, 0.5)), (4, 2, 8, (0.25, 0.3)), (64, 1, 1, None), (2, 5, 11, None)])
+@pytest.mark.parametrize("box", ["symmetric", "plane1", "plane2", "plane3", "thin3", "offset"])
+def test_sites_form(S, M, order, r3, box):
+    """Configurations side by side, site chunks, shared and separate r3 classes, parity sets, and
+    boxes with one plane per axis, fewer G3 than the supercell has k3, or none symmetric."""
+    n = (4, 3, 5) if order > 8 else (5, 4, 18)
+    m = sites_model(2000 + S + M + order, n, S, M, order, r3)
+    lim = {"symmetric": [(-n[a] - 1, 2 * n[a] + 3) for a in range(3)], "offset": [(-3, n[0] + 2), (1, n[1] + 3), (-n[2] - 4, 2 * n[2] + 1)]}
+    full = [(-n[a] - 2, 2 * n[a] + 4) for a in range(3)]
+    for a in range(3):
+        lim[f"plane{a + 1}"] = full[:a] + [(n[a] + 1, 1)] + full[a + 1:]
+    lim["thin3"] = full[:2] + [(n[2] - 2, 4)]
+    m.g0, m.count = tuple(v[0] for v in lim[box]), tuple(v[1] for v in lim[box])
+    say(f"sites form S={S} M={M} order={order} box={m.g0}+{m.count}")
+    sampled_parity(m, order if order else None, 1500)
+
+
+@pytest.mark.parametrize("n3,M", [(15, 1), (16, 7), (47, 2), (64, 1)])
+def test_sites_form_scattering_factors(n3, M):
+    """Slices of k3 (n3 >= 16) with |Q|-dependent factors in the class form."""
+    m = sites_model(2200 + n3, (3, 4, n3), 4, M, 3, (0.2, 0.7), ff=True)
+    m.cell = np.array([5.0, 6.0, 7.0, 90.0, 97.0, 90.0])
+    m.g0, m.count = (-4, -5, -n3 - 3), (9, 11, 2 * n3 + 7)
+    say(f"sites form with factors n={m.n} M={M}")
+    sampled_parity(m, 3, 1500)
