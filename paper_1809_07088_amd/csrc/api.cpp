@@ -286,6 +286,9 @@ struct DeviceTables {
     int ks3 = 0, nact3 = 0;    // the k3 with points in the box: nact3 of them, cyclically from ks3
     int4* work_mr = nullptr;   // magnetic models: blocks of the row-staged form (null: not used)
     int nwork_mr = 0, rows_mr = 0, csites_mr = 0, qmod_mr = 0, qmod2_mr = 0, qmod1_mr = 0;
+    // the lists in column order (before they are dealt to the XCDs), to cut them down to the
+    // rows a point list needs
+    std::vector<int4> h_work, h_work2, h_work3, h_work_s, h_work_mr;
 };
 
 // Releases every device buffer of one cached box.
@@ -294,6 +297,63 @@ void free_tables(DeviceTables& t)
     dfree(t.tab1); dfree(t.tab2); dfree(t.tabK2); dfree(t.tabK3); dfree(t.tabH3);
     dfree(t.work_s); dfree(t.work); dfree(t.work2); dfree(t.work3); dfree(t.k3tab); dfree(t.work_mr);
     t = DeviceTables{};
+}
+
+// Rows (G1, G2) of a box that are needed.
+struct RowMask {
+    int lo[2], cnt[2];
+    std::vector<unsigned char> need;   // [cnt0][cnt1]
+    bool at(long G1, long G2) const
+    {
+        const long a = G1 - lo[0], b = G2 - lo[1];
+        return a >= 0 && b >= 0 && a < cnt[0] && b < cnt[1] && need[(size_t)a * cnt[1] + b] != 0;
+    }
+};
+
+// Blocks are dealt round-robin to the 8 XCDs: XCD x runs the x-th contiguous eighth of the
+// list, in which the blocks of a column and of its mirror are adjacent.
+std::vector<int4> xcd_order(const std::vector<int4>& its)
+{
+    const size_t per = (its.size() + 7) / 8;
+    std::vector<int4> wl(8 * per, make_int4(-1, 0, 0, 0));
+    for (size_t b = 0; b < wl.size(); ++b) {
+        const size_t L = (b % 8) * per + b / 8;
+        if (L < its.size()) wl[b] = its[L];
+    }
+    return wl;
+}
+
+// A work list cut down to the rows of `mask`: items without one are dropped, the others keep
+// the span of their rows that has them.  A mirrored plane's rows serve -G too.  `step` is the
+// distance of an item's planes in G1, `planes` says how its word counts them (1: one plane;
+// 2: a second one by bit 25; 0: bits 28-29).  *rows: the most rows an item keeps.
+std::vector<int4> prune_work(const std::vector<int4>& its, const Box& bx, int n2, int step, int planes, const RowMask& mask,
+                             int* rows)
+{
+    std::vector<int4> out;
+    *rows = 1;
+    for (int4 it : its) {
+        const int h2a = it.w & 0xfff, h2b = (it.w >> 12) & 0xfff;
+        const long H2lo = ceildiv_l((long)bx.g0[1] - it.y, n2);
+        const int np = planes == 1 ? 1 : planes == 2 ? 1 + ((it.w >> 25) & 1) : 1 + ((it.w >> 28) & 3);
+        int a = h2b, b = h2a;
+        for (int p = 0; p < np; ++p) {
+            const long G1 = it.z + (long)p * step;
+            const bool mir = (it.w >> (planes == 2 ? 24 + 2 * p : 24 + p)) & 1;
+            for (int h = h2a; h < h2b; ++h) {
+                const long G2 = it.y + (long)n2 * (H2lo + h);
+                if (mask.at(G1, G2) || (mir && mask.at(-G1, -G2))) {
+                    a = std::min(a, h);
+                    b = std::max(b, h + 1);
+                }
+            }
+        }
+        if (a >= b) continue;
+        it.w = (it.w & ~0xffffff) | a | (b << 12);
+        *rows = std::max(*rows, b - a);
+        out.push_back(it);
+    }
+    return out;
 }
 
 struct LaunchPlan {
@@ -341,6 +401,7 @@ struct dsx_model_s {
     float* d_ext = nullptr;   size_t ext_cap = 0;
     float* d_pts = nullptr;   size_t pts_cap = 0;   // I(G) on the box of a point list's windows
     double* d_q = nullptr;    size_t q_cap = 0;     // the point list
+    int4* d_pwork = nullptr;  size_t pwork_cap = 0; // the work list cut down to the points' rows
     float* d_stage = nullptr; size_t stage_cap = 0;
     std::map<Box, DeviceTables> tables;
     std::map<std::tuple<int, int, int>, float*> lanczos_w;   // (m, m', s) -> weights
@@ -476,7 +537,7 @@ void free_model(dsx_model m)
     dfree(m->d_dsp); dfree(m->d_dwsums); dfree(m->d_dwc);
     dfree(m->d_site);
     for (auto& t : m->d_tw) dfree(t);
-    dfree(m->d_ext); dfree(m->d_stage); dfree(m->d_pts); dfree(m->d_q);
+    dfree(m->d_ext); dfree(m->d_stage); dfree(m->d_pts); dfree(m->d_q); dfree(m->d_pwork);
     for (auto& kv : m->tables) free_tables(kv.second);
     for (auto& kv : m->lanczos_w) dfree(kv.second);
     if (m->order_ev) (void)hipEventDestroy(m->order_ev);
@@ -492,6 +553,15 @@ dsx_status follow(dsx_model m, hipStream_t st)
     }
     m->last_stream = st;
     return DSX_OK;
+}
+
+// Configurations a block of the sites form takes side by side: what 512 threads and 64 KB of
+// level-A buffers hold (bs float2 elements a plane and configuration).
+int sites_configs(int M, int npl, int gthreads, int bs)
+{
+    int mg = std::max(1, std::min(M, 512 / (npl * gthreads)));
+    while (mg > 1 && (size_t)mg * npl * bs * sizeof(float2) > 64 * 1024) --mg;
+    return mg;
 }
 
 // Block shape of the sites form on a box (t.hc, t.nchunk3, t.nact3 are set): two planes per
@@ -526,12 +596,7 @@ void plan_sites_form(dsx_model m, const Box& bx, int maxH2, DeviceTables& t)
     t.rows_s = (std::max(1, maxH2) + parts - 1) / parts;
     const int maxg = 512 / t.npl_s / 64 * 64;
     t.gthreads_s = std::min(maxg, (t.rows_s * per_row + 63) / 64 * 64);
-    t.mg_s = 1;
-    if (m->M > 1) {
-        const size_t one = per_site(t.npl_s, t.n3s_s) * t.csites_s;
-        t.mg_s = std::max(1, std::min(m->M, 512 / (t.npl_s * t.gthreads_s)));
-        while (t.mg_s > 1 && t.mg_s * one > 64 * 1024) --t.mg_s;
-    }
+    t.mg_s = m->M > 1 ? sites_configs(m->M, t.npl_s, t.gthreads_s, t.csites_s * t.n3s_s * qp) : 1;
 }
 
 dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
@@ -766,21 +831,18 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
             }
         }
     }
-    // blocks are dealt round-robin to the 8 XCDs: XCD x runs the x-th contiguous eighth
-    // of the list, in which the blocks of a column and of its mirror are adjacent
-    auto xcd_order = [](std::vector<std::pair<long long, int4>>& its) {
+    auto sorted = [](std::vector<std::pair<long long, int4>>& its) {
         std::stable_sort(its.begin(), its.end(),
                          [](const std::pair<long long, int4>& x, const std::pair<long long, int4>& y) { return x.first < y.first; });
-        const size_t per = (its.size() + 7) / 8;
-        std::vector<int4> wl(8 * per, make_int4(-1, 0, 0, 0));
-        for (size_t b = 0; b < wl.size(); ++b) {
-            const size_t L = (b % 8) * per + b / 8;
-            if (L < its.size()) wl[b] = its[L].second;
-        }
-        return wl;
+        std::vector<int4> v;
+        v.reserve(its.size());
+        for (const auto& x : its) v.push_back(x.second);
+        return v;
     };
-    const std::vector<int4> work = xcd_order(items), work2 = xcd_order(items2), work3 = xcd_order(items3);
-    const std::vector<int4> work_mr = xcd_order(items_mr), work_s = xcd_order(items_s);
+    t.h_work = sorted(items); t.h_work2 = sorted(items2); t.h_work3 = sorted(items3);
+    t.h_work_mr = sorted(items_mr); t.h_work_s = sorted(items_s);
+    const std::vector<int4> work = xcd_order(t.h_work), work2 = xcd_order(t.h_work2), work3 = xcd_order(t.h_work3);
+    const std::vector<int4> work_mr = xcd_order(t.h_work_mr), work_s = xcd_order(t.h_work_s);
     t.nwork_s = (int)work_s.size();
     t.nwork_mr = (int)work_mr.size();
     t.nwork = (int)work.size();
@@ -851,6 +913,15 @@ Layout dense_layout(const Box& b) { return Layout{b.cnt[2], 0}; }
 bool direct_form_applies(dsx_model m)
 {
     return m->kind == DSX_NUCLEAR && m->order == 0 && m->F == 1 && !m->has_ff;
+}
+
+// LDS of the sites form (the groups' sums at the end take the place of the level-A buffer).
+size_t sites_lds(dsx_model m, const RecombParams& p, int hc)
+{
+    const bool par = p.parity && p.variant != 2;
+    const size_t lds = sizeof(float2) * sites_lds_elems(p.npl, p.mg, p.csites, p.n3s, m->order, m->S, p.rows,
+                                                        par ? 0 : m->nclass * p.nH3span);
+    return p.mg > 1 ? std::max(lds, sizeof(float) * (size_t)(p.mg - 1) * hc * p.npl * p.gthreads) : lds;
 }
 
 dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& lay, LaunchPlan& lp)
@@ -957,11 +1028,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         const bool multi = m->M > 1 || p.variant == 1;
         if (!multi) p.mg = 1;
         lp.block = p.npl * p.mg * p.gthreads;
-        const bool par = p.parity && p.variant != 2;
-        lp.lds = sizeof(float2) * sites_lds_elems(p.npl, p.mg, p.csites, p.n3s, m->order, m->S, p.rows,
-                                                  par ? 0 : m->nclass * tb->nH3span);
-        // the groups' sums at the end
-        if (p.mg > 1) lp.lds = std::max(lp.lds, sizeof(float) * (size_t)(p.mg - 1) * lp.hc * p.npl * p.gthreads);
+        lp.lds = sites_lds(m, p, lp.hc);
     }
     // direct form: asked for, or by default where the levelled forms would spend their
     // blocks on set-up (one or two sites x configurations)
@@ -1194,11 +1261,52 @@ dsx_status ensure_spectra(dsx_model m, hipStream_t st, bool force = false)
     return DSX_OK;
 }
 
-dsx_status run_box(dsx_model m, const Box& bx, float* dout, const Layout& lay, hipStream_t st)
+// Cut the plan's work list down to the rows of `mask` and put it in the model's own list
+// (uploaded on st; `list` holds it until the caller has waited for the stream).
+dsx_status prune_plan(dsx_model m, const Box& bx, const RowMask& mask, LaunchPlan& lp, hipStream_t st, std::vector<int4>& list)
+{
+    DeviceTables* tb = nullptr;
+    dsx_status s = tables_for(m, bx, &tb);
+    if (s != DSX_OK) return s;
+    RecombParams& p = lp.rp;
+    const bool sites = p.work == tb->work_s, mr = lp.mag_rows;
+    const std::vector<int4>& full = sites ? tb->h_work_s : mr ? tb->h_work_mr : p.work == tb->work3 ? tb->h_work3
+                                  : p.work == tb->work2 ? tb->h_work2 : tb->h_work;
+    const bool pairs = sites ? p.npl == 2 : p.fold != 0;
+    int rows = 1;
+    list = xcd_order(prune_work(full, bx, m->n[1], mr ? p.qmod1 * m->n[0] : m->n[0], mr ? 0 : pairs ? 2 : 1, mask, &rows));
+    if (m->pwork_cap < list.size()) {
+        dfree(m->d_pwork);
+        m->d_pwork = nullptr; m->pwork_cap = 0;
+        hipError_t e = hipMalloc(&m->d_pwork, sizeof(int4) * list.size());
+        if (e == hipErrorOutOfMemory) return fail(DSX_ERR_NOMEM, "out of device memory for the points' work list");
+        HIPCHK(m, e);
+        m->pwork_cap = list.size();
+    }
+    if (!list.empty())
+        HIPCHK(m, hipMemcpyAsync(m->d_pwork, list.data(), sizeof(int4) * list.size(), hipMemcpyHostToDevice, st));
+    p.work = m->d_pwork;
+    p.nwork = (int)list.size();
+    if (sites) {
+        // fewer rows a block: narrower groups, and more configurations side by side
+        p.rows = rows;
+        p.gthreads = std::min(p.gthreads, (rows * p.n3s * p.nchunk3 + 63) / 64 * 64);
+        p.mg = m->M > 1 ? sites_configs(m->M, p.npl, p.gthreads, p.bs_elems) : 1;
+        lp.block = p.npl * p.mg * p.gthreads;
+        lp.lds = sites_lds(m, p, lp.hc);
+    }
+    return DSX_OK;
+}
+
+// The intensity on a box; `mask`, when given, says which of its rows are needed (the others
+// may hold anything), and `list` then keeps the cut work list.
+dsx_status run_box(dsx_model m, const Box& bx, float* dout, const Layout& lay, hipStream_t st, const RowMask* mask = nullptr,
+                   std::vector<int4>* list = nullptr)
 {
     LaunchPlan lp;
     dsx_status s = plan_recombine(m, bx, dout, lay, lp);
     if (s != DSX_OK) return s;
+    if (mask && !lp.direct && (s = prune_plan(m, bx, *mask, lp, st, *list)) != DSX_OK) return s;
     if (lp.direct)
         HIPCHK(m, timed("recombine", st, [&] { return launch_recombine_direct(lp.rp, st); }));
     else if (lp.mag_rows)
@@ -2026,15 +2134,44 @@ dsx_status dsx_filter_points(dsx_model m, int32_t lanczos_m, int32_t mprime, int
         if ((s = ready(m)) != DSX_OK) return s;
         if (npts == 0) return DSX_OK;
         // the box of every window: floor(Q_a) - w + 1 .. floor(Q_a) + w
-        long lo[3] = {LONG_MAX, LONG_MAX, LONG_MAX}, hi[3] = {LONG_MIN, LONG_MIN, LONG_MIN};
+        auto floor_l = [](double v) { const long f = (long)v; return f - ((double)f > v ? 1 : 0); };
+        double vmin[3] = {1e300, 1e300, 1e300}, vmax[3] = {-1e300, -1e300, -1e300};
+        bool fine = true;
         for (int64_t i = 0; i < npts; ++i)
             for (int a = 0; a < 3; ++a) {
                 const double v = q[3 * i + a];
-                if (!std::isfinite(v) || std::fabs(v) > 1e6) return fail(DSX_ERR_ARG, "points must be finite, |Q| <= 1e6");
-                const long f = (long)std::floor(v);
-                lo[a] = std::min(lo[a], f - w + 1);
-                hi[a] = std::max(hi[a], f + w);
+                fine &= std::fabs(v) <= 1e6;        // (false for NaN)
+                vmin[a] = v < vmin[a] ? v : vmin[a];
+                vmax[a] = v > vmax[a] ? v : vmax[a];
             }
+        if (!fine) return fail(DSX_ERR_ARG, "points must be finite, |Q| <= 1e6");
+        long lo[3], hi[3];
+        for (int a = 0; a < 3; ++a) { lo[a] = floor_l(vmin[a]) - w + 1; hi[a] = floor_l(vmax[a]) + w; }
+        // the rows (G1, G2) the windows reach; on a plane or a line they are few of the box's
+        RowMask mask;
+        for (int a = 0; a < 2; ++a) { mask.lo[a] = (int)lo[a]; mask.cnt[a] = (int)(hi[a] - lo[a] + 1); }
+        bool use_mask = (long long)mask.cnt[0] * mask.cnt[1] <= (1LL << 22);
+        if (use_mask) {
+            const int c0 = mask.cnt[0], c1 = mask.cnt[1];
+            mask.need.assign((size_t)c0 * c1, 0);
+            for (int64_t i = 0; i < npts; ++i)      // the windows' first rows ...
+                mask.need[(size_t)(floor_l(q[3 * i]) - w + 1 - lo[0]) * c1 + (floor_l(q[3 * i + 1]) - w + 1 - lo[1])] = 1;
+            // ... then the 2 w of each, along axis 2 and along axis 1 (backwards: in place)
+            long long rows = 0;
+            for (int i = c0 - 1; i >= 0; --i) {
+                unsigned char* r = &mask.need[(size_t)i * c1];
+                for (int j = c1 - 1; j >= 0; --j)
+                    for (int d = 1; d < 2 * w && d <= j && !r[j]; ++d) r[j] = r[j - d];
+            }
+            for (int i = c0 - 1; i >= 0; --i)
+                for (int j = 0; j < c1; ++j) {
+                    unsigned char* r = &mask.need[(size_t)i * c1 + j];
+                    for (int d = 1; d < 2 * w && d <= i && !*r; ++d) *r = *(r - (size_t)d * c1);
+                    rows += *r;
+                }
+            // (a list of most rows is not worth the upload)
+            use_mask = rows * 4 < 3LL * c0 * c1;
+        }
         // a box nearly symmetric about G = 0 is made symmetric (at most ~10 % more volume):
         // the recombination then evaluates half of it (I(-G) = I(G))
         bool near_sym = true;
@@ -2073,9 +2210,18 @@ dsx_status dsx_filter_points(dsx_model m, int32_t lanczos_m, int32_t mprime, int
         float* dout = out;
         if (where == DSX_HOST && (s = stage(m, (size_t)npts, &dout)) != DSX_OK) return s;
         if ((s = follow(m, st)) != DSX_OK) return s;
+        // (the copy of the point list, staged by the host, comes after the launches: it then runs
+        // while the device computes)
+        std::vector<int4> cut;
+        auto wait = [&](dsx_status r) {             // `cut` and q stay alive until the copies have run
+            const std::string msg = g_err;
+            (void)hipStreamSynchronize(st);
+            g_err = msg;
+            return r;
+        };
+        if ((s = ensure_spectra(m, st, false)) != DSX_OK) return wait(s);
+        if ((s = run_box(m, bx, m->d_pts, dense_layout(bx), st, use_mask ? &mask : nullptr, &cut)) != DSX_OK) return wait(s);
         HIPCHK(m, hipMemcpyAsync(m->d_q, q, (size_t)npts * 3 * sizeof(double), hipMemcpyHostToDevice, st));
-        if ((s = ensure_spectra(m, st, false)) != DSX_OK) return s;
-        if ((s = run_box(m, bx, m->d_pts, dense_layout(bx), st)) != DSX_OK) return s;
         PointsParams pp{};
         pp.in = m->d_pts; pp.q = m->d_q; pp.out = dout; pp.npts = npts;
         for (int a = 0; a < 3; ++a) { pp.e0[a] = bx.g0[a]; pp.e[a] = bx.cnt[a]; }

@@ -86,3 +86,43 @@ def test_sites_form_scattering_factors(n3, M):
     m.g0, m.count = (-4, -5, -n3 - 3), (9, 11, 2 * n3 + 7)
     say(f"sites form with factors n={m.n} M={M}")
     sampled_parity(m, 3, 1500)
+
+
+# ------------------------------------------------------------------ points: rows of the windows only
+@pytest.mark.parametrize("shape", ["hhl", "line", "off"])
+@pytest.mark.parametrize("kind,S,M,order,basis", [("occ", 6, 20, 0, None), ("disp", 4, 1, 3, "fcc"), ("disp", 3, 2, 2, None),
+                                                  ("mag", 4, 1, 0, "fcc"), ("mag", 2, 2, 0, None), ("mag", 2, 1, 2, None)])
+def test_points_cut_work_lists(shape, kind, S, M, order, basis):
+    """Planes, lines and one-sided sets of points, whose windows reach few rows of their box: every
+    form's work list cut down to them (mirrored and paired planes among them)."""
+    import torch
+    from tests.helpers import to_dsx
+    magnetic = kind == "mag"
+    m = synth.random_model(2300 + S + M + order, n=(6, 5, 8), S=S, M=M, order=order, kind=synth.MAGNETIC if magnetic else synth.NUCLEAR,
+                           with_occ=kind == "occ", with_disp=order > 0, mag_order=order if magnetic else 0, sigma=0.03,
+                           cell=[6.0, 6.0, 6.0, 90.0, 90.0, 90.0] if magnetic else None)
+    if basis == "fcc":
+        m.frac = synth.FCC_BASIS[:S].copy()
+    t = np.linspace(-2.3, 2.3, 9)
+    h, l = (v.ravel() for v in np.meshgrid(t, t, indexing="ij"))
+    Q = {"hhl": np.stack([6 * h, 5 * h, 8 * l], -1), "line": np.stack([6 * t, 0 * t + 1.5, 8 * t], -1),
+         "off": np.stack([6 * h + 31.25, -5 * h - 20.5, 8 * l], -1)}[shape]
+    say(f"points {shape} {kind} S={S} M={M} order={order}")
+    d = to_dsx(m)
+    out = torch.full((len(Q),), float("nan"), dtype=torch.float32, device="cuda")
+    d.filter_points(2, Q, out)
+    got = out.cpu().numpy()
+    d.close()
+    assert_parity(got, O.filtered_points(m, 2, Q, order if order and not magnetic else None))
+
+
+# ------------------------------------------------------------------ Bragg points of ensembles
+@pytest.mark.parametrize("S,M,order", [(20, 64, 0), (3, 65, 0), (17, 130, 0), (2, 40, 2)])
+def test_bragg_points_of_ensembles(S, M, order):
+    """Lanes over the configurations: whole and ragged multiples of the wave, 1 to 64 sites."""
+    m = synth.random_model(2400 + S + M, n=(2, 3, 2), S=S, M=M, order=order, with_occ=True, with_disp=order > 0, sigma=0.03)
+    m.g0, m.count = (-4, -6, -4), (9, 13, 9)
+    say(f"Bragg ensemble S={S} M={M} order={order}")
+    I = gpu_intensity(m).reshape(m.count)[::2, ::3, ::2]
+    G = O.grid_points(m.g0, m.count).reshape(m.count + (3,))[::2, ::3, ::2].reshape(-1, 3)
+    assert_parity(I.reshape(-1), O.intensity(m, G, order if order else None))
