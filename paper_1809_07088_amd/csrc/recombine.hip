@@ -1911,6 +1911,108 @@ __global__ __launch_bounds__(64) void k_bragg_nuclear_merged(const BraggParams* 
     if (slot_of(slots, d, bx)) bragg_nuclear_body<N, const BraggParams&>(tab[d], bx);
 }
 
+// Ensembles: one wave per H, its lanes over the configurations.  The coefficient of every
+// (site, monomial) pair is formed once per H (in LDS), then each lane sums its configurations'
+// pairs serially, and the ensemble moments are the only wave reductions (fixed order), where
+// the form above reduces F across the wave for every configuration.  32 sites x 100
+// configurations on 13^3 points: 96 -> 18 us.
+constexpr int kBraggPairs = 1024;
+
+template <class PT>
+__device__ __forceinline__ void bragg_ensemble_body(PT P, const int bx)
+{
+#pragma clang fp contract(off)
+    __shared__ double Ar[3][kMaxOrder + 1], Ai[3][kMaxOrder + 1];
+    __shared__ double Wr[kMaxSites], Wi[kMaxSites];
+    __shared__ double Cr[kBraggPairs], Ci[kBraggPairs];
+    const int lane = threadIdx.x;
+    const int j3 = bx % P.nH[2], j2 = (bx / P.nH[2]) % P.nH[1], j1 = bx / (P.nH[2] * P.nH[1]);
+    const int H[3] = {P.Hlo[0] + j1, P.Hlo[1] + j2, P.Hlo[2] + j3};
+    const int items = P.S * P.T;
+    // (2 pi i H_a)^k / k! per axis
+    for (int t = lane; t < 3 * (kMaxOrder + 1); t += 64) {
+        const int a = t / (kMaxOrder + 1), k = t % (kMaxOrder + 1);
+        double mag = 1.0;
+        const double x = 6.283185307179586476925 * (double)H[a];
+        for (int i = 1; i <= k; ++i) mag *= x / i;
+        const int ph = k & 3;    // i^k
+        Ar[a][k] = ph == 0 ? mag : (ph == 2 ? -mag : 0.0);
+        Ai[a][k] = ph == 1 ? mag : (ph == 3 ? -mag : 0.0);
+    }
+    double s2 = 0.0;
+    if (P.has_ff) {
+        double q[3] = {0.0, 0.0, 0.0};
+        for (int a = 0; a < 3; ++a)
+            for (int c = 0; c < 3; ++c) q[c] += H[a] * P.recip[3 * a + c];
+        s2 = (q[0] * q[0] + q[1] * q[1] + q[2] * q[2]) / (16.0 * M_PI * M_PI);
+    }
+    for (int mu = lane; mu < P.S; mu += 64) {
+        const auto* sd = gptr(P.site) + 12 * mu;
+        double x = H[0] * sd[0] + H[1] * sd[1] + H[2] * sd[2];
+        x -= floor(x);
+        double sn, cs;
+        sincos(6.283185307179586476925 * x, &sn, &cs);
+        double wgt = sd[3];
+        if (P.has_ff) {
+            const auto* f = sd + 4;
+            wgt *= f[0] * exp(-f[1] * s2) + f[2] * exp(-f[3] * s2) + f[4] * exp(-f[5] * s2) + f[6];
+        }
+        Wr[mu] = wgt * cs;
+        Wi[mu] = wgt * sn;
+    }
+    __syncthreads();
+    for (int it = lane; it < items; it += 64) {
+        const int mu = it / P.T, t = it - mu * P.T;
+        const int p = P.mono[3 * t], q = P.mono[3 * t + 1], r = P.mono[3 * t + 2];
+        const double xr = Ar[0][p] * Ar[1][q] - Ai[0][p] * Ai[1][q];
+        const double xi = Ar[0][p] * Ai[1][q] + Ai[0][p] * Ar[1][q];
+        const double cr = xr * Ar[2][r] - xi * Ai[2][r], ci = xr * Ai[2][r] + xi * Ar[2][r];
+        Cr[it] = cr * Wr[mu] - ci * Wi[mu];
+        Ci[it] = cr * Wi[mu] + ci * Wr[mu];
+    }
+    __syncthreads();
+    double sq = 0.0, mre = 0.0, mim = 0.0;
+    for (int m = lane; m < P.M; m += 64) {
+        const auto* Sm = gptr(P.sums) + (size_t)m * items;
+        double fr = 0.0, fi = 0.0;
+#pragma unroll 4
+        for (int it = 0; it < items; ++it) {
+            const double sv = Sm[it];
+            fr += sv * Cr[it];
+            fi += sv * Ci[it];
+        }
+        sq += fr * fr + fi * fi;
+        mre += fr; mim += fi;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        sq += __shfl_down(sq, off, 64);
+        mre += __shfl_down(mre, off, 64);
+        mim += __shfl_down(mim, off, 64);
+    }
+    if (lane == 0) {
+        mre /= P.M; mim /= P.M;
+        const double I = (sq / P.M - (mre * mre + mim * mim)) * P.scale;
+        const int G[3] = {P.n[0] * H[0], P.n[1] * H[1], P.n[2] * H[2]};
+        gptr(P.out)[((size_t)(G[0] - P.g0[0]) * P.cnt[1] + (G[1] - P.g0[1])) * P.opitch + (G[2] - P.g0[2]) + P.ooff] = (float)I;
+    }
+}
+
+__global__ __launch_bounds__(64) void k_bragg_ensemble(BraggParams P) { bragg_ensemble_body<BraggParams>(P, blockIdx.x); }
+__global__ __launch_bounds__(64) void k_bragg_ensemble_merged(const BraggParams* __restrict__ tab, const Slot* __restrict__ slots)
+{
+    int d, bx;
+    if (slot_of(slots, d, bx)) bragg_ensemble_body<const BraggParams&>(tab[d], bx);
+}
+
+// Steps of a lane in the two forms: the ensemble form walks all pairs once per 64
+// configurations, the other one 1/64 of the pairs and a reduction (about a dozen steps' worth)
+// per configuration.
+static bool bragg_by_configs(const BraggParams& p)
+{
+    const long items = (long)p.S * p.T;
+    return items <= kBraggPairs && 2 * items * ((p.M + 63) / 64) <= (long)p.M * ((items + 63) / 64 + 12);
+}
+
 // Taylor order 0 with few sites (one field per site, the occupancy): one lane per H.  The
 // lane's site factors b_mu f(|H|) e^{2 pi i H.r_mu} are staged in its own LDS column, then
 // every configuration is summed over the sites serially, so a wave serves 64 H where the
@@ -2106,8 +2208,11 @@ hipError_t launch_bragg(const BraggParams& p, int order, hipStream_t st)
     if (p.kind == 1) {
         return dispatch(k_bragg_magnetic, k_bragg_magnetic_merged, (total + 3) / 4, 256, 0, st, p);
     }
-    if (order == 0 && p.S <= kBraggLaneSites)
+    // (one lane per H walks every configuration and site in turn, and needs some 16k points of
+    // H to fill the chip with waves)
+    if (order == 0 && p.S <= kBraggLaneSites && (total >= 16384 || !bragg_by_configs(p)))
         return dispatch(k_bragg_lanes, k_bragg_lanes_merged, (total + 63) / 64, 64, 0, st, p);
+    if (bragg_by_configs(p)) return dispatch(k_bragg_ensemble, k_bragg_ensemble_merged, total, 64, 0, st, p);
     switch (order) {
         case 0: return launch_bragg_t<0>(p, grid, st);
         case 1: return launch_bragg_t<1>(p, grid, st);
