@@ -210,10 +210,19 @@ def _ptr_out(a, nelem=None):
     return ptr, where
 
 
+def _current_stream():
+    """The handle of torch's current stream (read from its raw form where torch has one: the
+    Stream object costs several microseconds a call)."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch._C._cuda_getDevice())
+
+
 def _stream_handle(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -479,17 +488,23 @@ class Model:
         self.handle = create_model(**kw)
         self.g0 = self.count = None
 
+    _sizes = None
+
     def _site_sizes(self):
-        kw = self.desc_kw
-        n = [int(v) for v in kw["n"]]
-        S = np.asarray(kw["frac"]).reshape(-1, 3).shape[0]
-        per = S * n[0] * n[1] * n[2]
-        return (per, 3 * per, 3 * per)
+        """Elements of one configuration's occupancies, displacements and spins (the
+        description is fixed, so they are worked out once)."""
+        if self._sizes is None:
+            n = [int(v) for v in self.desc_kw["n"]]
+            S = np.asarray(self.desc_kw["frac"]).reshape(-1, 3).shape[0]
+            per = S * n[0] * n[1] * n[2]
+            self._sizes = (per, 3 * per, 3 * per)
+        return self._sizes
 
     def _box_voxels(self, s=1):
         if self.count is None:
             return None          # the library reports the missing grid
-        return int(np.prod([s * int(c) for c in self.count]))
+        c = self.count
+        return s * s * s * c[0] * c[1] * c[2]
 
     def set_sites(self, config, occ=None, disp=None, spin=None):
         set_sites(self.handle, config, occ, disp, spin, sizes=self._site_sizes())

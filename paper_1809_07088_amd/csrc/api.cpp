@@ -267,6 +267,7 @@ float2 cis(double x)   // e^{2 pi i x}, argument reduced mod 1 in float64 first
 }
 
 struct DeviceTables {
+    unsigned char* mem = nullptr;   // the device memory of all the arrays below
     float2* tab1 = nullptr;
     float2* tab2 = nullptr;
     float2* tabK2 = nullptr;
@@ -294,8 +295,7 @@ struct DeviceTables {
 // Releases every device buffer of one cached box.
 void free_tables(DeviceTables& t)
 {
-    dfree(t.tab1); dfree(t.tab2); dfree(t.tabK2); dfree(t.tabK3); dfree(t.tabH3);
-    dfree(t.work_s); dfree(t.work); dfree(t.work2); dfree(t.work3); dfree(t.k3tab); dfree(t.work_mr);
+    dfree(t.mem);
     t = DeviceTables{};
 }
 
@@ -555,6 +555,19 @@ dsx_status follow(dsx_model m, hipStream_t st)
     return DSX_OK;
 }
 
+// The folded form: every r_mu2 a multiple of 1/2 (exactly, as given), fewer r3 classes than
+// sites, and spectra of one configuration within 31-bit byte offsets.
+bool fold_applies(dsx_model m)
+{
+    if (m->kind == DSX_MAGNETIC || m->has_ff || m->nclass >= m->S || m->order > kMaxOrderFast) return false;
+    if ((unsigned long long)m->n[0] * m->n[1] * m->SF * m->nh * sizeof(float2) >= (1ULL << 31)) return false;
+    for (int i = 0; i < m->S; ++i) {
+        const double t2 = 2.0 * m->frac[3 * i + 1];
+        if (t2 != std::floor(t2)) return false;
+    }
+    return true;
+}
+
 // Configurations a block of the sites form takes side by side: what 512 threads and 64 KB of
 // level-A buffers hold (bs float2 elements a plane and configuration).
 int sites_configs(int M, int npl, int gthreads, int bs)
@@ -644,8 +657,10 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
         for (int h = 0; h < t.nH3span; ++h)
             th[(size_t)c * t.nH3span + h] = cis((double)(t.H3min + h) * m->frac[3 * mu + 2]);
     }
-    // ---- work list of the recombination: (k1, k2, G1, H2 range), one block each
+    // ---- work lists of the recombination: (k1, k2, G1, H2 range), one block each, for the
+    // forms the model may take
     const bool mag = m->kind == DSX_MAGNETIC;
+    const bool fold = fold_applies(m);
     int maxH2 = 0, maxH3 = 0;
     for (int k = 0; k < n2; ++k) maxH2 = std::max(maxH2, hcount(k, n2, bx.g0[1], bx.cnt[1]));
     for (int k = 0; k < n3; ++k) maxH3 = std::max(maxH3, hcount(k, n3, bx.g0[2], bx.cnt[2]));
@@ -810,13 +825,13 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
                 const int h2a = part * rpp, h2b = std::min(nH2, h2a + rpp);
                 if (h2a >= h2b) continue;
                 maxrows = std::max(maxrows, h2b - h2a);
-                for (size_t i = 0; i < planes.size(); ++i) {
+                for (size_t i = 0; mag && t.rows_mr * (m->dw_order == 0) == 0 && i < planes.size(); ++i) {
                     const int j1 = planes[i].first;
                     const int G1 = k1 + n1 * (H1lo + j1);
                     items.push_back({key * 4096 + j1, make_int4(k1, k2, G1, h2a | (h2b << 12) | (planes[i].second << 24))});
                 }
                 // planes are consecutive in H1 (the skipped ones are all at the end)
-                for (size_t i = 0; i < planes.size(); i += 2) {
+                for (size_t i = 0; fold && i < planes.size(); i += 2) {
                     const int j1 = planes[i].first;
                     const int G1 = k1 + n1 * (H1lo + j1);
                     const int hasb = i + 1 < planes.size() ? 1 : 0;
@@ -862,35 +877,31 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
         }
     }
 
-    auto up = [&](float2** dst, const std::vector<float2>& src) -> hipError_t {
-        hipError_t e = hipMalloc(dst, sizeof(float2) * std::max<size_t>(1, src.size()));
-        if (e != hipSuccess) return e;
-        return hipMemcpy(*dst, src.data(), sizeof(float2) * src.size(), hipMemcpyHostToDevice);
+    // one allocation and one copy for all of them
+    std::vector<unsigned char> host;
+    auto place = [&](const void* src, size_t bytes) {
+        const size_t at = host.size();
+        host.resize(at + (bytes + 255) / 256 * 256);
+        if (bytes) std::memcpy(host.data() + at, src, bytes);
+        return at;
     };
-    hipError_t e;
-    if ((e = up(&t.tab1, t1)) != hipSuccess || (e = up(&t.tab2, t2)) != hipSuccess ||
-        (e = up(&t.tabK2, tk2)) != hipSuccess ||
-        (e = up(&t.tabK3, tk)) != hipSuccess || (e = up(&t.tabH3, th)) != hipSuccess ||
-        (e = hipMalloc(&t.work, sizeof(int4) * std::max<size_t>(1, work.size()))) != hipSuccess ||
-        (e = hipMemcpy(t.work, work.data(), sizeof(int4) * work.size(), hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMalloc(&t.work2, sizeof(int4) * std::max<size_t>(1, work2.size()))) != hipSuccess ||
-        (e = hipMemcpy(t.work2, work2.data(), sizeof(int4) * work2.size(), hipMemcpyHostToDevice)) != hipSuccess ||
-        (!work3.empty() &&
-         ((e = hipMalloc(&t.work3, sizeof(int4) * work3.size())) != hipSuccess ||
-          (e = hipMemcpy(t.work3, work3.data(), sizeof(int4) * work3.size(), hipMemcpyHostToDevice)) != hipSuccess)) ||
-        (!work_s.empty() &&
-         ((e = hipMalloc(&t.work_s, sizeof(int4) * work_s.size())) != hipSuccess ||
-          (e = hipMemcpy(t.work_s, work_s.data(), sizeof(int4) * work_s.size(), hipMemcpyHostToDevice)) != hipSuccess)) ||
-        (!work_mr.empty() &&
-         ((e = hipMalloc(&t.work_mr, sizeof(int4) * work_mr.size())) != hipSuccess ||
-          (e = hipMemcpy(t.work_mr, work_mr.data(), sizeof(int4) * work_mr.size(), hipMemcpyHostToDevice)) != hipSuccess)) ||
-        (e = hipMalloc(&t.k3tab, sizeof(int2) * k3t.size())) != hipSuccess ||
-        (e = hipMemcpy(t.k3tab, k3t.data(), sizeof(int2) * k3t.size(), hipMemcpyHostToDevice)) != hipSuccess) {
+    auto add = [&](const auto& v) { return place(v.data(), v.size() * sizeof(v[0])); };
+    const size_t o1 = add(t1), o2 = add(t2), ok2 = add(tk2), ok3 = add(tk), oh = add(th), ow = add(work), ow2 = add(work2),
+                 ow3 = add(work3), ows = add(work_s), owm = add(work_mr), o3 = add(k3t);
+    hipError_t e = hipMalloc(&t.mem, host.size());
+    if (e == hipSuccess) e = hipMemcpy(t.mem, host.data(), host.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
         free_tables(t);
         if (e == hipErrorOutOfMemory) return fail(DSX_ERR_NOMEM, "out of device memory for phase tables");
         m->failed = true;
         return fail(DSX_ERR_DEVICE, std::string("phase tables: ") + hipGetErrorString(e));
     }
+    auto at2 = [&](size_t o) { return reinterpret_cast<float2*>(t.mem + o); };
+    auto at4 = [&](size_t o, const std::vector<int4>& v) { return v.empty() ? nullptr : reinterpret_cast<int4*>(t.mem + o); };
+    t.tab1 = at2(o1); t.tab2 = at2(o2); t.tabK2 = at2(ok2); t.tabK3 = at2(ok3); t.tabH3 = at2(oh);
+    t.work = at4(ow, work); t.work2 = at4(ow2, work2); t.work3 = at4(ow3, work3);
+    t.work_s = at4(ows, work_s); t.work_mr = at4(owm, work_mr);
+    t.k3tab = reinterpret_cast<int2*>(t.mem + o3);
     try {
         auto ins = m->tables.emplace(bx, t);
         *out = &ins.first->second;
@@ -1039,17 +1050,12 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         p.planes = stored_planes(bx);   // a half-stored box: its planes G1 <= 0 only
     }
     if (!lp.direct && std::max(lp.lds, staged_lds) > 160 * 1024) return fail(DSX_ERR_UNSUPPORTED, "recombination does not fit the LDS for this box");
-    // folded form: every r_mu2 a multiple of 1/2 (exactly, as given), fewer r3 classes
-    // than sites, and the class buffers fit the LDS
-    // (the folded kernel addresses the spectra of one configuration with 31-bit offsets)
-    const bool small_spectra = (unsigned long long)n1 * n2 * m->SF * m->nh * sizeof(float2) < (1ULL << 31);
-    if (!lp.direct && !mag && !p.nuc_ff && p.variant != 3 && m->nclass < m->S && small_spectra &&
-        m->order <= kMaxOrderFast) {
-        bool halves = true, whole = true;
+    // folded form, where the class buffers fit the LDS
+    if (!lp.direct && p.variant != 3 && fold_applies(m)) {
+        bool whole = true;
         for (int i = 0; i < m->S; ++i) {
             const double r2 = m->frac[3 * m->site_of[i] + 1];
             const double t2 = 2.0 * r2;
-            if (t2 != std::floor(t2)) halves = false;
             if (r2 != std::floor(r2)) whole = false;
             p.sgn2[i] = ((long long)std::floor(t2) % 2 == 0) ? 1 : -1;
         }
@@ -1063,7 +1069,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         const bool par = p.parity && p.variant != 2;
         const size_t lds = sizeof(float2) * (2 * bs + (size_t)4 * m->S * (m->order + 1) +
                                              (par ? 0 : (size_t)m->nclass * tb->nH3span));
-        if (halves && lds <= 140 * 1024) {
+        if (lds <= 140 * 1024) {
             p.fold = 1;
             p.fold_l2 = L2;
             p.n3s = n3s;

@@ -361,7 +361,8 @@ hipError_t launch_lanczos_stencil(const LanczosParams& p, hipStream_t st);
 int recombine_max_threads(int hc, int magnetic);
 size_t planes_lds_bytes(const PlaneParams& p);
 constexpr int kPlaneMaxFields = 8;    // fields per block of the plane kernels at most
-bool fft_reg_supported(int n);        // edges of the fixed-length register kernels
+// edges of the fixed-length register kernels
+inline bool fft_reg_supported(int n) { return n == 8 || n == 16 || n == 32; }
 size_t axis1_lds_bytes(const Axis1Params& p);
 size_t lanczos_lds_bytes(const LanczosParams& p);
 

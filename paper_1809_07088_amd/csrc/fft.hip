@@ -1280,8 +1280,6 @@ __global__ __launch_bounds__(kRegThreads) void k_fft_planes_reg_merged(const Pla
     if (slot_of(slots, d, bx)) fft_planes_reg_body<L2, L3, const PlaneParams&>(tab[d], bx);
 }
 
-bool fft_reg_supported(int n) { return n == 8 || n == 16 || n == 32; }
-
 template <int L2, int L3>
 static hipError_t launch_planes_reg(const PlaneParams& p, hipStream_t st)
 {
