@@ -40,6 +40,7 @@
 // float64 lattice sums (k_bragg_*), where the Bragg subtraction |<F>|^2 cancels
 // most of |F|^2 (Sec. II, Eq. bragg_diffuse_sf; Sec. III.A, Eq. bragg_sf); the
 // ensemble mean <F> is the mean over the model's configurations.
+#include <algorithm>
 #include <type_traits>
 
 #include "dsx_internal.h"
@@ -1565,15 +1566,15 @@ hipError_t launch_recombine_magnetic_rows(const RecombParams& p, int block, size
 }
 
 // ---------------------------------------------------------------------------- direct form
-// Taylor order 0 (occupancies only, one field per site): every voxel is computed on its
-// own, F_m(G) = sum_mu b_mu e^{2 pi i g.r_mu} X_mu,m(k), I(G) = scale sum_m |F_m(G)|^2.
+// Taylor order 0 (occupancies only, one field per site), a few sites: every voxel is computed on
+// its own, F_m(G) = sum_mu b_mu e^{2 pi i g.r_mu} X_mu,m(k), I(G) = scale sum_m |F_m(G)|^2.
 // A wave takes 64 consecutive columns i3 of the box, one a lane, over kDirectRows
 // consecutive rows (i1, i2): a lane's column fixes k3, H3 and the half of the spectra it
 // reads, a row fixes k1, k2 and the spectra column for the whole wave (scalar registers,
 // stepped from row to row), so a voxel costs its loads, |F|^2 and one store, and every
 // load and store of a wave is one contiguous run.  For one or two sites x configurations
 // this beats the levelled forms, whose blocks serve one column of the grid each.
-constexpr int kDirectThreads = 256, kDirectRows = 16, kDirectGroup = 16;
+constexpr int kDirectThreads = 256, kDirectRows = 16;
 constexpr int kDirectWaves = kDirectThreads / 64;
 
 // a / b for a < 2^32 through the float64 reciprocal rb of b (relative error well below
@@ -1638,50 +1639,7 @@ __device__ __forceinline__ void recombine_direct_body(PT P, const int bx)
     int k2 = __builtin_amdgcn_readfirstlane(P.g0[1] + i2 - n2 * floordiv_exact(P.g0[1] + i2, n2, __builtin_amdgcn_rcpf((float)n2)));
     const int k20 = __builtin_amdgcn_readfirstlane(P.g0[1] - n2 * floordiv_exact(P.g0[1], n2, __builtin_amdgcn_rcpf((float)n2)));
     auto* op = gptr(P.out) + P.ooff + (size_t)r0 * P.opitch + i3;
-    const bool one = P.S == 1;
-    const int mu0 = P.site_of[0];
-    const float2 t0 = ldg2(P.tab1, (size_t)mu0 * P.cnt[0]);
-    const float b2s = (t0.x * t0.x + t0.y * t0.y) * P.scale;
     const float cj = half ? -1.f : 1.f;
-    if (one) {
-        // one site: the phase has modulus b, so |F_m|^2 = b^2 |X_m(k)|^2 exactly.  Rows go
-        // in groups: the group's spectra offsets first (a direct-form spectrum has fewer than
-        // 2^32 elements), then all its loads of a configuration in flight at once
-        const float2* __restrict__ X0 = P.X + (size_t)mu0 * fstride;
-        for (int g = 0; g < nr; g += kDirectGroup) {
-            uint32_t colr[kDirectGroup];
-#pragma unroll
-            for (int r = 0; r < kDirectGroup; ++r) {
-                const uint32_t colp = (uint32_t)((k1 * n2 + k2) * SFnh);
-                const uint32_t colm = (uint32_t)(((k1 ? n1 - k1 : 0) * n2 + (k2 ? n2 - k2 : 0)) * SFnh);
-                colr[r] = (half ? colm : colp) + (uint32_t)koff;
-                if (++i2 == (int)c1) {
-                    i2 = 0;
-                    k2 = k20;
-                    k1 = (k1 + 1 == n1) ? 0 : k1 + 1;
-                } else {
-                    k2 = (k2 + 1 == n2) ? 0 : k2 + 1;
-                }
-            }
-            const int ng = min(kDirectGroup, nr - g);
-            float I[kDirectGroup];
-#pragma unroll
-            for (int r = 0; r < kDirectGroup; ++r) I[r] = 0.f;
-            for (int m = 0; m < P.M; ++m) {
-                const float2* __restrict__ Xm = X0 + (size_t)m * cstride;
-                float2 xv[kDirectGroup];
-#pragma unroll
-                for (int r = 0; r < kDirectGroup; ++r) xv[r] = r < ng ? ldg2(Xm, colr[r]) : make_float2(0.f, 0.f);
-#pragma unroll
-                for (int r = 0; r < kDirectGroup; ++r) I[r] += xv[r].x * xv[r].x + xv[r].y * xv[r].y;
-            }
-#pragma unroll
-            for (int r = 0; r < kDirectGroup; ++r)
-                if (r < ng) op[(size_t)r * P.opitch] = I[r] * b2s;
-            op += (size_t)kDirectGroup * P.opitch;
-        }
-        return;
-    }
     for (int r = 0; r < nr; ++r) {
         const size_t colp = ((size_t)k1 * n2 + k2) * SFnh;                                   // X(k)
         const size_t colm = ((size_t)(k1 ? n1 - k1 : 0) * n2 + (k2 ? n2 - k2 : 0)) * SFnh;   // X(-k), conjugated
@@ -1727,12 +1685,143 @@ __global__ __launch_bounds__(kDirectThreads) void k_recombine_direct_merged(cons
     if (slot_of(slots, d, bx)) recombine_direct_body<const RecombParams&>(tab[d], bx);
 }
 
+// One site (Taylor order 0): the site phase has modulus b, so I(G) = scale b^2 sum_m |X_m(k)|^2
+// repeats with the supercell.  A block takes P.rows consecutive rows (i1, i2): it forms the
+// intensities of their n3 residues k3 once (in LDS; several configurations split over the threads
+// that leaves idle), then writes the rows, c2 / n3 times as many values, as 16-byte stores of one
+// contiguous run.  Bound by those writes: 1024 boxes of 48^3 (453 MB) took 188 us with a load, an
+// |X|^2 and a 4-byte store per voxel (lanes idle past 48), 125 us here.
+constexpr int kTileThreads = 256;
+
+constexpr int kTileMaxRows = 256;
+
+template <class PT>
+__device__ __forceinline__ void recombine_tiles_body(PT P, const int bx)
+{
+    extern __shared__ float2 smem[];
+    __shared__ uint32_t colp[kTileMaxRows], colm[kTileMaxRows];   // spectra columns of k and -k, per row
+    const int n1 = P.n1, n2 = P.n2, n3 = P.n3, nh = P.nh, c1 = P.cnt[1], c2 = P.cnt[2], pitch = P.opitch;
+    const int rows = P.planes * c1, r0 = bx * P.rows, nr = min(P.rows, rows - r0);
+    const int items = nr * n3, parts = P.mg;
+    // a row's n3 intensities and the first three again: four from any residue on are contiguous
+    const int np = n3 + 3;
+    float* const tile = reinterpret_cast<float*>(smem);           // [rows][np]
+    float* const part = tile + P.rows * np;                       // [parts][items], several parts only
+    const int SFnh = P.SF * nh;                                   // (one site: nh)
+    const size_t cstride = (size_t)n1 * n2 * SFnh;
+    const float rn3 = 1.f / (float)n3;
+    if ((int)threadIdx.x < nr) {
+        const uint32_t row = (uint32_t)(r0 + threadIdx.x);
+        const int i1 = (int)udiv_exact(row, (uint32_t)c1, rcp_refined((uint32_t)c1)), i2 = (int)row - i1 * c1;
+        const int k1 = P.g0[0] + i1 - n1 * floordiv_exact(P.g0[0] + i1, n1, __builtin_amdgcn_rcpf((float)n1));
+        const int k2 = P.g0[1] + i2 - n2 * floordiv_exact(P.g0[1] + i2, n2, __builtin_amdgcn_rcpf((float)n2));
+        colp[threadIdx.x] = (uint32_t)(k1 * n2 + k2);
+        colm[threadIdx.x] = (uint32_t)((k1 ? n1 - k1 : 0) * n2 + (k2 ? n2 - k2 : 0));
+    }
+    __syncthreads();
+    const float2 t0 = ldg2(P.tab1, 0);
+    const float b2s = (t0.x * t0.x + t0.y * t0.y) * P.scale;
+    auto place = [&](int r, int k3, float v) {
+        for (int j = k3; j < np; j += n3) tile[r * np + j] = v;
+    };
+    for (int t = threadIdx.x; t < items * parts; t += kTileThreads) {
+        const int ms = parts == 1 ? 0 : qdiv_r(t, items, 1.f / (float)items), it = t - ms * items;
+        const int r = qdiv_r(it, n3, rn3), k3 = it - r * n3;
+        const bool half = k3 >= nh;                               // |X(k)| = |X(-k)|
+        const float2* X = P.X + (size_t)(half ? colm[r] : colp[r]) * SFnh + (half ? n3 - k3 : k3);
+        float v = 0.f;
+#pragma unroll 8
+        for (int m = ms; m < P.M; m += parts) {
+            const float2 x = ldg2(X, (size_t)m * cstride);
+            v += x.x * x.x + x.y * x.y;
+        }
+        if (parts == 1) place(r, k3, v * b2s);
+        else part[t] = v * b2s;
+    }
+    __syncthreads();
+    if (parts > 1) {
+        for (int it = threadIdx.x; it < items; it += kTileThreads) {
+            float v = part[it];
+            for (int ms = 1; ms < parts; ++ms) v += part[ms * items + it];
+            const int r = qdiv_r(it, n3, rn3);
+            place(r, it - r * n3, v);
+        }
+        __syncthreads();
+    }
+    const int k30 = P.g0[2] - n3 * floordiv_exact(P.g0[2], n3, __builtin_amdgcn_rcpf((float)n3));
+    auto* const out = gptr(P.out) + P.ooff + (size_t)r0 * pitch;
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(1))) f4 gf4;
+    if (P.ostream && (pitch & 3) == 0) {
+        // four values of one row a store (past c2 a padded row holds what is never read); row and
+        // column are stepped
+        const int qp = pitch >> 2;
+        const float rq = 1.f / (float)qp;
+        const int dr = qdiv_r(kTileThreads, qp, rq), dc = kTileThreads - dr * qp;
+        int r = qdiv_r(threadIdx.x, qp, rq), c = (int)threadIdx.x - r * qp;
+        for (; r < nr; r += dr) {
+            const int g = k30 + 4 * c, k3 = g - n3 * qdiv_r(g, n3, rn3);
+            const float* v = tile + r * np + k3;
+            *reinterpret_cast<gf4*>(out + (size_t)r * pitch + 4 * c) = f4{v[0], v[1], v[2], v[3]};
+            c += dc;
+            if (c >= qp) { c -= qp; ++r; }
+        }
+        return;
+    }
+    // rows of any length, one contiguous run of them; 16-byte stores where it starts on 16 bytes
+    const int total = (nr - 1) * pitch + c2;
+    const float rp = 1.f / (float)pitch;
+    const int step = P.ostream ? 4 : 1;
+    for (int e = step * threadIdx.x; e < total; e += step * kTileThreads) {
+        int r = qdiv_r(e, pitch, rp), i3 = e - r * pitch;
+        const int g = k30 + i3;
+        int k3 = g - n3 * qdiv_r(g, n3, rn3);
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            v[u] = r < nr ? tile[r * np + k3] : 0.f;
+            ++i3;
+            k3 = k3 + 1 == n3 ? 0 : k3 + 1;
+            if (i3 == pitch) { i3 = 0; ++r; k3 = k30; }
+        }
+        if (step == 4 && e + 4 <= total) *reinterpret_cast<gf4*>(out + e) = f4{v[0], v[1], v[2], v[3]};
+        else
+            for (int u = 0; u < step && e + u < total; ++u) out[e + u] = v[u];
+    }
+}
+
+__global__ __launch_bounds__(kTileThreads) void k_recombine_tiles(RecombParams P) { recombine_tiles_body<RecombParams>(P, blockIdx.x); }
+__global__ __launch_bounds__(kTileThreads) void k_recombine_tiles_merged(const RecombParams* __restrict__ tab, const Slot* __restrict__ slots)
+{
+    int d, bx;
+    if (slot_of(slots, d, bx)) recombine_tiles_body<const RecombParams&>(tab[d], bx);
+}
+
+// One site: rows per block for about 6144 values (24 a thread; the 1024 boxes of 48^3 took 158,
+// 125, 131 and 157 us at 4096, 6144, 8192 and 12288), in fours so that a dense box's
+// blocks start on 16 bytes; fewer where many configurations make the sums the longer part and
+// that leaves under 512 blocks.
+static hipError_t launch_recombine_tiles(const RecombParams& p, hipStream_t st)
+{
+    RecombParams q = p;
+    const long long rows = (long long)p.planes * p.cnt[1];
+    int r = std::max(4, std::min(kTileMaxRows, 6144 / p.opitch / 4 * 4));
+    while (p.M > 8 && r > 4 && (rows + r - 1) / r < 512) r -= 4;
+    while (r > 1 && (size_t)r * p.n3 > 8192) r /= 2;
+    q.rows = r;
+    q.mg = std::max(1, std::min(p.M, kTileThreads / (r * p.n3)));
+    q.ostream = r % 4 == 0 && (p.opitch % 4 == 0 || p.opitch == p.cnt[2]) && p.ooff % 4 == 0 && ((uintptr_t)p.out & 15) == 0;
+    const size_t lds = sizeof(float) * ((size_t)r * (p.n3 + 3) + (q.mg > 1 ? (size_t)q.mg * r * p.n3 : 0));
+    return dispatch(k_recombine_tiles, k_recombine_tiles_merged, (unsigned)((rows + r - 1) / r), kTileThreads, lds, st, q);
+}
+
 hipError_t launch_recombine_direct(const RecombParams& p, hipStream_t st)
 {
     if (p.planes < 0 || p.planes > p.cnt[0]) return hipErrorInvalidValue;
     const unsigned long long rows = (unsigned long long)p.planes * p.cnt[1];
     if (rows == 0 || p.cnt[2] == 0) return hipSuccess;
     if (rows * (unsigned long long)p.cnt[2] >= (1ULL << 32)) return hipErrorInvalidValue;
+    if (p.S == 1 && rows < (1ULL << 31)) return launch_recombine_tiles(p, st);
     const unsigned long long waves = (rows + kDirectRows - 1) / kDirectRows * ((p.cnt[2] + 63) / 64);
     return dispatch(k_recombine_direct, k_recombine_direct_merged, (unsigned)((waves + kDirectWaves - 1) / kDirectWaves),
                     kDirectThreads, 0, st, p);
@@ -2006,11 +2095,12 @@ __global__ __launch_bounds__(64) void k_bragg_ensemble_merged(const BraggParams*
 
 // Steps of a lane in the two forms: the ensemble form walks all pairs once per 64
 // configurations, the other one 1/64 of the pairs and a reduction (about a dozen steps' worth)
-// per configuration.
+// per configuration.  Under 16 configurations most of its lanes would idle (1024 single-site
+// models of one configuration: 18 us in the lane-per-H form, 165 in this one).
 static bool bragg_by_configs(const BraggParams& p)
 {
     const long items = (long)p.S * p.T;
-    return items <= kBraggPairs && 2 * items * ((p.M + 63) / 64) <= (long)p.M * ((items + 63) / 64 + 12);
+    return p.M >= 16 && items <= kBraggPairs && 2 * items * ((p.M + 63) / 64) <= (long)p.M * ((items + 63) / 64 + 12);
 }
 
 // Taylor order 0 with few sites (one field per site, the occupancy): one lane per H.  The

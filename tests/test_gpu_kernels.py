@@ -126,3 +126,23 @@ def test_bragg_points_of_ensembles(S, M, order):
     I = gpu_intensity(m).reshape(m.count)[::2, ::3, ::2]
     G = O.grid_points(m.g0, m.count).reshape(m.count + (3,))[::2, ::3, ::2].reshape(-1, 3)
     assert_parity(I.reshape(-1), O.intensity(m, G, order if order else None))
+
+
+# ------------------------------------------------------------------ one site: tiled rows
+@pytest.mark.parametrize("n,M", [((3, 4, 5), 1), ((12, 5, 7), 3), ((2, 3, 31), 70), ((9, 8, 64), 2), ((1, 2, 200), 1)])
+@pytest.mark.parametrize("box", ["symmetric", "offset", "short"])
+@pytest.mark.parametrize("lm", [0, 2])
+def test_one_site_tiles(n, M, box, lm):
+    """Dense rows of any length mod 4 and padded rows (under the filter), half-stored boxes, rows
+    shorter than the supercell, several configurations over the threads."""
+    from tests.helpers import gpu_filtered
+    m = synth.random_model(2500 + sum(n) + M, n=n, S=1, M=M, order=0, with_disp=False)
+    r = [min(v + 2, 9) for v in n]
+    m.g0, m.count = {"symmetric": ([-v for v in r], [2 * v + 1 for v in r]), "offset": ([-v for v in r], [2 * v + 2 for v in r]),
+                     "short": ([-r[0], -r[1], n[2] - 2], [2 * r[0] + 1, 2 * r[1] + 1, 3])}[box]
+    m.g0, m.count = tuple(m.g0), tuple(m.count)
+    say(f"one site n={n} M={M} box={m.g0}+{m.count} lm={lm}")
+    if lm:
+        assert_parity(gpu_filtered(m, lm), O.filtered_intensity(m, lm, 1))
+    else:
+        sampled_parity(m)
