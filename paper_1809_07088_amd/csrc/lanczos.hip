@@ -12,6 +12,8 @@
 // LDS (rows and halo), filtered along axis 3 then axis 2, and kept in a ring of
 // 2m filtered planes; an output plane is emitted as soon as its 2m input planes
 // are in the ring.  Every input value is read from HBM about once per block.
+#include <algorithm>
+
 #include "dsx_internal.h"
 
 namespace dsx {
@@ -262,6 +264,152 @@ __global__ __launch_bounds__(512, 2) void k_lanczos_ring_merged(const LanczosPar
     if (slot_of(slots, d, bx)) lanczos_ring_body<M2, S1, const LanczosParams&>(tab[d], bx);
 }
 
+// Oversampled outputs (s >= 2), and windows of 10 to 16 planes at s = 1: the same streaming as the
+// ring kernel, with the phase of an output (i mod s) choosing its weights.  An input plane's tile
+// (with halo) is staged in LDS; along axis 3 a thread keeps one output column, whose window and
+// weights are fixed (in registers); along axis 2 it takes four consecutive output rows, whose
+// phases are the same for its whole wave; the values join a register ring of the last M2 planes,
+// from which the s output planes between two input planes are emitted.  The next plane is in
+// flight in registers meanwhile.  Bound by latency (three barriers per input plane) on small
+// outputs and by the writes on large ones: 146 x 162 x 218 outputs at s = 2 took 100 us with the
+// generic kernel's divisions, LDS ring and four barriers, 19 us here.
+template <int M2, bool S1, class PT>
+__device__ __forceinline__ void lanczos_over_body(PT P, const int bx)
+{
+    constexpr int L2 = (S1 ? kRT2 - 1 : kRT2 / 2) + M2, L3 = (S1 ? kRT3 - 1 : kRT3 / 2) + M2;   // staged rows, columns at most
+    constexpr int NSTG = (L2 * L3 + kRThreads - 1) / kRThreads;
+    __shared__ float wn_s[(S1 ? 1 : 16) * M2];
+    __shared__ float stg[L2 * L3];
+    __shared__ float mid[L2 * kRT3];
+    int b = xcd_tile(bx, P.nb1 * P.nb2 * P.nb3);
+    if (b < 0) return;
+    b = __builtin_amdgcn_readfirstlane(b);
+    const int b12 = __builtin_amdgcn_readfirstlane(b / P.nb3), b3 = b - b12 * P.nb3;
+    const int b1 = __builtin_amdgcn_readfirstlane(b12 / P.nb2), b2 = b12 - b1 * P.nb2;
+    const int s = S1 ? 1 : P.s, eo = P.eoff;
+    const int o1 = b1 * P.t1, o2 = b2 * kRT2, o3 = b3 * kRT3;
+    const int T1 = min(P.t1, P.o[0] - o1), T2 = min(kRT2, P.o[1] - o2), T3 = min(kRT3, P.o[2] - o3);
+    const int E2lo = o2 / s + eo, E2n = (o2 + T2 - 1) / s + eo - E2lo + M2;
+    const int E3lo = o3 / s + eo, E3n = (o3 + T3 - 1) / s + eo - E3lo + M2;
+    for (int i = threadIdx.x; i < s * M2; i += kRThreads) wn_s[i] = gptr(P.wn)[i];
+
+    // this thread's staging elements (row-major, pitch L3), as offsets within a stored plane and
+    // within the mirrored plane (rows and columns reversed)
+    int soff[NSTG], moff[NSTG];
+#pragma unroll
+    for (int k = 0; k < NSTG; ++k) {
+        const int idx = threadIdx.x + kRThreads * k;
+        const int r = idx / L3, c = idx - r * L3;
+        const bool in = r < E2n && c < E3n;
+        soff[k] = in ? (E2lo + r) * P.ipitch + E3lo + c + P.ioff : -1;
+        moff[k] = in ? (P.e[1] - 1 - E2lo - r) * P.ipitch + (P.e[2] - 1 - E3lo - c) + P.ioff : -1;
+    }
+    const size_t plane = (size_t)P.e[1] * P.ipitch;
+    const int e1a = o1 / s + eo, e1b = (o1 + T1 - 1) / s + eo + M2 - 1;
+    float buf[NSTG];
+    auto fetch = [&](int e1) {
+        const bool mir = e1 >= P.ihalf;
+        const auto* src = gptr(P.in) + (size_t)(mir ? P.e[0] - 1 - e1 : e1) * plane;
+#pragma unroll
+        for (int k = 0; k < NSTG; ++k) buf[k] = soff[k] >= 0 ? src[mir ? moff[k] : soff[k]] : 0.f;
+    };
+    fetch(e1a);
+    const int j3 = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    __syncthreads();                               // weights visible
+    // axis 3: the thread's column
+    const int i3 = o3 + min(j3, T3 - 1), q3 = i3 / s;
+    const int c3 = q3 + eo - E3lo;
+    float w3[M2];
+#pragma unroll
+    for (int d = 0; d < M2; ++d) w3[d] = wn_s[(i3 - q3 * s) * M2 + d];
+    // axis 2: first staged row and weights of the thread's rows (rows past the tile repeat its last)
+    int r2[kRRun], p2[kRRun];
+#pragma unroll
+    for (int q = 0; q < kRRun; ++q) {
+        const int i2 = o2 + min(g * kRRun + q, T2 - 1), q2 = __builtin_amdgcn_readfirstlane(i2 / s);
+        r2[q] = q2 + eo - E2lo;
+        p2[q] = (i2 - q2 * s) * M2;
+    }
+    float ring[M2][kRRun];
+#pragma unroll
+    for (int d = 0; d < M2; ++d)
+#pragma unroll
+        for (int k = 0; k < kRRun; ++k) ring[d][k] = 0.f;
+    for (int e1 = e1a; e1 <= e1b; ++e1) {
+        // (the previous plane's staging was consumed before its second barrier)
+#pragma unroll
+        for (int k = 0; k < NSTG; ++k) {
+            const int idx = threadIdx.x + kRThreads * k;
+            if (idx < L2 * L3) stg[idx] = buf[k];
+        }
+        if (e1 < e1b) fetch(e1 + 1);
+        __syncthreads();
+        for (int r = g; r < E2n; r += kRThreads / 64) {
+            const float* x = stg + r * L3 + c3;
+            float acc = 0.f;
+#pragma unroll
+            for (int d = 0; d < M2; ++d) acc = fmaf(w3[d], x[d], acc);
+            mid[r * kRT3 + j3] = acc;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kRRun; ++q) {
+            const float* x = mid + r2[q] * kRT3 + j3;
+            const float* w = wn_s + p2[q];
+            float v = 0.f;
+#pragma unroll
+            for (int d = 0; d < M2; ++d) v = fmaf(w[d], x[d * kRT3], v);
+#pragma unroll
+            for (int d = 0; d < M2 - 1; ++d) ring[d][q] = ring[d + 1][q];
+            ring[M2 - 1][q] = v;
+        }
+        // the output planes whose window ends at plane e1
+        const int f1 = (e1 - M2 + 1 - eo) * s;
+        const int ia = max(o1, f1), ib = min(o1 + T1, f1 + s);
+        if (e1 - M2 + 1 < e1a || j3 >= T3) continue;
+        for (int i1 = ia; i1 < ib; ++i1) {
+            float w[M2];
+#pragma unroll
+            for (int d = 0; d < M2; ++d) w[d] = wn_s[(i1 - f1) * M2 + d];
+            auto* orow = gptr(P.out) + ((size_t)i1 * P.o[1] + o2) * P.o[2] + o3 + j3;
+#pragma unroll
+            for (int q = 0; q < kRRun; ++q) {
+                const int j2 = g * kRRun + q;
+                float acc = 0.f;
+#pragma unroll
+                for (int d = 0; d < M2; ++d) acc = fmaf(w[d], ring[d][q], acc);
+                if (j2 < T2) orow[(size_t)j2 * P.o[2]] = acc;
+            }
+        }
+    }
+}
+
+template <int M2, bool S1>
+__global__ __launch_bounds__(512, M2 > 12 ? 2 : 4) void k_lanczos_over(LanczosParams P) { lanczos_over_body<M2, S1, LanczosParams>(P, blockIdx.x); }
+template <int M2, bool S1>
+__global__ __launch_bounds__(512, M2 > 12 ? 2 : 4) void k_lanczos_over_merged(const LanczosParams* __restrict__ tab, const Slot* __restrict__ slots)
+{
+    int d, bx;
+    if (slot_of(slots, d, bx)) lanczos_over_body<M2, S1, const LanczosParams&>(tab[d], bx);
+}
+
+template <int M2>
+static hipError_t launch_over(const LanczosParams& p, hipStream_t st)
+{
+    LanczosParams q = p;
+    q.t2 = kRT2; q.t3 = kRT3;
+    // whole input planes a segment; shorter segments where long ones leave under 512 blocks
+    q.t1 = std::max(1, p.t1 / p.s) * p.s;
+    q.nb2 = (p.o[1] + kRT2 - 1) / kRT2;
+    q.nb3 = (p.o[2] + kRT3 - 1) / kRT3;
+    while (q.t1 > 2 * p.s && ((p.o[0] + q.t1 - 1) / q.t1) * q.nb2 * q.nb3 < 512) q.t1 -= p.s;
+    q.nb1 = (p.o[0] + q.t1 - 1) / q.t1;
+    const unsigned grid = 8 * ((q.nb1 * q.nb2 * q.nb3 + 7) / 8);
+    if constexpr (M2 > 8)      // (narrower windows at s = 1: the ring kernel)
+        if (p.s == 1) return dispatch(k_lanczos_over<M2, true>, k_lanczos_over_merged<M2, true>, grid, kRThreads, 0, st, q);
+    return dispatch(k_lanczos_over<M2, false>, k_lanczos_over_merged<M2, false>, grid, kRThreads, 0, st, q);
+}
+
 size_t lanczos_lds_bytes(const LanczosParams& p)
 {
     const int m2 = 2 * p.m;
@@ -287,6 +435,18 @@ hipError_t launch_lanczos(const LanczosParams& p, hipStream_t st)
         if (p.m == 2) return dispatch(k_lanczos_ring<4, true>, k_lanczos_ring_merged<4, true>, grid, kRThreads, 0, st, q);
         if (p.m == 3) return dispatch(k_lanczos_ring<6, true>, k_lanczos_ring_merged<6, true>, grid, kRThreads, 0, st, q);
         return dispatch(k_lanczos_ring<8, true>, k_lanczos_ring_merged<8, true>, grid, kRThreads, 0, st, q);
+    }
+    if (p.s <= 16) {
+        switch (p.m) {
+            case 2: return launch_over<4>(p, st);
+            case 3: return launch_over<6>(p, st);
+            case 4: return launch_over<8>(p, st);
+            case 5: return launch_over<10>(p, st);
+            case 6: return launch_over<12>(p, st);
+            case 7: return launch_over<14>(p, st);
+            case 8: return launch_over<16>(p, st);
+            default: break;      // wider windows: the generic kernel (its ring of planes is in LDS)
+        }
     }
     const size_t lds = lanczos_lds_bytes(p);
     if (lds > 65536) {

@@ -146,3 +146,18 @@ def test_one_site_tiles(n, M, box, lm):
         assert_parity(gpu_filtered(m, lm), O.filtered_intensity(m, lm, 1))
     else:
         sampled_parity(m)
+
+
+# ------------------------------------------------------------------ filter: oversampled and wide windows
+@pytest.mark.parametrize("lm,mp,s", [(2, 2, 2), (2, 2, 3), (3, 2, 2), (4, 2, 5), (2, 3, 16), (5, 2, 1), (5, 2, 2), (4, 3, 1),
+                                     (7, 2, 1), (4, 4, 1), (8, 2, 3), (3, 6, 2), (6, 3, 1)])
+@pytest.mark.parametrize("count", [(3, 9, 33), (14, 5, 2)])
+def test_oversampled_and_wide_filters(lm, mp, s, count):
+    """Every window width of the streaming kernel (and one past it), phases that do and do not
+    divide the tile, ragged tiles and segments, a half-stored and an unsymmetric box."""
+    from tests.helpers import gpu_filtered
+    m = synth.random_model(2600 + lm + mp + s, n=(3, 4, 5), S=1, M=2, order=0, with_disp=False)
+    m.count = count
+    m.g0 = tuple(-(c - 1) // 2 if c % 2 else -1 for c in count)
+    say(f"filter m={lm} m'={mp} s={s} box={m.g0}+{m.count}")
+    assert_parity(gpu_filtered(m, lm, s, mp), O.filtered_intensity(m, lm, s, mprime=mp))
