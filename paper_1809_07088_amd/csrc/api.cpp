@@ -286,7 +286,7 @@ struct DeviceTables {
     int nwork_s = 0, npl_s = 1, mg_s = 1, gthreads_s = 64, rows_s = 1, csites_s = 1, n3s_s = 1, slices_s = 1;
     int ks3 = 0, nact3 = 0;    // the k3 with points in the box: nact3 of them, cyclically from ks3
     int4* work_mr = nullptr;   // magnetic models: blocks of the row-staged form (null: not used)
-    int nwork_mr = 0, rows_mr = 0, csites_mr = 0, qmod_mr = 0, qmod2_mr = 0, qmod1_mr = 0;
+    int nwork_mr = 0, rows_mr = 0, csites_mr = 0, qmod_mr = 0, qmod2_mr = 0, qmod1_mr = 0, mc_mr = 1;
     // the lists in column order (before they are dealt to the XCDs), to cut them down to the
     // rows a point list needs
     std::vector<int4> h_work, h_work2, h_work3, h_work_s, h_work_mr;
@@ -686,7 +686,24 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
     // the row-staged magnetic form: one thread per G3 of the box (at most
     // kMagRowsMaxThreads), rows per block from the LDS budget (about four blocks per CU),
     // site chunks of the staging area, and the H3 residues the classes are summed over
-    if (mag && bx.cnt[2] <= kMagRowsMaxThreads) {
+    if (mag && m->dw_order > 0 && bx.cnt[2] <= kMagRowsMaxThreads) {
+        // the Debye-Waller form of it: four (or two, or one) configurations at a time, rows for
+        // 16 KB of T's coefficients, everything in 64 KB of LDS where a smaller pass allows it
+        // and in 150 KB at most (else one configuration and one site at a time in registers)
+        const int N = m->dw_order;
+        int rows = std::max(1, std::min(kMagRowsMaxRows, (int)(16 * 1024 / sizeof(float2) / ((size_t)S * (N + 2)))));
+        rows = std::min(rows, std::max(1, maxH2));
+        for (int mc : {4, 2, 1}) {
+            if (mc > 1 && mc / 2 >= m->M) continue;
+            const size_t lds = sizeof(float2) * magnetic_dw_rows_lds_elems(mc, rows, S, m->nclass, n3, t.nH3span, N,
+                                                                          m->M > mc ? rows * bx.cnt[2] : 0);
+            if (lds > (size_t)(mc > 1 ? 64 : 150) * 1024) continue;
+            t.rows_mr = rows;
+            t.mc_mr = mc;
+            break;
+        }
+    }
+    if (mag && m->dw_order == 0 && bx.cnt[2] <= kMagRowsMaxThreads) {
         const int NC = m->nclass;
         int q = 0;
         bool uniform = true;
@@ -825,7 +842,7 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
                 const int h2a = part * rpp, h2b = std::min(nH2, h2a + rpp);
                 if (h2a >= h2b) continue;
                 maxrows = std::max(maxrows, h2b - h2a);
-                for (size_t i = 0; mag && t.rows_mr * (m->dw_order == 0) == 0 && i < planes.size(); ++i) {
+                for (size_t i = 0; mag && t.rows_mr == 0 && i < planes.size(); ++i) {
                     const int j1 = planes[i].first;
                     const int G1 = k1 + n1 * (H1lo + j1);
                     items.push_back({key * 4096 + j1, make_int4(k1, k2, G1, h2a | (h2b << 12) | (planes[i].second << 24))});
@@ -1007,11 +1024,22 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
     lp.hc = tb->hc;
     lp.block = tb->block;
     lp.lds = m->chunk_lds + sizeof(float2) * ((size_t)m->nclass * tb->nH3span + p.dw_elems);
+    size_t staged_lds = lp.lds;     // (the limit on sites, order and box, whatever the form)
     {
         int c = 0;
         for (int i = 0; i < m->S; ++i)
             while (c <= m->class_of[i]) p.class_start[c++] = i;
         while (c <= m->nclass) p.class_start[c++] = m->S;
+    }
+    if (mag && m->dw_order > 0 && tb->work_mr) {
+        lp.mag_rows = true;
+        p.work = tb->work_mr;
+        p.nwork = tb->nwork_mr;
+        p.rows = tb->rows_mr;
+        p.mg = tb->mc_mr;
+        lp.block = std::max(64, (bx.cnt[2] + 63) / 64 * 64);
+        lp.lds = sizeof(float2) * magnetic_dw_rows_lds_elems(p.mg, p.rows, m->S, m->nclass, n3, tb->nH3span, m->dw_order,
+                                                             m->M > p.mg ? p.rows * bx.cnt[2] : 0);
     }
     if (mag && m->dw_order == 0 && tb->work_mr) {
         lp.mag_rows = true;
@@ -1025,8 +1053,8 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         lp.block = std::max(64, (bx.cnt[2] + 63) / 64 * 64);
         const int staged = tb->qmod2_mr > 0 ? std::min(tb->rows_mr, tb->qmod2_mr) : tb->rows_mr;
         lp.lds = sizeof(float2) * magnetic_rows_lds_elems(staged, tb->csites_mr, m->S, m->nclass, n3, tb->nH3span);
+        staged_lds = lp.lds;
     }
-    const size_t staged_lds = lp.lds;     // (the limit on sites, order and box is this one's)
     if (!mag) {
         // the sites form
         p.work = tb->work_s;

@@ -133,7 +133,7 @@ struct RecombParams {
                             // level A sums the sites of each r3 class (per H2 residue)
     int32_t fold_l2;        // H2 residues of the folded form: 1 (every r_mu2 whole) or 2
     int32_t n3s;            // folded form: k3 per slice; block slice s covers k3 in [s n3s, (s + 1) n3s)
-    // sites form: planes per block (1 or 2), configurations at a time, threads per group, the
+    // sites form (mg also: the Debye-Waller rows form): planes per block (1 or 2), configurations at a time, threads per group, the
     // first k3 with points in the box and how many there are (cyclically), blocks of at most
     // `rows` rows and site chunks of `csites` sites
     int32_t npl, mg, gthreads, ks3, nact3;
@@ -330,7 +330,7 @@ hipError_t launch_recombine_magnetic(const RecombParams& p, int hc, int block, s
                                      hipStream_t st);
 // the direct form (Taylor order 0, one field per site): one thread per voxel of the box
 hipError_t launch_recombine_direct(const RecombParams& p, hipStream_t st);
-// the row-staged magnetic form (no Debye-Waller factor); p.work lists its blocks, and
+// the row-staged magnetic form (with dw_order > 0, its Debye-Waller form); p.work lists its blocks, and
 // the launch has one thread per G3 of the box (block >= cnt3)
 constexpr int kMagRowsMaxThreads = 512;
 constexpr int kMagRowsMaxRows = 16;
@@ -342,6 +342,13 @@ inline size_t magnetic_rows_lds_elems(int rows, int csites, int S, int nclass, i
 {
     return (size_t)rows * nclass * 3 * n3 + (size_t)S * n3 + (size_t)rows * S + (size_t)nclass * nH3span
          + (size_t)csites * 3 * n3;
+}
+// float2 elements of the LDS of its form with Debye-Waller factors of order N: mc configurations
+// at a time, `sums` floats for the sums of several passes
+inline size_t magnetic_dw_rows_lds_elems(int mc, int rows, int S, int nclass, int n3, int nH3span, int N, int sums)
+{
+    return (size_t)mc * S * 3 * n3 + (size_t)rows * S * (N + 2) + (size_t)nclass * nH3span + (size_t)S * n_pairs(N)
+         + (sums + 1) / 2;
 }
 hipError_t launch_bragg(const BraggParams& p, int order, hipStream_t st);
 // dwc[mu][t] = sum_m sums[m][mu][t] / sum_m sums[m][mu][0] (0 for a site with no atom):

@@ -1532,6 +1532,165 @@ __global__ __launch_bounds__(kMagRowsMaxThreads) void k_recombine_magnetic_rows_
     if (slot_of(slots, d, bx)) recombine_magnetic_rows_body<MULTI, NCT, const RecombParams&>(tab[d], bx);
 }
 
+// Magnetic sites with Debye-Waller factors, rows form: blocks and threads as above (one plane), but
+// each site enters on its own with T_mu(G).  T depends on no configuration, so a voxel's factors
+// W = e^{2 pi i (g2 r2 + H3 r3)} f_mu T_mu are formed once for MC configurations, whose three
+// components they then multiply:
+//   A, Bd    T's coefficients contracted over p (per block, float64) and q (per row), in LDS;
+//   level A  Bs[configuration][site][comp][k3] with the g1 and k3 phases;
+//   level C  per voxel and site W (Horner in i t3), then F of the MC configurations; the sums over
+//            further configurations in LDS.
+// The form that took T per configuration, voxel and run of H3 in registers ran at 218 us on 121^3
+// with 4 sites, order 3 and 4 configurations, this one at 36.
+template <int MC, class PT>
+__device__ __forceinline__ void recombine_magnetic_dw_rows_body(PT P, const int bx)
+{
+    extern __shared__ float2 smem[];
+    BlockWork w;
+    if (!decode_block(P, w, bx)) return;
+    const int n1 = P.n1, n2 = P.n2, n3 = P.n3, nh = P.nh, S = P.S, NC = P.nclass, cnt3 = P.cnt[2];
+    const int rows = w.h2b - w.h2a, N = P.dw_order, QR = n_pairs(N), N1 = N + 1;
+    float2* Bs = smem;                             // [MC][S][3][n3]
+    float2* t2 = Bs + MC * S * 3 * n3;             // [rows][S]
+    float2* tHs = t2 + P.rows * S;                 // [NC][nH3span]
+    float2* A = tHs + NC * P.nH3span;              // [S][QR]
+    float2* Bd = A + S * QR;                       // [rows][S][N + 1]
+    float* Iacc = reinterpret_cast<float*>(Bd + P.rows * S * N1);   // [rows][cnt3], several passes only
+    const float2* tH0 = stage_class_phases(P, tHs);
+    const float rn3 = 1.f / (float)n3, rS = 1.f / (float)S;
+    dw_level_a(P, 6.283185307179586 * (double)w.G1 / (double)n1, A);
+    for (int idx = threadIdx.x; idx < rows * S; idx += blockDim.x) {
+        const int r = qdiv_r(idx, S, rS), i = idx - r * S;
+        t2[idx] = P.tab2[(size_t)P.site_of[i] * P.cnt[1] + (w.k2 + n2 * (w.H2lo + w.h2a + r) - P.g0[1])];
+    }
+    __syncthreads();
+    // sum_q (i t2)^q / q! A[(q, r)] / r! of every row and (sorted) site
+    for (int idx = threadIdx.x; idx < rows * S * N1; idx += blockDim.x) {
+        const int rs = idx / N1, r = idx - rs * N1;
+        const int row = rs / S, i = rs - row * S;
+        const float tau2 = (float)(6.283185307179586 * (double)(w.k2 + n2 * (w.H2lo + w.h2a + row)) / (double)n2);
+        const float2* a = A + P.site_of[i] * QR;
+        float2 v = make_float2(0.f, 0.f);
+        float mag = inv_factorial_rt(r);
+        for (int q = 0; q + r <= N; ++q) {
+            const float2 x = a[pair_index(q, r)];
+            const float2 y = (q & 1) ? make_float2(-x.y, x.x) : x;          // times i^q
+            const float c = (q & 2) ? -mag : mag;
+            v.x = fmaf(c, y.x, v.x);
+            v.y = fmaf(c, y.y, v.y);
+            mag *= tau2 / (float)(q + 1);
+        }
+        Bd[idx] = v;
+    }
+    const int SFnh = P.SF * nh;
+    const size_t cstride = (size_t)n1 * n2 * SFnh;
+    const size_t col = ((size_t)w.k1 * n2 + w.k2) * SFnh;
+    const size_t colm = ((size_t)((n1 - w.k1) % n1) * n2 + (n2 - w.k2) % n2) * SFnh;
+    const int i3 = threadIdx.x;
+    const bool active = i3 < cnt3;
+    const int G3 = P.g0[2] + (active ? i3 : 0);
+    const int H3 = floordiv(G3, n3), k3 = G3 - n3 * H3;
+    const float inv16pi2 = 1.f / (16.f * 9.8696044010893586f);
+    const float g1 = (float)((double)w.G1 / (double)n1), g3 = (float)((double)G3 / (double)n3);
+    const float tau3 = (float)(6.283185307179586 * (double)G3 / (double)n3);
+    const float q13x = g1 * P.recip[0] + g3 * P.recip[6];
+    const float q13y = g1 * P.recip[1] + g3 * P.recip[7];
+    const float q13z = g1 * P.recip[2] + g3 * P.recip[8];
+    const size_t plane = (size_t)P.cnt[1] * P.opitch;
+    float* const orow0 = P.out + P.ooff + (size_t)w.i1 * plane + i3;
+    float* const mrow0 = P.out + P.ooff + (size_t)(P.cnt[0] - 1 - w.i1) * plane + (P.cnt[2] - 1 - i3);
+    for (int m0 = 0; m0 < P.M; m0 += MC) {
+        const int mc = min(MC, P.M - m0);
+        const bool last = m0 + MC >= P.M;
+        __syncthreads();
+        const int tot = S * 3 * n3;
+        for (int idx = threadIdx.x; idx < MC * tot; idx += blockDim.x) {
+            const int rj = qdiv_r(idx, n3, rn3), kk = idx - rj * n3;
+            const int mj = qdiv_r(rj, 3 * S, rS * (1.f / 3.f)), sj = rj - mj * 3 * S;
+            const int i = sj / 3, comp = sj - 3 * i;
+            float2 v = make_float2(0.f, 0.f);
+            if (mj < mc) {
+                const int mu = P.site_of[i];
+                const size_t f = (size_t)(m0 + mj) * cstride + ((size_t)mu * 3 + comp) * nh;
+                float2 x;
+                if (kk < nh) x = P.X[f + col + kk];
+                else { x = P.X[f + colm + (n3 - kk)]; x.y = -x.y; }
+                v = cmulf(cmulf(P.tab1[(size_t)mu * P.cnt[0] + w.i1], P.tabK3[(size_t)mu * n3 + kk]), x);
+            }
+            Bs[idx] = v;
+        }
+        __syncthreads();
+        for (int r = 0; r < rows && active; ++r) {
+            const int G2 = w.k2 + n2 * (w.H2lo + w.h2a + r);
+            const float g2 = (float)((double)G2 / (double)n2);
+            const float qx = q13x + g2 * P.recip[3], qy = q13y + g2 * P.recip[4], qz = q13z + g2 * P.recip[5];
+            const float q2 = qx * qx + qy * qy + qz * qz, s2 = q2 * inv16pi2;
+            float2 F[MC][3];
+#pragma unroll
+            for (int mj = 0; mj < MC; ++mj)
+#pragma unroll
+                for (int comp = 0; comp < 3; ++comp) F[mj][comp] = make_float2(0.f, 0.f);
+            for (int i = 0; i < S; ++i) {
+                float2 W = cmulf(t2[r * S + i], tH0[P.class_of[i] * P.nH3span + H3]);
+                const float2* b = Bd + (r * S + i) * N1;
+                float2 T = b[N];
+                for (int k = N - 1; k >= 0; --k) T = make_float2(b[k].x - tau3 * T.y, b[k].y + tau3 * T.x);
+                W = cmulf(W, T);
+                if (!P.ff_uniform) {
+                    const float f = mag_ff(P.ff[i], s2);
+                    W.x *= f;
+                    W.y *= f;
+                }
+                const float2* x = Bs + (size_t)i * 3 * n3 + k3;
+#pragma unroll
+                for (int mj = 0; mj < MC; ++mj)
+#pragma unroll
+                    for (int comp = 0; comp < 3; ++comp) cmac(F[mj][comp], W, x[mj * tot + comp * n3]);
+            }
+            // |F_perp|^2 = |F|^2 - |Qhat.F|^2 (0 at Q = 0)
+            const float iq = rsqrtf(q2), ex = qx * iq, ey = qy * iq, ez = qz * iq;
+            float val = 0.f;
+#pragma unroll
+            for (int mj = 0; mj < MC; ++mj) {
+                const float px = ex * F[mj][0].x + ey * F[mj][1].x + ez * F[mj][2].x;
+                const float py = ex * F[mj][0].y + ey * F[mj][1].y + ez * F[mj][2].y;
+                float f2 = 0.f;
+#pragma unroll
+                for (int comp = 0; comp < 3; ++comp) f2 += F[mj][comp].x * F[mj][comp].x + F[mj][comp].y * F[mj][comp].y;
+                val += f2 - (px * px + py * py);
+            }
+            if (P.ff_uniform) {
+                const float f = mag_ff(P.ff[0], s2);
+                val *= f * f;
+            }
+            val = q2 > 0.f ? val : 0.f;
+            if (m0 > 0) val += Iacc[r * cnt3 + i3];
+            if (!last) { Iacc[r * cnt3 + i3] = val; continue; }
+            const int i2 = G2 - P.g0[1];
+            const float o = val * P.scale;
+            orow0[(size_t)i2 * P.opitch] = o;
+            if (w.mirror) mrow0[(size_t)(P.cnt[1] - 1 - i2) * P.opitch] = o;
+        }
+    }
+}
+
+template <int MC>
+__global__ __launch_bounds__(kMagRowsMaxThreads) void k_recombine_magnetic_dw_rows(RecombParams P) { recombine_magnetic_dw_rows_body<MC, RecombParams>(P, blockIdx.x); }
+template <int MC>
+__global__ __launch_bounds__(kMagRowsMaxThreads) void k_recombine_magnetic_dw_rows_merged(const RecombParams* __restrict__ tab, const Slot* __restrict__ slots)
+{
+    int d, bx;
+    if (slot_of(slots, d, bx)) recombine_magnetic_dw_rows_body<MC, const RecombParams&>(tab[d], bx);
+}
+
+template <int MC>
+static hipError_t launch_mag_dw_rows(const RecombParams& p, int block, size_t lds, hipStream_t st)
+{
+    hipError_t e = set_lds(k_recombine_magnetic_dw_rows<MC>, lds);
+    if (e != hipSuccess) return e;
+    return dispatch(k_recombine_magnetic_dw_rows<MC>, k_recombine_magnetic_dw_rows_merged<MC>, p.nwork, block, lds, st, p);
+}
+
 template <bool MULTI, int NCT>
 static hipError_t launch_mag_rows_v(const RecombParams& p, int block, size_t lds, hipStream_t st)
 {
@@ -1560,6 +1719,14 @@ hipError_t launch_recombine_magnetic_rows(const RecombParams& p, int block, size
 {
     if (p.nwork <= 0) return hipSuccess;
     if (block < p.cnt[2] || block > kMagRowsMaxThreads || p.rows > kMagRowsMaxRows) return hipErrorInvalidValue;
+    if (p.dw_order > 0) {
+        switch (p.mg) {
+            case 1: return launch_mag_dw_rows<1>(p, block, lds, st);
+            case 2: return launch_mag_dw_rows<2>(p, block, lds, st);
+            case 4: return launch_mag_dw_rows<4>(p, block, lds, st);
+            default: return hipErrorInvalidValue;
+        }
+    }
     if (p.qmod > 0 && (p.qmod > p.nclass || p.nclass > kMagRowsMaxClasses)) return hipErrorInvalidValue;
     if (p.M > 1 && p.qmod1 > 0) return hipErrorInvalidValue;   // grouped planes: one configuration
     return p.M > 1 ? launch_mag_rows<true>(p, block, lds, st) : launch_mag_rows<false>(p, block, lds, st);

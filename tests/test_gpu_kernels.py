@@ -161,3 +161,24 @@ def test_oversampled_and_wide_filters(lm, mp, s, count):
     m.g0 = tuple(-(c - 1) // 2 if c % 2 else -1 for c in count)
     say(f"filter m={lm} m'={mp} s={s} box={m.g0}+{m.count}")
     assert_parity(gpu_filtered(m, lm, s, mp), O.filtered_intensity(m, lm, s, mprime=mp))
+
+
+# ------------------------------------------------------------------ magnetic, Debye-Waller rows form
+@pytest.mark.parametrize("S,M,order,n", [(1, 1, 1, (3, 4, 5)), (3, 4, 2, (4, 3, 6)), (5, 9, 3, (3, 3, 4)), (2, 2, 16, (2, 3, 3)),
+                                         (20, 3, 2, (2, 2, 9)), (64, 1, 3, (1, 2, 40)), (16, 5, 4, (2, 1, 64))])
+@pytest.mark.parametrize("box", ["symmetric", "offset", "long"])
+def test_debye_waller_rows(S, M, order, n, box):
+    """One, two and four configurations a pass, ragged last passes, uniform and separate form
+    factors, few rows a block, and G3 ranges past the threads of a block (the other form)."""
+    m = synth.random_model(2700 + S + M + order, n=n, S=S, M=M, kind=synth.MAGNETIC, mag_order=order, sigma=0.03,
+                           cell=[5.0, 6.0, 7.0, 90.0, 97.0, 90.0])
+    if S % 2:
+        m.ff[::2, 6] = 0.3
+    r = [v + 1 for v in n]
+    m.g0, m.count = {"symmetric": ([-v for v in r], [2 * v + 1 for v in r]), "offset": ([1, -r[1], -2], [r[0], 2 * r[1], n[2] + 3]),
+                     "long": ([0, 0, -2], [2, 2, 515])}[box]
+    if box == "long" and (n[2] > 9 or n[2] * -(-515 // n[2] // 17) > 512):
+        m.count[2] = 4 * n[2]
+    m.g0, m.count = tuple(m.g0), tuple(m.count)
+    say(f"Debye-Waller rows S={S} M={M} order={order} n={n} box={m.g0}+{m.count}")
+    sampled_parity(m, None, 1200)
