@@ -722,7 +722,7 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
         // rows whose H2 agree modulo q2 (every r_mu2 a multiple of 1/q2) share their site
         // phases e^{2 pi i g2 r_mu2}, so a block stages min(rows, q2) of them only; planes
         // whose H1 agree modulo q1 share e^{2 pi i g1 r_mu1}, and one block serves up to four
-        // of them (one configuration: the sums of several are accumulated per row)
+        // of them (where one pass takes all the configurations)
         auto grid_of = [&](int axis) {
             for (int cand : {1, 2, 3, 4, 6, 8}) {
                 bool ok = true;
@@ -735,23 +735,37 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
             return 0;
         };
         const int q2 = grid_of(1);
-        t.qmod2_mr = q2;
-        t.qmod1_mr = m->M == 1 ? grid_of(0) : 0;
-        int cs = S;
-        while (cs > 1 && (size_t)cs * 3 * n3 * sizeof(float2) > 12 * 1024) cs = (cs + 1) / 2;
-        const size_t budget = 48 * 1024 / sizeof(float2);
-        const size_t fixed = magnetic_rows_lds_elems(0, cs, S, NC, n3, t.nH3span);
-        const size_t per_row = magnetic_rows_lds_elems(1, 0, S, NC, n3, 0) - (size_t)S * n3;
-        // residue rows: every row of a column in one block when q2 staged rows fit; else the
-        // rows are staged one by one, as many as fit
-        if (q2 > 0 && fixed + std::min(q2, kMagRowsMaxRows) * per_row > budget) t.qmod2_mr = 0;
-        int rows;
-        if (t.qmod2_mr > 0)
-            rows = kMagRowsMaxRows;
-        else
-            rows = fixed < budget ? (int)((budget - fixed) / per_row) : 0;
-        rows = std::min(std::min(rows, kMagRowsMaxRows), maxH2);
-        if (rows >= 1) { t.rows_mr = rows; t.csites_mr = cs; }
+        const int q1 = grid_of(0);
+        // configurations a pass: four, two or one, the first that holds the row residues (or four
+        // rows staged one by one) in 32 KB.  Blocks in flight count for more than what a pass of
+        // several saves (16 sites, 40^3 cells, two configurations: one a pass in 30 KB 130 us, two
+        // in 47 KB 176), so larger passes are for small n3; one configuration takes up to 48 KB
+        for (int mc : {4, 2, 1}) {
+            if (mc > 1 && mc / 2 >= m->M) continue;
+            const bool passes = m->M > mc;
+            const size_t budget = (mc > 1 ? 32 : passes ? 64 : 48) * 1024 / sizeof(float2);
+            int cs = S;
+            while (cs > 1 && (size_t)mc * cs * 3 * n3 * sizeof(float2) > 12 * 1024) cs = (cs + 1) / 2;
+            // (every row takes its sums over the passes, staged or not)
+            const size_t fixed = magnetic_rows_lds_elems(mc, 0, cs, S, NC, n3, t.nH3span, 0);
+            const size_t per_row = magnetic_rows_lds_elems(mc, 1, 0, S, NC, n3, 0, 0);
+            const size_t per_sum = passes ? (size_t)(bx.cnt[2] + 1) / 2 : 0;
+            const int most = std::min(kMagRowsMaxRows, std::max(1, maxH2));
+            // residue rows: every row of a column in one block when q2 staged rows fit; else the
+            // rows are staged one by one, as many as fit
+            int qm2 = 0, rows = 0;
+            if (q2 > 0 && fixed + std::min(q2, most) * per_row + most * per_sum <= budget) {
+                qm2 = q2;
+                rows = most;
+            } else if (fixed < budget) {
+                rows = std::min(most, (int)((budget - fixed) / (per_row + per_sum)));
+            }
+            if (rows < 1 || (mc > 1 && rows < std::min(most, 4))) continue;
+            t.qmod2_mr = qm2;
+            t.qmod1_mr = passes ? 0 : q1;
+            t.rows_mr = rows; t.csites_mr = cs; t.mc_mr = mc;
+            break;
+        }
     }
     // the k3 with points in the box (a box shorter than the supercell has none on the others)
     t.nact3 = std::min(n3, bx.cnt[2]);
@@ -1047,12 +1061,14 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         p.nwork = tb->nwork_mr;
         p.rows = tb->rows_mr;
         p.csites = tb->csites_mr;
+        p.mg = tb->mc_mr;
         p.qmod = tb->qmod_mr;
         p.qmod2 = tb->qmod2_mr;
         p.qmod1 = tb->qmod1_mr;
         lp.block = std::max(64, (bx.cnt[2] + 63) / 64 * 64);
         const int staged = tb->qmod2_mr > 0 ? std::min(tb->rows_mr, tb->qmod2_mr) : tb->rows_mr;
-        lp.lds = sizeof(float2) * magnetic_rows_lds_elems(staged, tb->csites_mr, m->S, m->nclass, n3, tb->nH3span);
+        lp.lds = sizeof(float2) * magnetic_rows_lds_elems(p.mg, staged, tb->csites_mr, m->S, m->nclass, n3, tb->nH3span,
+                                                          m->M > p.mg ? p.rows * bx.cnt[2] : 0);
         staged_lds = lp.lds;
     }
     if (!mag) {

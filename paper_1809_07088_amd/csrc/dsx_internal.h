@@ -336,12 +336,13 @@ constexpr int kMagRowsMaxThreads = 512;
 constexpr int kMagRowsMaxRows = 16;
 constexpr int kMagRowsMaxClasses = 8;   // the per-residue class sums need q <= nclass <= this
 hipError_t launch_recombine_magnetic_rows(const RecombParams& p, int block, size_t lds, hipStream_t st);
-// float2 elements of its LDS for `rows` staged rows (a block's rows, or min(rows, qmod2)),
-// site chunks of csites, S sites, nclass classes
-inline size_t magnetic_rows_lds_elems(int rows, int csites, int S, int nclass, int n3, int nH3span)
+// float2 elements of its LDS for mc configurations a pass, `rows` staged rows (a block's rows, or
+// min(rows, qmod2)), site chunks of csites, S sites, nclass classes, `sums` floats for the sums of
+// several passes
+inline size_t magnetic_rows_lds_elems(int mc, int rows, int csites, int S, int nclass, int n3, int nH3span, int sums)
 {
-    return (size_t)rows * nclass * 3 * n3 + (size_t)S * n3 + (size_t)rows * S + (size_t)nclass * nH3span
-         + (size_t)csites * 3 * n3;
+    return (size_t)mc * rows * nclass * 3 * n3 + (size_t)rows * S + (size_t)nclass * nH3span
+         + (size_t)mc * csites * 3 * n3 + (sums + 1) / 2;
 }
 // float2 elements of the LDS of its form with Debye-Waller factors of order N: mc configurations
 // at a time, `sums` floats for the sums of several passes

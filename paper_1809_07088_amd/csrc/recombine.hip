@@ -1285,7 +1285,10 @@ __device__ __forceinline__ void cmac(float2& acc, float2 a, float2 b) {
 
 // NCT: the number of r3 classes when the classes are summed per residue of H3 mod q
 // (then at most kMagRowsMaxClasses, and the residue sums unroll over it), else 0.
-template <bool MULTI, int NCT, class PT>
+// MC: configurations a pass takes (their sums side by side in LDS, a voxel's |Q|, form factor and
+// projection worked out once for them); more than MC are added up over the passes in LDS, and
+// only then do planes not share a block.
+template <int MC, int NCT, class PT>
 __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
 {
     extern __shared__ float2 smem[];
@@ -1300,17 +1303,14 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
     // staged rows: with every r_mu2 a multiple of 1/q2, row r has the site phases of row
     // r mod q2 (their H2 differ by a multiple of q2), so only the first q2 are staged
     const int rowsB = q2 > 0 ? min(rows, q2) : rows;
-    float2* D = smem;                              // [rowsB][NC][3][n3]; then E [rowsB][q][3][n3]
-    float2* tK3 = D + rowsB * NC * 3 * n3;         // [S][n3]   (sorted positions)
-    float2* t2 = tK3 + S * n3;                     // [rowsB][S]
+    const int Dm = rowsB * NC * 3 * n3;            // one configuration's
+    float2* D = smem;                              // [MC][rowsB][NC][3][n3]; then E [MC][rowsB][q][3][n3]
+    float2* t2 = D + MC * Dm;                      // [rowsB][S]
     float2* tHs = t2 + rowsB * S;                  // [NC][nH3span]
-    float2* Bs = tHs + NC * P.nH3span;             // [csites][3][n3]
+    float2* Bs = tHs + NC * P.nH3span;             // [MC][csites][3][n3]
+    float* Iacc = reinterpret_cast<float*>(Bs + MC * P.csites * 3 * n3);   // [rows][cnt3], several passes only
     const float2* tH0 = stage_class_phases(P, tHs);
     const float rn3 = 1.f / (float)n3, rS = 1.f / (float)S, rNC = 1.f / (float)NC;
-    for (int idx = threadIdx.x; idx < S * n3; idx += blockDim.x) {
-        const int i = qdiv_r(idx, n3, rn3), k = idx - i * n3;
-        tK3[idx] = P.tabK3[(size_t)P.site_of[i] * n3 + k];
-    }
     for (int idx = threadIdx.x; idx < rowsB * S; idx += blockDim.x) {
         const int r = qdiv_r(idx, S, rS), i = idx - r * S;
         const int i2 = w.k2 + n2 * (w.H2lo + w.h2a + r) - P.g0[1];
@@ -1349,33 +1349,37 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
         }
     }
     const size_t plane = (size_t)P.cnt[1] * P.opitch;
-    float I[MULTI ? kMagRowsMaxRows : 1];
-#pragma unroll
-    for (int r = 0; r < (MULTI ? kMagRowsMaxRows : 1); ++r) I[r] = 0.f;
-
-    for (int m = 0; m < P.M; ++m) {
-        const float2* Xm = P.X + (size_t)m * n1 * n2 * SFnh;
+    const size_t cstride = (size_t)n1 * n2 * SFnh;
+    for (int m0 = 0; m0 < P.M; m0 += MC) {
+        const int mc = MC == 1 ? 1 : min(MC, P.M - m0);
+        const bool last = MC == 1 ? m0 + 1 >= P.M : m0 + MC >= P.M;
         __syncthreads();
-        for (int idx = threadIdx.x; idx < rowsB * NC * 3 * n3; idx += blockDim.x) D[idx] = make_float2(0.f, 0.f);
+        for (int idx = threadIdx.x; idx < MC * Dm; idx += blockDim.x) D[idx] = make_float2(0.f, 0.f);
         for (int s0 = 0; s0 < S; s0 += P.csites) {
             const int ns = min(P.csites, S - s0);
             __syncthreads();
             // level A (with the k3 phase of the site)
-            for (int idx = threadIdx.x; idx < ns * 3 * n3; idx += blockDim.x) {
-                const int rj = qdiv_r(idx, n3, rn3);
-                const int kk = idx - rj * n3;
+            const float rs3 = 1.f / (float)(3 * ns);
+            for (int idx = threadIdx.x; idx < mc * ns * 3 * n3; idx += blockDim.x) {
+                const int mrj = qdiv_r(idx, n3, rn3);
+                const int kk = idx - mrj * n3;
+                const int mj = MC == 1 ? 0 : qdiv_r(mrj, 3 * ns, rs3), rj = mrj - mj * 3 * ns;
                 const int sl = rj / 3, comp = rj - 3 * sl;
-                const size_t f = ((size_t)P.site_of[s0 + sl] * 3 + comp) * nh;
+                const int mu = P.site_of[s0 + sl];
+                const float2* Xm = P.X + (size_t)(m0 + mj) * cstride;
+                const size_t f = ((size_t)mu * 3 + comp) * nh;
                 float2 x;
                 if (kk < nh) x = Xm[col + f + kk];
                 else { x = Xm[colm + f + (n3 - kk)]; x.y = -x.y; }
-                Bs[idx] = cmulf(cmulf(t1s[s0 + sl], tK3[(s0 + sl) * n3 + kk]), x);
+                Bs[idx] = cmulf(cmulf(t1s[s0 + sl], P.tabK3[(size_t)mu * n3 + kk]), x);
             }
             __syncthreads();
-            // level B: one (row, class, k3) per thread, the chunk's sites of the class
-            for (int idx = threadIdx.x; idx < rowsB * NC * n3; idx += blockDim.x) {
-                const int rc = qdiv_r(idx, n3, rn3);
-                const int kk = idx - rc * n3;
+            // level B: one (configuration, row, class, k3) per thread, the chunk's sites of the class
+            const float rrc = 1.f / (float)(rowsB * NC);
+            for (int idx = threadIdx.x; idx < mc * rowsB * NC * n3; idx += blockDim.x) {
+                const int mrc = qdiv_r(idx, n3, rn3);
+                const int kk = idx - mrc * n3;
+                const int mj = MC == 1 ? 0 : qdiv_r(mrc, rowsB * NC, rrc), rc = mrc - mj * rowsB * NC;
                 const int r = qdiv_r(rc, NC, rNC);
                 const int c = rc - r * NC;
                 const int i0 = max(cls[c], s0), i1 = min(cls[c + 1], s0 + ns);
@@ -1383,11 +1387,11 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
                 float2 acc[3] = {make_float2(0.f, 0.f), make_float2(0.f, 0.f), make_float2(0.f, 0.f)};
                 for (int i = i0; i < i1; ++i) {
                     const float2 ph = t2[r * S + i];
-                    const float2* b = Bs + (size_t)(i - s0) * 3 * n3 + kk;
+                    const float2* b = Bs + (size_t)(mj * ns + i - s0) * 3 * n3 + kk;
 #pragma unroll
                     for (int comp = 0; comp < 3; ++comp) cmac(acc[comp], ph, b[comp * n3]);
                 }
-                float2* d = D + (size_t)rc * 3 * n3 + kk;
+                float2* d = D + (size_t)mrc * 3 * n3 + kk;
 #pragma unroll
                 for (int comp = 0; comp < 3; ++comp) {
                     d[comp * n3].x += acc[comp].x;
@@ -1400,7 +1404,7 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
         // thread reads its NCT classes' D, then writes E over the first q of them (the
         // block's q x NCT phases staged once; a residue with no H3 in the box stays 0)
         if constexpr (NCT > 0) {
-            if (m == 0) {
+            if (m0 == 0) {
                 for (int t = threadIdx.x; t < NCT * NCT; t += blockDim.x) {
                     const int j = t / NCT, c = t - j * NCT;
                     const int h = P.H3min + ((j - P.H3min) % q + q) % q;   // an H3 of residue j
@@ -1408,7 +1412,7 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
                 }
                 __syncthreads();
             }
-            for (int idx = threadIdx.x; idx < rowsB * 3 * n3; idx += blockDim.x) {
+            for (int idx = threadIdx.x; idx < mc * rowsB * 3 * n3; idx += blockDim.x) {
                 const int rc = qdiv_r(idx, n3, rn3);
                 const int kk = idx - rc * n3;
                 const int r = rc / 3, comp = rc - 3 * r;
@@ -1456,14 +1460,18 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
                 const float qz = q13z + g2 * P.recip[5];
                 const float q2 = qx * qx + qy * qy + qz * qz;
                 const float s2 = q2 * inv16pi2;
-                float2 F[3];
+                float2 F[MC][3];
                 if (NCT > 0) {
                     const float2* e = D + rd * erow + ebase;
 #pragma unroll
-                    for (int comp = 0; comp < 3; ++comp) F[comp] = e[comp * n3];
+                    for (int mj = 0; mj < MC; ++mj)
+#pragma unroll
+                        for (int comp = 0; comp < 3; ++comp) F[mj][comp] = e[mj * Dm + comp * n3];
                 } else {
 #pragma unroll
-                    for (int comp = 0; comp < 3; ++comp) F[comp] = make_float2(0.f, 0.f);
+                    for (int mj = 0; mj < MC; ++mj)
+#pragma unroll
+                        for (int comp = 0; comp < 3; ++comp) F[mj][comp] = make_float2(0.f, 0.f);
                     const float2* d = D + (size_t)rd * NC * 3 * n3 + k3;
                     const float2* th = tH0 + H3;
                     for (int c = 0; c < NC; ++c) {
@@ -1473,16 +1481,25 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
                             e3.x *= f; e3.y *= f;
                         }
 #pragma unroll
-                        for (int comp = 0; comp < 3; ++comp) cmac(F[comp], e3, d[(c * 3 + comp) * n3]);
+                        for (int mj = 0; mj < MC; ++mj)
+#pragma unroll
+                            for (int comp = 0; comp < 3; ++comp) cmac(F[mj][comp], e3, d[mj * Dm + (c * 3 + comp) * n3]);
                     }
                 }
-                // |F_perp|^2 = |F|^2 - |Q.F|^2 / |Q|^2 (0 at Q = 0), times f(|Q|)^2
-                const float pr = qx * F[0].x + qy * F[1].x + qz * F[2].x;
-                const float pim = qx * F[0].y + qy * F[1].y + qz * F[2].y;
-                float f2 = 0.f;
+                // |F_perp|^2 = |F|^2 - |Q.F|^2 / |Q|^2 (0 at Q = 0), times f(|Q|)^2 (a
+                // configuration past the last has zero sums)
+                float val = 0.f;
+                const float rq2 = __builtin_amdgcn_rcpf(q2);
 #pragma unroll
-                for (int comp = 0; comp < 3; ++comp) f2 += F[comp].x * F[comp].x + F[comp].y * F[comp].y;
-                float val = fmaf(-(pr * pr + pim * pim), __builtin_amdgcn_rcpf(q2), f2);
+                for (int mj = 0; mj < MC; ++mj) {
+                    const float pr = qx * F[mj][0].x + qy * F[mj][1].x + qz * F[mj][2].x;
+                    const float pim = qx * F[mj][0].y + qy * F[mj][1].y + qz * F[mj][2].y;
+                    float f2 = 0.f;
+#pragma unroll
+                    for (int comp = 0; comp < 3; ++comp) f2 += F[mj][comp].x * F[mj][comp].x + F[mj][comp].y * F[mj][comp].y;
+                    const float v = fmaf(-(pr * pr + pim * pim), rq2, f2);
+                    val = mj == 0 ? v : val + v;
+                }
                 if (sep) {
                     const float4 e2 = ffrow[r];
                     const float f = fmaf(e13a, e2.x, fmaf(e13b, e2.y, fmaf(e13c, e2.z, P.ff[0][6])));
@@ -1492,44 +1509,25 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
                     val *= f * f;
                 }
                 val = q2 > 0.f ? val : 0.f;
-                if constexpr (MULTI) {
-#pragma unroll
-                    for (int rr = 0; rr < kMagRowsMaxRows; ++rr)
-                        if (rr == r) I[rr] += val;
-                } else {
-                    const int i2 = G2 - P.g0[1];
-                    const float o = val * P.scale;
-                    orow0[(size_t)i2 * P.opitch] = o;
-                    if (mirror) mrow0[(size_t)(P.cnt[1] - 1 - i2) * P.opitch] = o;
-                }
-            }
-        }
-    }
-    if constexpr (MULTI) {
-        // several configurations: one plane per block (the planner groups no planes)
-        float* const orow0 = P.out + P.ooff + (size_t)w.i1 * plane + i3;
-        float* const mrow0 = P.out + P.ooff + (size_t)(P.cnt[0] - 1 - w.i1) * plane + (P.cnt[2] - 1 - i3);
-        if (active) {
-#pragma unroll
-            for (int r = 0; r < kMagRowsMaxRows; ++r) {
-                if (r < rows) {
-                    const int i2 = w.k2 + n2 * (w.H2lo + w.h2a + r) - P.g0[1];
-                    const float o = I[r] * P.scale;
-                    orow0[(size_t)i2 * P.opitch] = o;
-                    if (w.mirror) mrow0[(size_t)(P.cnt[1] - 1 - i2) * P.opitch] = o;
-                }
+                // (several passes: one plane per block, the sums so far in the thread's own places)
+                if (m0 > 0) val += Iacc[r * cnt3 + i3];
+                if (!last) { Iacc[r * cnt3 + i3] = val; continue; }
+                const int i2 = G2 - P.g0[1];
+                const float o = val * P.scale;
+                orow0[(size_t)i2 * P.opitch] = o;
+                if (mirror) mrow0[(size_t)(P.cnt[1] - 1 - i2) * P.opitch] = o;
             }
         }
     }
 }
 
-template <bool MULTI, int NCT>
-__global__ __launch_bounds__(kMagRowsMaxThreads) void k_recombine_magnetic_rows(RecombParams P) { recombine_magnetic_rows_body<MULTI, NCT, RecombParams>(P, blockIdx.x); }
-template <bool MULTI, int NCT>
+template <int MC, int NCT>
+__global__ __launch_bounds__(kMagRowsMaxThreads) void k_recombine_magnetic_rows(RecombParams P) { recombine_magnetic_rows_body<MC, NCT, RecombParams>(P, blockIdx.x); }
+template <int MC, int NCT>
 __global__ __launch_bounds__(kMagRowsMaxThreads) void k_recombine_magnetic_rows_merged(const RecombParams* __restrict__ tab, const Slot* __restrict__ slots)
 {
     int d, bx;
-    if (slot_of(slots, d, bx)) recombine_magnetic_rows_body<MULTI, NCT, const RecombParams&>(tab[d], bx);
+    if (slot_of(slots, d, bx)) recombine_magnetic_rows_body<MC, NCT, const RecombParams&>(tab[d], bx);
 }
 
 // Magnetic sites with Debye-Waller factors, rows form: blocks and threads as above (one plane), but
@@ -1691,27 +1689,27 @@ static hipError_t launch_mag_dw_rows(const RecombParams& p, int block, size_t ld
     return dispatch(k_recombine_magnetic_dw_rows<MC>, k_recombine_magnetic_dw_rows_merged<MC>, p.nwork, block, lds, st, p);
 }
 
-template <bool MULTI, int NCT>
+template <int MC, int NCT>
 static hipError_t launch_mag_rows_v(const RecombParams& p, int block, size_t lds, hipStream_t st)
 {
-    hipError_t e = set_lds(k_recombine_magnetic_rows<MULTI, NCT>, lds);
+    hipError_t e = set_lds(k_recombine_magnetic_rows<MC, NCT>, lds);
     if (e != hipSuccess) return e;
-    return dispatch(k_recombine_magnetic_rows<MULTI, NCT>, k_recombine_magnetic_rows_merged<MULTI, NCT>, p.nwork, block,
+    return dispatch(k_recombine_magnetic_rows<MC, NCT>, k_recombine_magnetic_rows_merged<MC, NCT>, p.nwork, block,
                     lds, st, p);
 }
 
-template <bool MULTI>
+template <int MC>
 static hipError_t launch_mag_rows(const RecombParams& p, int block, size_t lds, hipStream_t st)
 {
     // residue sums for up to four classes (the unrolled sums keep the block's q x NC
     // phases in registers); more classes, or no residue grid, take level C per class,
     // which is exact for any q
-    if (p.qmod <= 0 || p.nclass > 4) return launch_mag_rows_v<MULTI, 0>(p, block, lds, st);
+    if (p.qmod <= 0 || p.nclass > 4) return launch_mag_rows_v<MC, 0>(p, block, lds, st);
     switch (p.nclass) {
-        case 1: return launch_mag_rows_v<MULTI, 1>(p, block, lds, st);
-        case 2: return launch_mag_rows_v<MULTI, 2>(p, block, lds, st);
-        case 3: return launch_mag_rows_v<MULTI, 3>(p, block, lds, st);
-        default: return launch_mag_rows_v<MULTI, 4>(p, block, lds, st);
+        case 1: return launch_mag_rows_v<MC, 1>(p, block, lds, st);
+        case 2: return launch_mag_rows_v<MC, 2>(p, block, lds, st);
+        case 3: return launch_mag_rows_v<MC, 3>(p, block, lds, st);
+        default: return launch_mag_rows_v<MC, 4>(p, block, lds, st);
     }
 }
 
@@ -1728,8 +1726,13 @@ hipError_t launch_recombine_magnetic_rows(const RecombParams& p, int block, size
         }
     }
     if (p.qmod > 0 && (p.qmod > p.nclass || p.nclass > kMagRowsMaxClasses)) return hipErrorInvalidValue;
-    if (p.M > 1 && p.qmod1 > 0) return hipErrorInvalidValue;   // grouped planes: one configuration
-    return p.M > 1 ? launch_mag_rows<true>(p, block, lds, st) : launch_mag_rows<false>(p, block, lds, st);
+    if (p.M > p.mg && p.qmod1 > 0) return hipErrorInvalidValue;   // grouped planes: one pass
+    switch (p.mg) {
+        case 1: return launch_mag_rows<1>(p, block, lds, st);
+        case 2: return launch_mag_rows<2>(p, block, lds, st);
+        case 4: return launch_mag_rows<4>(p, block, lds, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 // ---------------------------------------------------------------------------- direct form

@@ -182,3 +182,20 @@ def test_debye_waller_rows(S, M, order, n, box):
     m.g0, m.count = tuple(m.g0), tuple(m.count)
     say(f"Debye-Waller rows S={S} M={M} order={order} n={n} box={m.g0}+{m.count}")
     sampled_parity(m, None, 1200)
+
+
+# ------------------------------------------------------------------ magnetic rows, several configurations
+@pytest.mark.parametrize("S,M,r", [(4, 2, 0.5), (4, 3, 0.5), (8, 4, 0.25), (3, 5, 1 / 3), (5, 9, None), (64, 2, None), (2, 6, 1.0)])
+@pytest.mark.parametrize("n", [(4, 3, 6), (3, 2, 64)])
+@pytest.mark.parametrize("box", ["symmetric", "offset", "wide"])
+def test_magnetic_rows_configurations(S, M, r, n, box):
+    """One, two and four configurations a pass, one and several passes, planes grouped (sites on a
+    grid) and not, residue sums and separate classes."""
+    m = synth.random_model(2800 + S + M, n=n, S=S, M=M, kind=synth.MAGNETIC, cell=[6.0, 7.0, 8.0, 90.0, 90.0, 90.0])
+    if r is not None:
+        m.frac = np.round(m.frac / r) * r
+    m.g0, m.count = {"symmetric": ([-9, -7, -n[2] - 2], [19, 15, 2 * n[2] + 5]), "offset": ([2, -5, 1], [14, 9, n[2]]),
+                     "wide": ([-1, -1, -150], [3, 3, 300 if S == 64 else 500])}[box]
+    m.g0, m.count = tuple(m.g0), tuple(m.count)
+    say(f"magnetic rows S={S} M={M} grid={r} n={n} box={m.g0}+{m.count}")
+    sampled_parity(m, None, 1500)
