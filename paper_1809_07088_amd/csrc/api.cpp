@@ -1243,7 +1243,7 @@ dsx_status ensure_spectra(dsx_model m, hipStream_t st, bool force = false)
     const long long planes = (long long)m->M * m->S * m->n[0];
     bool by_rows = false;
     const bool fixed = fft_reg_supported(m->n[1]) && fft_reg_supported(m->n[2]);
-    if (!fixed && split_length(m->n[2], &pp.a3, &pp.b3) && split_length(m->n[1], &pp.a2, &pp.b2)) {
+    if (!fixed && split_length(m->n[2], &pp.a3, &pp.b3, kMaxPlanePrime) && split_length(m->n[1], &pp.a2, &pp.b2, kMaxPlanePrime)) {
         plan_plane_regs(m, planes, pp);
         by_rows = pp.row_pairs > 0;
     } else {
@@ -2414,9 +2414,10 @@ dsx_status dsx_autotune(dsx_model m, int32_t lanczos_m, void* hip_stream)
         // FFT radix orders of the axes the LDS kernels transform (the register kernels of
         // edges 8, 16, 32 have a fixed order), one axis at a time
         // (the register transforms have one order: only the Stockham passes are tuned)
-        const auto reg = [](int n) { int a, b; return split_length(n, &a, &b); };
+        const auto reg = [](int n, int prime) { int a, b; return split_length(n, &a, &b, prime); };
         for (int a : {2, 1, 0}) {
-            const bool used = a == 0 ? !reg(m->n[0]) : !(reg(m->n[1]) && reg(m->n[2]));
+            const bool used = a == 0 ? !reg(m->n[0], kMaxRegPrime)
+                                     : !(reg(m->n[1], kMaxPlanePrime) && reg(m->n[2], kMaxPlanePrime));
             if (!used) continue;
             const std::vector<AxisPlan> cands = plan_candidates(m->n[a], 12);
             if (cands.size() < 2) continue;

@@ -25,14 +25,20 @@ struct AxisPlan {
     int32_t rad[kMaxRadices];
 };
 
-// Lengths the register transforms take: n = A B with A, B <= kMaxRegRadix, one pass of
-// length-A transforms and one of length-B ones (B = 1: a single pass).  The most even split is
-// taken (least work and fewest registers per thread).  False where a prime factor, or what is
-// left over, exceeds kMaxRegRadix.
-constexpr int kMaxRegRadix = 16;
-inline bool split_length(int n, int* A, int* B)
+// Lengths the register transforms take: n = A B, one pass of length-A transforms and one of
+// length-B ones (B = 1: a single pass), A and B <= kMaxRegRadix, or A a prime up to
+// kMaxRegPrime (kMaxPlanePrime in the plane kernel, whose lines of 53 to 61 points spill).  The
+// most even split is taken (least work and fewest registers per thread).  False for the other
+// lengths up to 256: those with a larger prime factor, and a few products like 5^3 or 2 5^3.
+constexpr int kMaxRegRadix = 16, kMaxRegPrime = 61, kMaxPlanePrime = 47;
+inline bool split_length(int n, int* A, int* B, int max_prime = kMaxRegPrime)
 {
     if (n <= kMaxRegRadix) { *A = n; *B = 1; return true; }
+    for (int p = max_prime; p > kMaxRegRadix; --p) {
+        bool prime = p % 2 != 0;
+        for (int f = 3; prime && f * f <= p; f += 2) prime = p % f != 0;
+        if (prime && n % p == 0) { *A = p; *B = n / p; return *B <= kMaxRegRadix; }
+    }
     for (int b = 1; b * b <= n; ++b)
         if (n % b == 0) { *A = n / b; *B = b; }
     return *A <= kMaxRegRadix;

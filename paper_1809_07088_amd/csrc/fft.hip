@@ -552,7 +552,7 @@ __global__ __launch_bounds__(256) void k_fft_rows_merged(const PlaneParams* __re
 
 // ---------------------------------------------------------------------------- register lines
 // Lengths n = A B with A, B <= kMaxRegRadix (powers of two up to 256, 10, 12, 18, 20, 24, 40,
-// 96, ...): each thread transforms A (then B) points in registers, so a line takes one or two
+// 96, ...) or A a prime up to kMaxRegPrime: each thread transforms A (then B) points in registers, so a line takes one or two
 // passes where the Stockham form takes one per radix, and its indices, twiddles and barriers
 // are paid once per A or B points.  The transform of A points is unrolled at compile time
 // (fours first, then the smallest prime; primes above 5 through the cosine and sine sums of
@@ -685,6 +685,53 @@ __device__ __forceinline__ void fft_small(float2 (&z)[N])
     }
 }
 
+// The transform of length N of z, each value handed to put(k, X_k) (z is overwritten).  Primes
+// above kMaxRegRadix: the sums and differences of the pairs take z's place and every output is
+// put as soon as it is formed, so a thread holds the line once (2 N registers), not twice.
+template <int N, class Put>
+__device__ __forceinline__ void fft_line(float2 (&z)[N], Put put)
+{
+    if constexpr (N <= kMaxRegRadix) {
+        fft_small<N>(z);
+#pragma unroll
+        for (int k = 0; k < N; ++k) put(k, z[k]);
+    } else {
+        constexpr TwTable<N> tb = tw_table<N>();
+        constexpr int H = (N - 1) / 2;
+        float2 x0 = z[0];
+#pragma unroll
+        for (int r = 1; r <= H; ++r) {
+            const float2 a = z[r], b = z[N - r];
+            z[r] = cadd(a, b);
+            z[N - r] = csub(a, b);
+            x0 = cadd(x0, z[r]);
+        }
+        put(0, x0);
+#pragma unroll
+        for (int k = 1; k <= H; ++k) {
+            float2 e = z[0], o = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int r = 1; r <= H; ++r) {
+                const float c = tb.c[(r * k) % N], s = tb.s[(r * k) % N];
+                e.x = fmaf(c, z[r].x, e.x);
+                e.y = fmaf(c, z[r].y, e.y);
+                o.x = fmaf(-s, z[N - r].y, o.x);
+                o.y = fmaf(s, z[N - r].x, o.y);
+            }
+            put(k, cadd(e, o));
+            put(N - k, csub(e, o));
+            __builtin_amdgcn_sched_barrier(0);       // one pair of outputs at a time in registers
+        }
+    }
+}
+
+// Long lines: addresses for eight loads at a time, not for the whole line.
+template <int N>
+__device__ __forceinline__ void load_fence(int i)
+{
+    if (N > kMaxRegRadix && (i & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+}
+
 // x as it is, its derivation hidden from the compiler: base + i * stride then stays one add per
 // element instead of a product rebuilt for each
 __device__ __forceinline__ int opaque(int x)
@@ -699,10 +746,33 @@ __device__ __forceinline__ float2* opaque(float2* p)
     return p;
 }
 
-// f(std::integral_constant<int, n>) for the run-time (block-uniform) n in 1..kMaxRegRadix
-template <class F>
+// f(std::integral_constant<int, n>) for the run-time (block-uniform) n in 1..kMaxRegRadix, and,
+// with BIG > 0, the primes above it up to BIG (kernels of their own: their lines take more registers)
+template <int BIG = 0, class F>
 __device__ __forceinline__ void with_radix(int n, F f)
 {
+    if constexpr (BIG >= 61) {
+        switch (n) {
+            case 53: f(std::integral_constant<int, 53>{}); return;
+            case 59: f(std::integral_constant<int, 59>{}); return;
+            case 61: f(std::integral_constant<int, 61>{}); return;
+            default: break;
+        }
+    }
+    if constexpr (BIG >= 47) {
+        switch (n) {
+            case 17: f(std::integral_constant<int, 17>{}); return;
+            case 19: f(std::integral_constant<int, 19>{}); return;
+            case 23: f(std::integral_constant<int, 23>{}); return;
+            case 29: f(std::integral_constant<int, 29>{}); return;
+            case 31: f(std::integral_constant<int, 31>{}); return;
+            case 37: f(std::integral_constant<int, 37>{}); return;
+            case 41: f(std::integral_constant<int, 41>{}); return;
+            case 43: f(std::integral_constant<int, 43>{}); return;
+            case 47: f(std::integral_constant<int, 47>{}); return;
+            default: break;
+        }
+    }
     switch (n) {
         case 1: f(std::integral_constant<int, 1>{}); break;
         case 2: f(std::integral_constant<int, 2>{}); break;
@@ -728,6 +798,7 @@ __device__ __forceinline__ void with_radix(int n, F f)
 // the lines along axis 3.  Line l = b nj + jj (b = pl nfb + fb) holds Z_k, k < n3, at
 // Q[l lp + k]; its two half spectra are separated by whoever reads it (unpack_row).  A is
 // the other buffer.  Lanes run over the lines (lp odd): no bank conflicts at any n3.
+template <bool BIG>
 __device__ __forceinline__ void plane_lines(const PlaneParams& P, float2* A, float2* Q, const float2* tw3, const float* meanf, const int* expo, int m, int mu,
                             int R1, int npl, int j0, int nj, int fa, int nfb)
 {
@@ -819,7 +890,7 @@ __device__ __forceinline__ void plane_lines(const PlaneParams& P, float2* A, flo
     __syncthreads();
     const int A3 = P.a3, B3 = P.b3;
     const float rnl = 1.f / (float)nl;
-    with_radix(A3, [&](auto len) {
+    with_radix<BIG ? kMaxPlanePrime : 0>(A3, [&](auto len) {
         constexpr int R = decltype(len)::value;
 #pragma unroll 1
         for (int it = threadIdx.x; it < nl * B3; it += T) {
@@ -827,8 +898,19 @@ __device__ __forceinline__ void plane_lines(const PlaneParams& P, float2* A, flo
             const int line = opaque(l * lp), a0 = line + j;
             float2 z[R];
 #pragma unroll
-            for (int i = 0; i < R; ++i) z[i] = A[a0 + i * B3];
-            fft_small<R>(z);
+            for (int i = 0; i < R; ++i) {
+                z[i] = A[a0 + i * B3];
+                load_fence<R>(i);
+            }
+            if constexpr (R > kMaxRegRadix) {
+                fft_line<R>(z, [&](int k, float2 v) {
+                    if (B3 > 1) A[a0 + k * B3] = cmul(v, tw3[j * k]);
+                    else Q[line + k] = v;
+                });
+                continue;
+            } else {
+                fft_small<R>(z);
+            }
             if (B3 > 1) {
                 // (in place: y_j[k] takes the place of x[j + B k])
 #pragma unroll
@@ -888,7 +970,7 @@ __device__ __forceinline__ void group_chunk(int bx, int ng, int nc, int& g, int&
 }
 
 // Plane transforms of any A B edges: generation, axis 3, axis 2, written to the spectra.
-template <class PT>
+template <bool BIG, class PT>
 __device__ __forceinline__ void plane_regs_body(PT P, const int bx)
 {
     extern __shared__ float2 smem[];
@@ -925,7 +1007,7 @@ __device__ __forceinline__ void plane_regs_body(PT P, const int bx)
         meanf[threadIdx.x] = (float)(gptr(P.sums)[(size_t)(m * P.S + mu) * P.T + t] / (double)(P.n1 * n2 * n3));
     }
     __syncthreads();
-    plane_lines(P, A, Q, tw3, meanf, expo, m, mu, R1, npl, j0, nj, fa, nfb);
+    plane_lines<BIG>(P, A, Q, tw3, meanf, expo, m, mu, R1, npl, j0, nj, fa, nfb);
     // one (k1, k2) column of the spectra (scalar: steps between columns are scalar offsets)
     const int col = __builtin_amdgcn_readfirstlane(P.S * P.F * nh);
     const int run = nfb * nh;                       // contiguous in the spectra for each (k1, k2)
@@ -944,7 +1026,7 @@ __device__ __forceinline__ void plane_regs_body(PT P, const int bx)
     const int A2 = P.a2, B2 = P.b2;
     const int colA = __builtin_amdgcn_readfirstlane(A2 * col), B2nh = B2 * nh;
     const float rB2 = 1.f / (float)B2, rA2 = 1.f / (float)A2;
-    with_radix(A2, [&](auto len) {
+    with_radix<BIG ? kMaxPlanePrime : 0>(A2, [&](auto len) {
         constexpr int R = decltype(len)::value;
 #pragma unroll 1
         for (int it = threadIdx.x; it < npl * B2 * run; it += T) {
@@ -958,8 +1040,19 @@ __device__ __forceinline__ void plane_regs_body(PT P, const int bx)
             for (int i = 0; i < R; ++i) {
                 const int row = j + B2 * i;
                 z[i] = unpack_row(Z + __umul24(row >> 1, lp), k3, n3, row & 1);
+                load_fence<R>(i);
             }
-            fft_small<R>(z);
+            if constexpr (R > kMaxRegRadix) {
+                const int a0 = opaque((bi * n2 + j) * nh + k3);
+                float2* const o = opaque(out + (size_t)pl * n2 * col + e);
+                fft_line<R>(z, [&](int k, float2 v) {
+                    if (B2 > 1) A[a0 + k * B2nh] = cmul(v, tw2[j * k]);
+                    else stg2(o + k * (size_t)col, 0, v);
+                });
+                continue;
+            } else {
+                fft_small<R>(z);
+            }
             if (B2 > 1) {
                 const int a0 = opaque((bi * n2 + j) * nh + k3);
 #pragma unroll
@@ -995,17 +1088,19 @@ __device__ __forceinline__ void plane_regs_body(PT P, const int bx)
 }
 
 // (at most 96 VGPRs: the transforms of up to 16 points fit, and two 512-thread blocks or more share a CU)
-__global__ __launch_bounds__(512, 5) void k_plane_regs(PlaneParams P) { plane_regs_body<PlaneParams>(P, blockIdx.x); }
-__global__ __launch_bounds__(512, 5) void k_plane_regs_merged(const PlaneParams* __restrict__ tab, const Slot* __restrict__ slots)
+template <bool BIG>
+__global__ __launch_bounds__(512, BIG ? 3 : 5) void k_plane_regs(PlaneParams P) { plane_regs_body<BIG, PlaneParams>(P, blockIdx.x); }
+template <bool BIG>
+__global__ __launch_bounds__(512, BIG ? 3 : 5) void k_plane_regs_merged(const PlaneParams* __restrict__ tab, const Slot* __restrict__ slots)
 {
     int d, bx;
-    if (slot_of(slots, d, bx)) plane_regs_body<const PlaneParams&>(tab[d], bx);
+    if (slot_of(slots, d, bx)) plane_regs_body<BIG, const PlaneParams&>(tab[d], bx);
 }
 
 // Axis 1 in place for n1 = A B: a thread loads A values of a column straight into registers
 // (the lanes' columns are contiguous), transforms them, and exchanges them through LDS for its
 // B values of the second pass: one read and one write of the spectra, one barrier.
-template <class PT>
+template <bool BIG, class PT>
 __device__ __forceinline__ void axis1_regs_body(PT P, const int bx)
 {
     extern __shared__ float2 smem[];
@@ -1023,7 +1118,7 @@ __device__ __forceinline__ void axis1_regs_body(PT P, const int bx)
         for (int i = threadIdx.x; i < n1; i += blockDim.x) tw[i] = ldg2(P.tw1, i);
         __syncthreads();
     }
-    with_radix(A1, [&](auto len) {
+    with_radix<BIG ? kMaxRegPrime : 0>(A1, [&](auto len) {
         constexpr int R = decltype(len)::value;
         for (int it = threadIdx.x; it < tc * B1; it += blockDim.x) {
             const int j = qdiv(it, tc, rtc), c = it - j * tc;
@@ -1031,8 +1126,20 @@ __device__ __forceinline__ void axis1_regs_body(PT P, const int bx)
             float2* const src = opaque(base + (size_t)j * rowstride + c);
             float2 z[R];
 #pragma unroll
-            for (int i = 0; i < R; ++i) z[i] = ldg2(src + i * rowB, 0);
-            fft_small<R>(z);
+            for (int i = 0; i < R; ++i) {
+                z[i] = ldg2(src + i * rowB, 0);
+                load_fence<R>(i);
+            }
+            if constexpr (R > kMaxRegRadix) {
+                const int w0 = opaque(it);
+                fft_line<R>(z, [&](int k, float2 v) {
+                    if (B1 > 1) W[w0 + k * B1 * tc] = cmul(v, tw[j * k]);
+                    else stg2(src + k * rowstride, 0, v);
+                });
+                continue;
+            } else {
+                fft_small<R>(z);
+            }
             if (B1 > 1) {
                 const int w0 = opaque(it);              // j tc + c
 #pragma unroll
@@ -1064,11 +1171,13 @@ __device__ __forceinline__ void axis1_regs_body(PT P, const int bx)
     });
 }
 
-__global__ __launch_bounds__(256) void k_axis1_regs(Axis1Params P) { axis1_regs_body<Axis1Params>(P, blockIdx.x); }
+template <bool BIG>
+__global__ __launch_bounds__(256) void k_axis1_regs(Axis1Params P) { axis1_regs_body<BIG, Axis1Params>(P, blockIdx.x); }
+template <bool BIG>
 __global__ __launch_bounds__(256) void k_axis1_regs_merged(const Axis1Params* __restrict__ tab, const Slot* __restrict__ slots)
 {
     int d, bx;
-    if (slot_of(slots, d, bx)) axis1_regs_body<const Axis1Params&>(tab[d], bx);
+    if (slot_of(slots, d, bx)) axis1_regs_body<BIG, const Axis1Params&>(tab[d], bx);
 }
 
 // ---------------------------------------------------------------------------- register FFTs
@@ -1320,15 +1429,19 @@ hipError_t launch_fft_planes(const PlaneParams& p, hipStream_t st)
     }
     const size_t lds = planes_lds_bytes(p);
     if (p.a3 > 0) {
+        if (p.a3 > kMaxPlanePrime || p.a2 > kMaxPlanePrime) return hipErrorInvalidValue;
         const int groups = p.row_pairs > 0 ? p.n1 * p.nrchunk : (p.n1 + p.npl - 1) / p.npl;
         if (p.npl < 1 || p.fchunk < 1 || p.fchunk > kPlaneMaxFields || p.threads < 64 || p.threads > 512 || p.a3 * p.b3 != p.n3 ||
             p.lp < p.n3 || (p.row_pairs <= 0 && p.a2 * p.b2 != p.n2))
             return hipErrorInvalidValue;
+        const bool big = p.a3 > kMaxRegRadix || (p.row_pairs <= 0 && p.a2 > kMaxRegRadix);
+        const auto one = big ? k_plane_regs<true> : k_plane_regs<false>;
         if (lds > 65536) {
-            hipError_t e = hipFuncSetAttribute((const void*)k_plane_regs, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            hipError_t e = hipFuncSetAttribute((const void*)one, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        return dispatch(k_plane_regs, k_plane_regs_merged, p.M * p.S * groups * p.nfchunk, p.threads, lds, st, p);
+        return dispatch(one, big ? k_plane_regs_merged<true> : k_plane_regs_merged<false>, p.M * p.S * groups * p.nfchunk,
+                        p.threads, lds, st, p);
     }
     if (p.row_pairs > 0) {
         if (lds > 65536) {
@@ -1412,13 +1525,16 @@ hipError_t launch_fft_axis1(const Axis1Params& p, hipStream_t st)
     const size_t lds = axis1_lds_bytes(p);
     if (p.a > 0) {
         if (p.a * p.b != p.n1) return hipErrorInvalidValue;
+        const bool big = p.a > kMaxRegRadix;
+        const auto one = big ? k_axis1_regs<true> : k_axis1_regs<false>;
         if (lds > 65536) {
-            hipError_t e = hipFuncSetAttribute((const void*)k_axis1_regs, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            hipError_t e = hipFuncSetAttribute((const void*)one, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
         const int items = p.tc * (p.b > 1 ? std::max(p.a, p.b) : 1);
         const unsigned threads = std::min(256, (items + 63) / 64 * 64);
-        return dispatch(k_axis1_regs, k_axis1_regs_merged, p.M * p.n2 * p.ncolblk, threads, lds, st, p);
+        return dispatch(one, big ? k_axis1_regs_merged<true> : k_axis1_regs_merged<false>, p.M * p.n2 * p.ncolblk, threads,
+                        lds, st, p);
     }
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute((const void*)k_fft_axis1,

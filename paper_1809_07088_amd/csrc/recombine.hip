@@ -1969,13 +1969,15 @@ __global__ __launch_bounds__(kTileThreads) void k_recombine_tiles_merged(const R
 
 // One site: rows per block for about 6144 values (24 a thread; the 1024 boxes of 48^3 took 158,
 // 125, 131 and 157 us at 4096, 6144, 8192 and 12288), in fours so that a dense box's
-// blocks start on 16 bytes; fewer where many configurations make the sums the longer part and
+// blocks start on 16 bytes, and at least 16 blocks a box (25 boxes of 41 x 25 x 37 in one
+// launch: 18 us with seven blocks each, 9 with 17); fewer where many configurations make the sums the longer part and
 // that leaves under 512 blocks.
 static hipError_t launch_recombine_tiles(const RecombParams& p, hipStream_t st)
 {
     RecombParams q = p;
     const long long rows = (long long)p.planes * p.cnt[1];
     int r = std::max(4, std::min(kTileMaxRows, 6144 / p.opitch / 4 * 4));
+    while (r > 4 && (rows + r - 1) / r < 16) r -= 4;
     while (p.M > 8 && r > 4 && (rows + r - 1) / r < 512) r -= 4;
     while (r > 1 && (size_t)r * p.n3 > 8192) r /= 2;
     q.rows = r;

@@ -199,3 +199,19 @@ def test_magnetic_rows_configurations(S, M, r, n, box):
     m.g0, m.count = tuple(m.g0), tuple(m.count)
     say(f"magnetic rows S={S} M={M} grid={r} n={n} box={m.g0}+{m.count}")
     sampled_parity(m, None, 1500)
+
+
+# ------------------------------------------------------------------ lines of a prime length
+@pytest.mark.parametrize("p", [17, 19, 23, 29, 31, 37, 41, 43, 47, 53, 59, 61, 67])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_prime_edges(p, axis):
+    """Every prime past the small radices on every axis, alone and times 2 to 4 (67: the Stockham
+    passes)."""
+    f = 1 + p % 4 if p < 60 else 1
+    n = [3, 2, 4]
+    n[axis] = p * f
+    m = synth.random_model(2900 + p + axis, n=tuple(n), S=2, M=2, order=1, sigma=0.03)
+    m.g0 = tuple(-min(v + 1, 30) for v in n)
+    m.count = tuple(min(2 * v + 3, 63) for v in n)
+    say(f"prime edges n={m.n}")
+    sampled_parity(m, 1, 1000)
