@@ -1211,9 +1211,31 @@ void plan_plane_regs(dsx_model m, long long planes, PlaneParams& pp)
     pp.threads = (int)std::max<long long>(64, ((lines + rounds - 1) / rounds + 63) / 64 * 64);
 }
 
+// Boxes transformed whole by one block per (configuration, site, field chunk).
+bool whole_box(dsx_model m) { return m->n[0] <= kMaxRegRadix && m->n[1] <= kMaxRegRadix && m->n[2] <= kMaxRegRadix; }
+
+// Its block shape: fields within 64 KB of LDS, at least 512 blocks where there are fields enough.
+void plan_whole_box(dsx_model m, PlaneParams& pp)
+{
+    const int n2 = m->n[1], npairs = (n2 + 1) / 2;
+    pp.a1 = m->n[0]; pp.a2 = n2; pp.b2 = 1; pp.a3 = m->n[2]; pp.b3 = 1;
+    pp.lp = m->n[2] | 1;
+    pp.buf_elems = std::max(npairs * pp.lp, n2 * m->nh);
+    pp.npl = m->n[0];
+    int fb = std::min(m->F, kPlaneMaxFields);
+    while (fb > 1 && (long long)m->M * m->S * ((m->F + fb - 1) / fb) < 512) --fb;
+    if (m->tune_fchunk > 0) fb = std::min(m->tune_fchunk, m->F);
+    for (pp.fchunk = fb; pp.fchunk > 1 && planes_lds_bytes(pp) > 64 * 1024; --pp.fchunk) {}
+    pp.nfchunk = (m->F + pp.fchunk - 1) / pp.fchunk;
+    const int lines = pp.fchunk * std::max(m->n[0] * std::max(npairs, m->nh), n2 * m->nh);
+    const int rounds = (lines + 319) / 320;
+    pp.threads = std::max(64, ((lines + rounds - 1) / rounds + 63) / 64 * 64);
+}
+
 dsx_status ensure_spectra(dsx_model m, hipStream_t st, bool force = false)
 {
     if (!m->dirty && !force) return DSX_OK;
+    const bool whole = whole_box(m);
     SumsParams sp{};
     sp.occ = m->has_occ ? m->d_occ : nullptr;
     sp.vec = m->d_vec;
@@ -1243,7 +1265,9 @@ dsx_status ensure_spectra(dsx_model m, hipStream_t st, bool force = false)
     const long long planes = (long long)m->M * m->S * m->n[0];
     bool by_rows = false;
     const bool fixed = fft_reg_supported(m->n[1]) && fft_reg_supported(m->n[2]);
-    if (!fixed && split_length(m->n[2], &pp.a3, &pp.b3, kMaxPlanePrime) && split_length(m->n[1], &pp.a2, &pp.b2, kMaxPlanePrime)) {
+    if (whole) {
+        plan_whole_box(m, pp);
+    } else if (!fixed && split_length(m->n[2], &pp.a3, &pp.b3, kMaxPlanePrime) && split_length(m->n[1], &pp.a2, &pp.b2, kMaxPlanePrime)) {
         plan_plane_regs(m, planes, pp);
         by_rows = pp.row_pairs > 0;
     } else {
@@ -1285,6 +1309,10 @@ dsx_status ensure_spectra(dsx_model m, hipStream_t st, bool force = false)
                 }
     }
     HIPCHK(m, timed("fft_planes", st, [&] { return launch_fft_planes(pp, st); }));
+    if (whole) {
+        m->dirty = false;
+        return DSX_OK;
+    }
     if (by_rows) {
         // axis 2 in place: the spectra seen as [M n1][n2][1][S F nh]
         Axis1Params a2{};
@@ -2633,7 +2661,8 @@ dsx_status plan_nodes(const std::vector<std::vector<LaunchRec>>& seq, bool merge
             if (head[i] >= seq[i].size()) continue;
             const LaunchRec& r = seq[i][head[i]];
             if (stage_rank(r.stage) != best) continue;
-            const unsigned per_cu = r.lds ? std::min(64u, (160u * 1024u) / r.lds) : 64u;
+            // (16 and more blocks a CU are one class)
+            const unsigned per_cu = r.lds ? std::min(16u, (160u * 1024u) / r.lds) : 16u;
             const auto key = std::make_tuple(r.merged, r.block, per_cu);
             auto g = std::find_if(groups.begin(), groups.end(), [&](const auto& x) { return x.first == key; });
             if (g == groups.end()) groups.push_back({key, {i}});

@@ -92,6 +92,8 @@ struct PlaneParams {
                           // and transform along axis 3 only (axis 2 follows in place)
     int32_t nrchunk;      // row-pair chunks per plane
     int32_t a2, b2, a3, b3;   // register transforms: n2 = a2 b2, n3 = a3 b3 (a3 = 0: Stockham passes)
+    int32_t a1;           // > 0: whole boxes (edges <= kMaxRegRadix): the block also transforms along
+                          // axis 1 (n1 = a1 = npl)
     int32_t lp;           // register transforms: complex elements between packed row pairs in LDS
     int32_t threads;      // register transforms: threads per block
     int8_t mono[3 * kMaxMono];   // exponents (p, q, r) of field f (spectra order)
