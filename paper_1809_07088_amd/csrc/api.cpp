@@ -962,7 +962,7 @@ size_t sites_lds(dsx_model m, const RecombParams& p, int hc)
 {
     const bool par = p.parity && p.variant != 2;
     const size_t lds = sizeof(float2) * sites_lds_elems(p.npl, p.mg, p.csites, p.n3s, m->order, m->S, p.rows,
-                                                        par ? 0 : m->nclass * p.nH3span);
+                                                        par ? 0 : m->nclass * p.nH3span + hc);
     return p.mg > 1 ? std::max(lds, sizeof(float) * (size_t)(p.mg - 1) * hc * p.npl * p.gthreads) : lds;
 }
 
@@ -1113,7 +1113,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         // the class phases
         const bool par = p.parity && p.variant != 2;
         const size_t lds = sizeof(float2) * (2 * bs + (size_t)4 * m->S * (m->order + 1) +
-                                             (par ? 0 : (size_t)m->nclass * tb->nH3span));
+                                             (par ? 0 : (size_t)m->nclass * tb->nH3span + tb->hc));
         if (lds <= 140 * 1024) {
             p.fold = 1;
             p.fold_l2 = L2;
@@ -2160,6 +2160,7 @@ dsx_status dsx_noise_filter_spherical(dsx_model m, int32_t lanczos_m, int32_t ov
         for (int a = 0; a < 3; ++a) { lp.e[a] = ext.cnt[a]; lp.o[a] = sv * m->box.cnt[a]; }
         lp.m = lm; lp.s = sv;
         lp.eoff = kExtEoff;
+        lp.ohalf = (sv == 1 && symmetric_box(m->box)) ? (lp.o[0] + 1) / 2 : 0;
         HIPCHK(m, timed("lanczos_spherical", st, [&] { return launch_lanczos_stencil(lp, st); }));
         if (where == DSX_HOST) {
             HIPCHK(m, hipMemcpyAsync(out, dout, out_vox * sizeof(float), hipMemcpyDeviceToHost, st));

@@ -159,6 +159,14 @@ __device__ __forceinline__ int wave_min_uniform(int v)
     return __builtin_amdgcn_readfirstlane(v);
 }
 
+// The most H3 values any lane of the wave has: a level-C loop up to it, the same for the whole
+// wave, needs no per-lane masks (a lane's values past its own count are never written).
+__device__ __forceinline__ int wave_max_uniform(int v)
+{
+    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
 // The thread's output voxels G3 = G3(h = 0) + n3 h of row (G1, G2) and, on symmetric
 // boxes, their mirrors -G: byte offsets from block-uniform plane bases (a plane of
 // the box is below 4 GiB), so each store is one 32-bit add and a global store.
@@ -287,8 +295,8 @@ __device__ __forceinline__ void recombine_sites_body(PT P, const int bx)
     float2* Bs = smem;                                          // [mg][npl][csites][n3s][QP]
     float2* wbt = Bs + (size_t)mg * npl * P.bs_elems;           // [npl][S]  b e^{2 pi i g1 r1}
     float2* t2 = wbt + npl * S;                                 // [rows][S] e^{2 pi i g2 r2}
-    float2* tHs = t2 + P.rows * S;                              // [nclass][nH3span] (class form)
-    float* cm = reinterpret_cast<float*>(tHs + (PAR ? 0 : P.nclass * P.nH3span));   // [npl][N + 1]
+    float2* tHs = t2 + P.rows * S;                              // [nclass][nH3span] (class form), and HC more
+    float* cm = reinterpret_cast<float*>(tHs + (PAR ? 0 : P.nclass * P.nH3span + HC));   // [npl][N + 1]
     __shared__ int jtab[2][QR];              // terms N - e + 1, field of p = 0 of pair j
     __shared__ float jfr[QR];                // 1/r! of pair j
     const int SFnh = P.SF * nh;
@@ -339,6 +347,7 @@ __device__ __forceinline__ void recombine_sites_body(PT P, const int bx)
     const int H3lo = h3.x, hbeg = ch * HC;
     const int hcnt = active ? max(0, min(HC, h3.y - hbeg)) : 0;
     const int hmin = wave_min_uniform(active ? hcnt : HC);     // iterations every lane needs
+    const int hmax = wave_max_uniform(hcnt);
     const float tau2 = (float)(6.283185307179586 * (double)G2 / (double)n2);
     const float c3 = (float)(6.283185307179586 / (double)n3);
     const float t3base = (float)(k3 + n3 * (H3lo + hbeg)) * c3; // tau3 of h = 0
@@ -484,25 +493,38 @@ __device__ __forceinline__ void recombine_sites_body(PT P, const int bx)
                     }
                     if constexpr (!PAR) {
                         const float2* tH = tH0 + (size_t)c * P.nH3span + H3lo + hbeg;
+                        // four H3 at a time: their phases are read together (16 occupational sites,
+                        // 261^3: 129 us with a read and a wait per H3, 107 so)
 #pragma unroll
-                        for (int h = 0; h < HC; ++h) {
-                            if (h < hmin || h < hcnt) {
-                                const float t3 = t3base + (float)h * dt3;
-                                float2 acc = D[N];
+                        for (int h0 = 0; h0 < HC; h0 += 4) {
+                            if (h0 < hmax) {
+                                float2 e3[4];
 #pragma unroll
-                                for (int r = N - 1; r >= 0; --r)
-                                    acc = make_float2(D[r].x - t3 * acc.y, D[r].y + t3 * acc.x);
-                                float2 e3 = tH[h];
+                                for (int u = 0; u < 4 && h0 + u < HC; ++u) e3[u] = tH[h0 + u];
                                 if (P.nuc_ff) {
                                     // the class's scattering factor f(|Q|), s = |Q|/(4 pi)
-                                    const float g3 = (float)(k3 + n3 * (H3lo + hbeg + h)) / (float)n3;
-                                    const float qx = q12x + g3 * P.recip[6], qy = q12y + g3 * P.recip[7],
-                                                qz = q12z + g3 * P.recip[8];
-                                    const float f = site_ff(P.ff[sp], (qx * qx + qy * qy + qz * qz) * 0.00633257397764611f);
-                                    e3 = make_float2(e3.x * f, e3.y * f);
+#pragma unroll
+                                    for (int u = 0; u < 4 && h0 + u < HC; ++u) {
+                                        if (h0 + u >= hmax) break;
+                                        const float g3 = (float)(k3 + n3 * (H3lo + hbeg + h0 + u)) / (float)n3;
+                                        const float qx = q12x + g3 * P.recip[6], qy = q12y + g3 * P.recip[7],
+                                                    qz = q12z + g3 * P.recip[8];
+                                        const float f = site_ff(P.ff[sp], (qx * qx + qy * qy + qz * qz) * 0.00633257397764611f);
+                                        e3[u] = make_float2(e3[u].x * f, e3[u].y * f);
+                                    }
                                 }
-                                F[h].x += e3.x * acc.x - e3.y * acc.y;
-                                F[h].y += e3.x * acc.y + e3.y * acc.x;
+#pragma unroll
+                                for (int u = 0; u < 4 && h0 + u < HC; ++u) {
+                                    if (N > 0 && h0 + u >= hmax) break;
+                                    const float t3 = t3base + (float)(h0 + u) * dt3;
+                                    float2 acc = D[N];
+#pragma unroll
+                                    for (int r = N - 1; r >= 0; --r)
+                                        acc = make_float2(fmaf(-t3, acc.y, D[r].x), fmaf(t3, acc.x, D[r].y));
+                                    float2& f = F[h0 + u];
+                                    f.x = fmaf(e3[u].x, acc.x, fmaf(-e3[u].y, acc.y, f.x));
+                                    f.y = fmaf(e3[u].x, acc.y, fmaf(e3[u].y, acc.x, f.y));
+                                }
                             }
                         }
                     }
@@ -516,7 +538,7 @@ __device__ __forceinline__ void recombine_sites_body(PT P, const int bx)
                     parity_order<N>(DE, DO, H3lo + hbeg);
 #pragma unroll
                     for (int h = 0; h < HC; ++h)
-                        if (h < hmin || h < hcnt) I[h] += parity_eval<N>((h & 1) ? DO : DE, t3base + (float)h * dt3);
+                        if (h < hmax) I[h] += parity_eval<N>((h & 1) ? DO : DE, t3base + (float)h * dt3);
                 } else {
 #pragma unroll
                     for (int h = 0; h < HC; ++h) I[h] += F[h].x * F[h].x + F[h].y * F[h].y;
@@ -575,7 +597,7 @@ __global__ __launch_bounds__(512, 4) void k_recombine_sites_merged(const RecombP
 //   Bs   [2][nclass][L2][n3s][QR] level A summed over the sites of each r3 class,
 //                                 with the site phase (but the H2-parity sign) and 1/r!
 //   wt   [2][2][S][N + 1]         level-A weights (conjugated copy, plane, site, p)
-//   tHs  [nclass][nH3span]        class phases e^{2 pi i H3 r_c3} (class form only)
+//   tHs  [nclass][nH3span] + HC   class phases e^{2 pi i H3 r_c3} (class form only)
 // Level A reads the spectra straight from the (L2-resident) column: every thread
 // owns (pair, k3) items and accumulates the sites of a class in registers, with the
 // loads of the next site in flight, so the level needs no staging and no barrier.
@@ -673,6 +695,7 @@ __device__ __forceinline__ void recombine_folded_body(PT P, const int bx)
     const int hbeg = ch * HC;
     const int hcnt = active ? max(0, min(HC, nH3 - hbeg)) : 0;
     const int hmin = P.hmin_s[(wi.w >> 27) & 7];   // iterations every lane of a full wave needs
+    const int hmax = (MULTI || !PAR) ? wave_max_uniform(hcnt) : 0;
     const float tau2 = (float)((double)G2 * P.tw[1]);
     const float c3 = (float)P.tw[2];
     const float t3base = (float)(k3 + n3 * (H3lo + hbeg)) * c3;   // tau3 of h = 0
@@ -863,16 +886,23 @@ __device__ __forceinline__ void recombine_folded_body(PT P, const int bx)
                 if constexpr (!PAR) {
                     const float2* tH = tH0 + (size_t)c * P.nH3span + H3lo + hbeg;
 #pragma unroll
-                    for (int h = 0; h < HC; ++h) {
-                        if (h < hmin || h < hcnt) {
-                            const float t3 = t3base + (float)h * dt3;
-                            float2 acc = D[N];
+                    for (int h0 = 0; h0 < HC; h0 += 4) {
+                        if (h0 < hmax) {
+                            float2 e3[4];
 #pragma unroll
-                            for (int r = N - 1; r >= 0; --r)
-                                acc = make_float2(D[r].x - t3 * acc.y, D[r].y + t3 * acc.x);
-                            const float2 e3 = tH[h];
-                            F[h].x += e3.x * acc.x - e3.y * acc.y;
-                            F[h].y += e3.x * acc.y + e3.y * acc.x;
+                            for (int u = 0; u < 4 && h0 + u < HC; ++u) e3[u] = tH[h0 + u];
+#pragma unroll
+                            for (int u = 0; u < 4 && h0 + u < HC; ++u) {
+                                if (N > 0 && h0 + u >= hmax) break;
+                                const float t3 = t3base + (float)(h0 + u) * dt3;
+                                float2 acc = D[N];
+#pragma unroll
+                                for (int r = N - 1; r >= 0; --r)
+                                    acc = make_float2(fmaf(-t3, acc.y, D[r].x), fmaf(t3, acc.x, D[r].y));
+                                float2& f = F[h0 + u];
+                                f.x = fmaf(e3[u].x, acc.x, fmaf(-e3[u].y, acc.y, f.x));
+                                f.y = fmaf(e3[u].x, acc.y, fmaf(e3[u].y, acc.x, f.y));
+                            }
                         }
                     }
                 }
@@ -888,7 +918,7 @@ __device__ __forceinline__ void recombine_folded_body(PT P, const int bx)
             if constexpr (PAR) {
 #pragma unroll
                 for (int h = 0; h < HC; ++h)
-                    if (h < hmin || h < hcnt) I[h] += parity_eval<N>((h & 1) ? DO : DE, t3base + (float)h * dt3);
+                    if (h < hmax) I[h] += parity_eval<N>((h & 1) ? DO : DE, t3base + (float)h * dt3);
             } else {
 #pragma unroll
                 for (int h = 0; h < HC; ++h) I[h] += F[h].x * F[h].x + F[h].y * F[h].y;
