@@ -281,7 +281,8 @@ struct DeviceTables {
     int hmin_slice[8] = {};    // ... and of any item of one k3 slice
     int H3min = 0, nH3span = 0;
     int nwork = 0, nwork2 = 0, nwork3 = 0, hc = 0, nchunk3 = 0, block = 0;
-    int n3s = 0, block3 = 0;   // k3 per slice, threads per plane of a sliced block
+    int n3s = 0, block3 = 0;   // k3 per slice, threads per plane of a sliced block ...
+    int block2 = 0;            // ... and of an unsliced one
     int4* work_s = nullptr;    // nuclear models: blocks of the sites form
     int nwork_s = 0, npl_s = 1, mg_s = 1, gthreads_s = 64, rows_s = 1, csites_s = 1, n3s_s = 1, slices_s = 1;
     int ks3 = 0, nact3 = 0;    // the k3 with points in the box: nact3 of them, cyclically from ks3
@@ -773,8 +774,8 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
     if (!mag) plan_sites_form(m, bx, maxH2, t);
     // k3 slices of the two-plane blocks: halves of the k3 range when it is long enough
     // that a slice still writes 64-byte runs of an output row
-    const int nsl = (n3 >= 16) ? 2 : 1;
-    t.n3s = (n3 + nsl - 1) / nsl;
+    const int nsl = (t.nact3 >= 16) ? 2 : 1;
+    t.n3s = (t.nact3 + nsl - 1) / nsl;
     for (int k1 = 0; k1 < n1; ++k1) {
         const int nH1 = hcount(k1, n1, bx.g0[0], bx.cnt[0]);
         const int H1lo = (int)ceildiv_l((long)bx.g0[0] - k1, n1);
@@ -895,16 +896,19 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
     t.nwork2 = (int)work2.size();
     t.nwork3 = (int)work3.size();
     t.block = ((std::min(maxT, maxrows * per_h2) + 63) / 64) * 64;
+    t.block2 = ((std::min(maxT, maxrows * t.nact3 * t.nchunk3) + 63) / 64) * 64;
     t.block3 = ((std::min(maxT, maxrows * t.n3s * t.nchunk3) + 63) / 64) * 64;
     std::vector<int2> k3t(n3);
     t.hmin_all = t.hc;
     for (int s = 0; s < 8; ++s) t.hmin_slice[s] = t.hc;
-    for (int k = 0; k < n3; ++k) {
+    for (int k = 0; k < n3; ++k)
         k3t[k] = make_int2((int)ceildiv_l((long)bx.g0[2] - k, n3), hcount(k, n3, bx.g0[2], bx.cnt[2]));
+    for (int i = 0; i < t.nact3; ++i) {
+        const int k = (t.ks3 + i) % n3;
         for (int c = 0; c < t.nchunk3; ++c) {
             const int h = std::max(0, std::min(t.hc, k3t[k].y - c * t.hc));
             t.hmin_all = std::min(t.hmin_all, h);
-            t.hmin_slice[k / t.n3s] = std::min(t.hmin_slice[k / t.n3s], h);
+            t.hmin_slice[i / t.n3s] = std::min(t.hmin_slice[i / t.n3s], h);
         }
     }
 
@@ -1107,8 +1111,8 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         const int L2 = whole ? 1 : 2;
         // k3 slices (variant 4: none): smaller blocks, two of them resident per CU
         const bool sliced = tb->work3 != nullptr && p.variant != 4;
-        const int n3s = sliced ? tb->n3s : n3;
-        const size_t bs = (size_t)m->nclass * L2 * n3s * n_pairs(m->order);
+        const int n3s = sliced ? tb->n3s : tb->nact3;
+        const size_t bs = (size_t)m->nclass * L2 * n3s * (n_pairs(m->order) | 1);
         // two planes per block: level A buffers of both, the weights of level A, then
         // the class phases
         const bool par = p.parity && p.variant != 2;
@@ -1124,7 +1128,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
             p.nwork = sliced ? tb->nwork3 : tb->nwork2;
             p.k3tab = tb->k3tab;
             for (int s = 0; s < 8; ++s) p.hmin_s[s] = sliced ? tb->hmin_slice[s] : tb->hmin_all;
-            lp.block = 2 * (sliced ? tb->block3 : tb->block);
+            lp.block = 2 * (sliced ? tb->block3 : tb->block2);
             lp.lds = lds;
             // a slice covers part of each 128-byte line of a row: cached stores only
             if (sliced) p.ostream = 0;

@@ -594,7 +594,7 @@ __global__ __launch_bounds__(512, 4) void k_recombine_sites_merged(const RecombP
 // both planes, and each half of the block then runs levels B and C of one plane.
 // Slicing k3 keeps the LDS of a block small enough for two blocks per CU, so the
 // load-bound level A of one overlaps the arithmetic and stores of the other.  LDS:
-//   Bs   [2][nclass][L2][n3s][QR] level A summed over the sites of each r3 class,
+//   Bs   [2][nclass][L2][n3s][QP] (QP = QR | 1: no bank conflicts between the k3) level A summed over the sites of each r3 class,
 //                                 with the site phase (but the H2-parity sign) and 1/r!
 //   wt   [2][2][S][N + 1]         level-A weights (conjugated copy, plane, site, p)
 //   tHs  [nclass][nH3span] + HC   class phases e^{2 pi i H3 r_c3} (class form only)
@@ -608,13 +608,14 @@ template <int N, int HC, bool MULTI, bool PAR, class PT>
 __device__ __forceinline__ void recombine_folded_body(PT P, const int bx)
 {
     extern __shared__ float2 smem[];
-    constexpr int QR = n_pairs(N);
+    constexpr int QR = n_pairs(N), QP = kPairPitch<N>;
     const int4 wi = P.work[bx];
     if (wi.x < 0) return;
     const bool hasb = (wi.w >> 25) & 1;
     const int n3s = P.n3s;
-    const int k3a = ((wi.w >> 27) & 7) * n3s;       // first k3 of the slice
-    const int k3n = min(n3s, P.n3 - k3a);          // k3 in the slice
+    const int k3a = ((wi.w >> 27) & 7) * n3s;       // the slice's first k3 of those with points ...
+    const int k3n = min(n3s, P.nact3 - k3a);       // ... and how many it has
+    const int k3b = P.ks3 + k3a;                    // (they run cyclically from ks3)
     const int bh = blockDim.x >> 1;                 // threads per plane (a multiple of 64)
     // the plane of this thread's B / C item (wave-uniform: its output bases are scalars)
     const int sel = __builtin_amdgcn_readfirstlane((int)threadIdx.x >= bh ? 1 : 0);
@@ -678,14 +679,15 @@ __device__ __forceinline__ void recombine_folded_body(PT P, const int bx)
     const int nitems = (w.h2b - w.h2a) * k3n * P.nchunk3;
     const int item = threadIdx.x - sel * bh;
     const bool active = item < nitems && (sel == 0 || hasb);
-    int k3 = k3a, ch = 0, h2 = w.h2a;
+    int kl3 = 0, ch = 0, h2 = w.h2a;
     if (active) {
         const int r = qdiv_r(item, k3n, 1.f / (float)k3n);
-        k3 = k3a + (item - r * k3n);
+        kl3 = item - r * k3n;
         const int rc = P.nchunk3 == 1 ? r : qdiv_r(r, P.nchunk3, 1.f / (float)P.nchunk3);
         ch = r - rc * P.nchunk3;
         h2 = w.h2a + rc;
     }
+    const int k3 = (int)min((uint32_t)(k3b + kl3), (uint32_t)(k3b + kl3 - P.n3));   // mod n3
     const int H2 = w.H2lo + h2;
     const int rho = (L2 == 2) ? (H2 & 1) : 0;
     const int G2 = w.k2 + n2 * H2;
@@ -736,7 +738,7 @@ __device__ __forceinline__ void recombine_folded_body(PT P, const int bx)
             const int gg = ok ? g : nitemA - 1;
             const int j = qdiv_r(gg, k3n, rn3);
             const int kl = gg - j * k3n;                  // k3 within the slice
-            const int kk = k3a + kl;
+            const int kk = (int)min((uint32_t)(k3b + kl), (uint32_t)(k3b + kl - n3));
             const int pc = jtab[0][j], f0 = jtab[1][j];
             const float fr = jfr[j];
             const bool half = kk >= nh;                   // conj X(-k) from the mirrored column
@@ -807,13 +809,13 @@ __device__ __forceinline__ void recombine_folded_body(PT P, const int bx)
                     // the sites of a class share r3, hence the k3 phase: applied once, with 1/r!
                     const float2 kf = make_float2(x[N + 1].x * fr, x[N + 1].y * fr);
                     if (ok) {
-                        float2* b0 = smem + ((size_t)(c * L2) * n3s + kl) * QR + j;
+                        float2* b0 = smem + ((size_t)(c * L2) * n3s + kl) * QP + j;
                         float2* b1 = b0 + P.bs_elems;
                         b0[0] = cmulf(kf, aE0);
                         b1[0] = cmulf(kf, aE1);
                         if (L2 == 2) {
-                            b0[(size_t)n3s * QR] = cmulf(kf, aO0);
-                            b1[(size_t)n3s * QR] = cmulf(kf, aO1);
+                            b0[(size_t)n3s * QP] = cmulf(kf, aO0);
+                            b1[(size_t)n3s * QP] = cmulf(kf, aO1);
                         }
                     }
                     aE0 = aO0 = aE1 = aO1 = make_float2(0.f, 0.f);
@@ -850,10 +852,12 @@ __device__ __forceinline__ void recombine_folded_body(PT P, const int bx)
         // sgn_c^H3 split as sgn_c^(H3lo + hbeg) (the weight wa) times sgn_c^h (wb = wa sgn_c
         // for odd h); the first class initialises the sets.
         const bool odd0 = ((H3lo + hbeg) & 1) != 0;
+        // (the item's place in the slice, from k3 again: no register is held for it through level A)
+        const int klb = (int)min((uint32_t)(k3 - k3b), (uint32_t)(k3 - k3b + n3));
         auto level_b = [&](int c, auto first_tag) {
             constexpr bool FIRST = decltype(first_tag)::value;
             {
-                const float2* Bp = Bs + ((size_t)(c * L2 + rho) * n3s + (k3 - k3a)) * QR;
+                const float2* Bp = Bs + ((size_t)(c * L2 + rho) * n3s + klb) * QP;
                 const float sgn = PAR ? (float)P.class_sign[c] : 1.f;
                 const float wa = odd0 ? sgn : 1.f, wb = odd0 ? 1.f : sgn;
                 float2 D[PAR ? 1 : N + 1];

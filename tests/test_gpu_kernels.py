@@ -234,3 +234,16 @@ def test_whole_boxes(n, kind, order, M, occ):
     m.count = tuple(v + 5 for v in n)
     say(f"whole box n={n} kind={kind} order={order}")
     sampled_parity(m, order if order and kind == synth.NUCLEAR else None, 1200)
+
+
+# ------------------------------------------------------------------ folded form on thin boxes
+@pytest.mark.parametrize("order,M", [(2, 1), (3, 3), (6, 1), (7, 2), (8, 1)])
+@pytest.mark.parametrize("n3,g3,c3", [(18, 5, 1), (18, -3, 5), (18, 15, 17), (6, 4, 4), (32, -16, 20)])
+def test_folded_form_with_fewer_g3_than_k3(order, M, n3, g3, c3):
+    """Boxes whose G3 leave some k3 without points (the active ones wrap around), sliced and not,
+    with odd and even numbers of (q, r) pairs."""
+    m = synth.random_model(3100 + order + n3, n=(3, 4, n3), S=4, M=M, order=order, with_occ=False, sigma=0.03)
+    m.frac = synth.FCC_BASIS.copy()
+    m.g0, m.count = (-4, -6, g3), (9, 12, c3)
+    say(f"folded thin order={order} M={M} box={m.g0}+{m.count}")
+    sampled_parity(m, order, 1500)
