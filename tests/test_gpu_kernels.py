@@ -247,3 +247,24 @@ def test_folded_form_with_fewer_g3_than_k3(order, M, n3, g3, c3):
     m.g0, m.count = (-4, -6, g3), (9, 12, c3)
     say(f"folded thin order={order} M={M} box={m.g0}+{m.count}")
     sampled_parity(m, order, 1500)
+
+
+# ------------------------------------------------------------------ Bragg points of one configuration
+@pytest.mark.parametrize("kind,order", [(synth.NUCLEAR, 0), (synth.NUCLEAR, 2), (synth.MAGNETIC, 0), (synth.MAGNETIC, 2)])
+@pytest.mark.parametrize("bad", [None, np.nan, np.inf])
+def test_bragg_points_of_one_configuration(kind, order, bad):
+    """Exactly 0, and not a number where an input is not (but 0 at the origin of magnetic models)."""
+    m = synth.random_model(3200 + order, n=(3, 4, 5), S=3, M=1, order=order, kind=kind, with_disp=order > 0, mag_order=order, sigma=0.03,
+                           cell=None if kind == synth.NUCLEAR else [6.0, 7.0, 8.0, 90.0, 90.0, 90.0])
+    m.g0, m.count = (-6, -8, -10), (13, 17, 21)
+    if bad is not None:
+        (m.spin if kind == synth.MAGNETIC else m.disp if order else m.occ)[0, 1, 0, 0, 0] = bad
+    say(f"Bragg points of one configuration kind={kind} order={order} bad={bad}")
+    I = gpu_intensity(m).reshape(m.count)[::3, ::4, ::5]
+    if bad is None:
+        assert not np.any(I)
+    else:
+        want = np.ones(I.shape, bool)
+        if kind == synth.MAGNETIC:
+            want[2, 2, 2] = False
+        assert np.array_equal(np.isnan(I), want)
