@@ -740,9 +740,13 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
         // configurations a pass: four, two or one, the first that holds the row residues (or four
         // rows staged one by one) in 32 KB.  Blocks in flight count for more than what a pass of
         // several saves (16 sites, 40^3 cells, two configurations: one a pass in 30 KB 130 us, two
-        // in 47 KB 176), so larger passes are for small n3; one configuration takes up to 48 KB
+        // in 47 KB 176), so larger passes are for small n3; one configuration takes up to 48 KB.
+        // Rows that are staged one by one (q2 = 0) are bound by the sums over their classes, where a
+        // pass of four costs more than two of two (3 sites, 20^3 cells, five configurations: 69 us
+        // at four a pass, 45 at two, 49 at one), and one with an idle half more than two of one
+        // (6 sites, 12^3 cells, three configurations: 68 and 59 us)
         for (int mc : {4, 2, 1}) {
-            if (mc > 1 && mc / 2 >= m->M) continue;
+            if (mc > 1 && (mc / 2 >= m->M || (q2 == 0 && (mc > 2 || m->M == 3)))) continue;
             const bool passes = m->M > mc;
             const size_t budget = (mc > 1 ? 32 : passes ? 64 : 48) * 1024 / sizeof(float2);
             int cs = S;
@@ -760,6 +764,9 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
                 rows = most;
             } else if (fixed < budget) {
                 rows = std::min(most, (int)((budget - fixed) / (per_row + per_sum)));
+                // (three blocks a CU: 10 sites, 62^3 cells, three configurations ran at 947 us with
+                // as many rows as 64 KB hold, two blocks, and at 541 with 48 KB)
+                while (rows > 1 && fixed + rows * (per_row + per_sum) > 48 * 1024 / sizeof(float2)) --rows;
             }
             if (rows < 1 || (mc > 1 && rows < std::min(most, 4))) continue;
             t.qmod2_mr = qm2;

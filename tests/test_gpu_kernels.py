@@ -205,6 +205,16 @@ def test_magnetic_rows_configurations(S, M, r, n, box):
     sampled_parity(m, None, 1500)
 
 
+@pytest.mark.parametrize("S,M,n", [(10, 3, (2, 3, 62)), (6, 3, (3, 4, 12)), (3, 6, (4, 3, 20)), (15, 2, (2, 3, 45)), (24, 1, (2, 2, 62))])
+def test_magnetic_rows_staged_one_by_one(S, M, n):
+    """Sites off every grid: one or two configurations a pass, the rows a block holds bounded by the
+    LDS that three blocks of a compute unit share, down to one."""
+    m = synth.random_model(2870 + S + M, n=n, S=S, M=M, kind=synth.MAGNETIC, cell=[6.0, 7.0, 8.0, 90.0, 90.0, 90.0])
+    m.g0, m.count = (-n[0], -3 * n[1] - 1, -n[2] - 1), (2 * n[0] + 1, 6 * n[1] + 3, 2 * n[2] + 3)
+    say(f"staged magnetic rows S={S} M={M} n={n}")
+    sampled_parity(m, None, 1500)
+
+
 # ------------------------------------------------------------------ lines of a prime length
 @pytest.mark.parametrize("p", [17, 19, 23, 29, 31, 37, 41, 43, 47, 53, 59, 61, 67])
 @pytest.mark.parametrize("axis", [0, 1, 2])
