@@ -261,10 +261,11 @@ __device__ __forceinline__ float parity_eval(const float2 (&S)[N + 1], float t3)
 //            multiple of 1/2), the classes folded into the coefficient sets of even and odd H3.
 // A pass over the configurations costs two barriers per site chunk and one latency of loads
 // for all its sites, where staging the sites one by one paid both per site: 16 occupational
-// sites on a 261^3 box (half of it computed) ran at 377 us that way and 137 us here, six sites at
-// order 5 with three configurations on 77 x 85 x 113 at 103 and 62 us, 32 occupational sites with
-// 100 configurations on 125^3 at 5.0 and 0.97 ms, five sites at order 4 with two on 389 x 389 x 5
-// at 282 and 47 us (there only the k3 with points in the box are taken).  Bound by vector issue (levels B and C) and
+// sites on a 261^3 box (half of it computed) ran at 377 us that way and 107 us here, six sites at
+// order 5 with three configurations on 77 x 85 x 113 at 103 and 61 us, 32 occupational sites with
+// 100 configurations on 125^3 at 5.0 and 0.97 ms (the latter still with a read and a wait per
+// phase), five sites at order 4 with two on 389 x 389 x 5 at 282 and 46 us (there only the k3
+// with points in the box are taken).  Bound by vector issue (levels B and C) and
 // by the latency of level A, which other blocks of the CU cover (LDS of a block <= 64 KB).
 // Several configurations share a block wherever its items leave threads over: each group keeps
 // its own |F|^2 sums, added through LDS in a fixed order at the end.
@@ -1894,7 +1895,9 @@ __global__ __launch_bounds__(kDirectThreads) void k_recombine_direct_merged(cons
 // intensities of their n3 residues k3 once (in LDS; several configurations split over the threads
 // that leaves idle), then writes the rows, c2 / n3 times as many values, as 16-byte stores of one
 // contiguous run.  Bound by those writes: 1024 boxes of 48^3 (453 MB) took 188 us with a load, an
-// |X|^2 and a 4-byte store per voxel (lanes idle past 48), 125 us here.
+// |X|^2 and a 4-byte store per voxel (lanes idle past 48), 125 us here, 114 with streaming stores
+// (whole runs are written once: nothing is gained by keeping them in L2; a 513^3 box that the
+// filter reads next: 323 us for the call, 306 with them).
 constexpr int kTileThreads = 256;
 
 constexpr int kTileMaxRows = 256;
@@ -1966,7 +1969,7 @@ __device__ __forceinline__ void recombine_tiles_body(PT P, const int bx)
         for (; r < nr; r += dr) {
             const int g = k30 + 4 * c, k3 = g - n3 * qdiv_r(g, n3, rn3);
             const float* v = tile + r * np + k3;
-            *reinterpret_cast<gf4*>(out + (size_t)r * pitch + 4 * c) = f4{v[0], v[1], v[2], v[3]};
+            __builtin_nontemporal_store(f4{v[0], v[1], v[2], v[3]}, reinterpret_cast<gf4*>(out + (size_t)r * pitch + 4 * c));
             c += dc;
             if (c >= qp) { c -= qp; ++r; }
         }
@@ -1988,7 +1991,7 @@ __device__ __forceinline__ void recombine_tiles_body(PT P, const int bx)
             k3 = k3 + 1 == n3 ? 0 : k3 + 1;
             if (i3 == pitch) { i3 = 0; ++r; k3 = k30; }
         }
-        if (step == 4 && e + 4 <= total) *reinterpret_cast<gf4*>(out + e) = f4{v[0], v[1], v[2], v[3]};
+        if (step == 4 && e + 4 <= total) __builtin_nontemporal_store(f4{v[0], v[1], v[2], v[3]}, reinterpret_cast<gf4*>(out + e));
         else
             for (int u = 0; u < step && e + u < total; ++u) out[e + u] = v[u];
     }
