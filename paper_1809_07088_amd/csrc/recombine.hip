@@ -1895,7 +1895,8 @@ __global__ __launch_bounds__(kDirectThreads) void k_recombine_direct_merged(cons
 // intensities of their n3 residues k3 once (in LDS; several configurations split over the threads
 // that leaves idle), then writes the rows, c2 / n3 times as many values, as 16-byte stores of one
 // contiguous run.  Bound by those writes: 1024 boxes of 48^3 (453 MB) took 188 us with a load, an
-// |X|^2 and a 4-byte store per voxel (lanes idle past 48), 125 us here, 114 with streaming stores
+// |X|^2 and a 4-byte store per voxel (lanes idle past 48), 125 us here, 100 with streaming stores
+// and blocks of half the length
 // (whole runs are written once: nothing is gained by keeping them in L2; a 513^3 box that the
 // filter reads next: 323 us for the call, 306 with them).
 constexpr int kTileThreads = 256;
@@ -2004,17 +2005,17 @@ __global__ __launch_bounds__(kTileThreads) void k_recombine_tiles_merged(const R
     if (slot_of(slots, d, bx)) recombine_tiles_body<const RecombParams&>(tab[d], bx);
 }
 
-// One site: rows per block for about 6144 values (24 a thread; the 1024 boxes of 48^3 took 158,
-// 125, 131 and 157 us at 4096, 6144, 8192 and 12288), in fours so that a dense box's
-// blocks start on 16 bytes, and at least 16 blocks a box (25 boxes of 41 x 25 x 37 in one
-// launch: 18 us with seven blocks each, 9 with 17); fewer where many configurations make the sums the longer part and
-// that leaves under 512 blocks.
+// One site: rows per block for about 6144 values (24 a thread), in fours so that a dense box's
+// blocks start on 16 bytes, and at least 32 blocks a box: 1024 boxes of 48^3 took 203, 177 and
+// 188 us a call with at least 64, 32 and 16, 39 boxes of 61 x 33 x 41 (rows of no multiple of
+// four) 37, 37 and 42, 300 of 43 x 55 x 67 147, 134 and 149.  Fewer where many configurations
+// make the sums the longer part and that leaves under 512 blocks.
 static hipError_t launch_recombine_tiles(const RecombParams& p, hipStream_t st)
 {
     RecombParams q = p;
     const long long rows = (long long)p.planes * p.cnt[1];
     int r = std::max(4, std::min(kTileMaxRows, 6144 / p.opitch / 4 * 4));
-    while (r > 4 && (rows + r - 1) / r < 16) r -= 4;
+    while (r > 4 && (rows + r - 1) / r < 32) r -= 4;
     while (p.M > 8 && r > 4 && (rows + r - 1) / r < 512) r -= 4;
     while (r > 1 && (size_t)r * p.n3 > 8192) r /= 2;
     q.rows = r;
