@@ -1895,7 +1895,7 @@ __global__ __launch_bounds__(kDirectThreads) void k_recombine_direct_merged(cons
 // intensities of their n3 residues k3 once (in LDS; several configurations split over the threads
 // that leaves idle), then writes the rows, c2 / n3 times as many values, as 16-byte stores of one
 // contiguous run.  Bound by those writes: 1024 boxes of 48^3 (453 MB) took 188 us with a load, an
-// |X|^2 and a 4-byte store per voxel (lanes idle past 48), 125 us here, 100 with streaming stores
+// |X|^2 and a 4-byte store per voxel (lanes idle past 48), 125 us here, 110 with streaming stores
 // and blocks of half the length
 // (whole runs are written once: nothing is gained by keeping them in L2; a 513^3 box that the
 // filter reads next: 323 us for the call, 306 with them).
