@@ -581,7 +581,7 @@ int sites_configs(int M, int npl, int gthreads, int bs)
 // Block shape of the sites form on a box (t.hc, t.nchunk3, t.nact3 are set): two planes per
 // block where a column has more than one, halves of the k3 range when they still are 8 or more
 // long, the sites of a chunk within 48 KB of LDS (three blocks per CU; a smaller slice where one
-// site alone exceeds 96 KB), rows for about 320 items a group, and, with the threads that
+// site alone exceeds 96 KB), rows for at most 320 items a group, and, with the threads that
 // leaves over, several configurations at a time.
 void plan_sites_form(dsx_model m, const Box& bx, int maxH2, DeviceTables& t)
 {
@@ -603,12 +603,12 @@ void plan_sites_form(dsx_model m, const Box& bx, int maxH2, DeviceTables& t)
     // even chunks
     const int nch = (S + t.csites_s - 1) / t.csites_s;
     t.csites_s = (S + nch - 1) / nch;
-    const int per_row = t.n3s_s * t.nchunk3;
-    int rows = std::max(1, std::min(std::max(1, 320 / per_row), std::max(1, 2048 / S)));
+    // (a group has a thread for every item: 256 threads of each of two planes, 512 of one)
+    const int per_row = t.n3s_s * t.nchunk3, maxg = 512 / t.npl_s / 64 * 64;
+    int rows = std::max(1, std::min(std::min(320, maxg) / per_row, 2048 / S));
     rows = std::min(rows, std::max(1, maxH2));
     const int parts = (std::max(1, maxH2) + rows - 1) / rows;
     t.rows_s = (std::max(1, maxH2) + parts - 1) / parts;
-    const int maxg = 512 / t.npl_s / 64 * 64;
     t.gthreads_s = std::min(maxg, (t.rows_s * per_row + 63) / 64 * 64);
     t.mg_s = m->M > 1 ? sites_configs(m->M, t.npl_s, t.gthreads_s, t.csites_s * t.n3s_s * qp) : 1;
 }

@@ -969,6 +969,7 @@ template <int N, int HC, bool MULTI, bool PAR>
 static hipError_t launch_nuc_v(const RecombParams& p, int block, size_t lds, hipStream_t st)
 {
     if (block != p.npl * (MULTI ? p.mg : 1) * p.gthreads || block > 512 || p.gthreads % 64) return hipErrorInvalidValue;
+    if (p.rows * p.n3s * p.nchunk3 > p.gthreads) return hipErrorInvalidValue;      // one item a thread
     hipError_t e = set_lds(k_recombine_sites<N, HC, MULTI, PAR>, lds);
     if (e != hipSuccess) return e;
     return dispatch(k_recombine_sites<N, HC, MULTI, PAR>, k_recombine_sites_merged<N, HC, MULTI, PAR>, p.nwork,

@@ -278,3 +278,29 @@ def test_bragg_points_of_one_configuration(kind, order, bad):
         if kind == synth.MAGNETIC:
             want[2, 2, 2] = False
         assert np.array_equal(np.isnan(I), want)
+
+
+# ------------------------------------------------------------------ sites form: rows a group holds
+@pytest.mark.parametrize("n,rows,c3,S,M,order,r3", [((2, 2, 64), 9, 131, 3, 1, 0, None), ((3, 15, 125), 5, 251, 4, 1, 3, (0.2, 0.7)),
+                                                    ((2, 2, 32), 17, 65, 5, 1, 2, (0.0, 0.5)), ((2, 1, 50), 12, 53, 2, 3, 1, None),
+                                                    ((2, 2, 16), 17, 640, 3, 1, 0, None), ((2, 1, 96), 6, 97, 2, 9, 0, None),
+                                                    ((1, 2, 20), 32, 41, 3, 1, 5, None), ((2, 1, 24), 26, 49, 2, 2, 9, None)])
+def test_sites_form_writes_every_row(n, rows, c3, S, M, order, r3):
+    """Columns of so many rows that blocks of 320 items would pass the threads a plane of a
+    two-plane block has: every voxel is written (the output starts as NaN)."""
+    import torch
+    from tests.helpers import to_dsx
+    m = sites_model(3300 + S + M + order, n, S, M, order, r3)
+    m.frac[:, 1] = 0.3 + 0.1 * np.arange(S)          # (no folding)
+    m.g0 = (-2 * n[0], -((rows * n[1]) // 2), -(c3 // 2))
+    m.count = (4 * n[0] + 1, rows * n[1], c3)
+    say(f"sites form rows n={n} box={m.g0}+{m.count} S={S} M={M} order={order}")
+    h = to_dsx(m)
+    out = torch.full(m.count, float("nan"), dtype=torch.float32, device="cuda")
+    h.compute_intensity(out)
+    got = out.cpu().numpy()
+    h.close()
+    assert not np.any(np.isnan(got)), f"{int(np.isnan(got).sum())} voxels not written"
+    G = O.grid_points(m.g0, m.count)
+    pick = np.random.default_rng(1).choice(len(G), min(len(G), 4000), replace=False)
+    assert_parity(got.reshape(-1)[pick], O.intensity(m, G[pick], order if order else None))
