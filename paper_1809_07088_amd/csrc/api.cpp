@@ -977,6 +977,31 @@ size_t sites_lds(dsx_model m, const RecombParams& p, int hc)
     return p.mg > 1 ? std::max(lds, sizeof(float) * (size_t)(p.mg - 1) * hc * p.npl * p.gthreads) : lds;
 }
 
+// Whether |F|^2 at every Bragg point of q stays far below the overflow of float64 while the sums it
+// is formed from stay below kBraggPlainSum: site weights up to 4e20 (|b| and the form factor's
+// terms up to 1e10, none of which grows with |Q|), Taylor coefficients of one degree up to 1e50
+// (they add up to X^d / d!, X = 2 pi (|H1| + |H2| + |H3|)); with 64 sites of 969 monomials twice
+// (spins and Debye-Waller means), |F| < 1e138.
+bool bragg_weights_plain(dsx_model m, const BraggParams& q)
+{
+    for (double b : m->b)
+        if (!(std::fabs(b) <= 1e10)) return false;
+    for (size_t i = 0; i + 8 <= m->ff.size(); i += 8)
+        for (int k = 0; k < 7; ++k) {
+            const double f = m->ff[i + k];
+            if (!(std::fabs(f) <= 1e10) || (k % 2 == 1 && f < 0.0)) return false;
+        }
+    double X = 0.0;
+    for (int a = 0; a < 3; ++a)
+        X += 2 * M_PI * std::max(std::abs((double)q.Hlo[a]), std::abs((double)q.Hlo[a] + q.nH[a] - 1));
+    double c = 1.0;
+    for (int d = 1; d <= std::max(m->order, m->dw_order); ++d)
+        if (!((c *= X / d) <= 1e50)) return false;
+    for (double r : m->recip)
+        if (!(std::fabs(r) <= 1e30)) return false;
+    return std::isfinite(q.scale);
+}
+
 dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& lay, LaunchPlan& lp)
 {
     DeviceTables* tb = nullptr;
@@ -1180,6 +1205,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
     }
     for (int i = 0; i < 9; ++i) q.recip[i] = m->recip[i];
     q.has_ff = m->has_ff ? 1 : 0;
+    q.plain = bragg_weights_plain(m, q) ? 1 : 0;
     return DSX_OK;
 }
 

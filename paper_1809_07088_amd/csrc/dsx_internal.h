@@ -207,7 +207,10 @@ struct BraggParams {
                                  // Debye-Waller means of a magnetic model)
     const double* dwc;      // magnetic: [S][dwT] Debye-Waller means, or null (T = 1)
     int32_t dwT;
+    int32_t plain;          // weights, |H| and scale so small that lattice sums (and Debye-Waller means)
+                            // up to kBraggPlainSum give squares far below the overflow of float64
 };
+constexpr double kBraggPlainSum = 1e30;
 
 // ---------------------------------------------------------------------------- Lanczos
 struct LanczosParams {

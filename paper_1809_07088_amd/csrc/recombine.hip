@@ -2494,26 +2494,78 @@ __global__ __launch_bounds__(256) void k_bragg_magnetic_merged(const BraggParams
     if (slot_of(slots, d, bx)) bragg_magnetic_body<const BraggParams&>(tab[d], bx);
 }
 
+// The value at one H of one configuration as the forms above compute it, by one lane.
+__device__ __forceinline__ float bragg_one(const BraggParams& P, const int (&H)[3])
+{
+#pragma clang fp contract(off)
+    double e[3];
+    for (int c = 0; c < 3; ++c) e[c] = H[0] * P.recip[c] + H[1] * P.recip[3 + c] + H[2] * P.recip[6 + c];
+    const double q2 = e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
+    if (P.kind == 1) {
+        if (!(q2 > 0.0)) return 0.f;
+        const double iq = 1.0 / sqrt(q2);
+        for (int c = 0; c < 3; ++c) e[c] *= iq;
+    }
+    double fr[3] = {0.0, 0.0, 0.0}, fi[3] = {0.0, 0.0, 0.0};
+    for (int mu = 0; mu < P.S; ++mu) {
+        const auto* sd = gptr(P.site) + 12 * mu;
+        double x = H[0] * sd[0] + H[1] * sd[1] + H[2] * sd[2];
+        x -= floor(x);
+        double sn, cs;
+        sincos(6.283185307179586476925 * x, &sn, &cs);
+        const double wgt = P.has_ff ? sd[3] * mag_ff_d(sd + 4, q2 / (16.0 * 9.869604401089358618834)) : sd[3];
+        const double wr = wgt * cs, wi = wgt * sn;
+        // the phase series over the monomials: lattice sums (nuclear) or Debye-Waller means
+        const auto* s = gptr(P.kind == 1 ? P.dwc : P.sums) + (size_t)mu * (P.kind == 1 ? P.dwT : P.T);
+        double tr = 0.0, ti = 0.0;
+        for (int t = 0; t < (P.kind == 1 ? (P.dwc ? P.dwT : 0) : P.T); ++t) {
+            double mag = 1.0;
+            int deg = 0;
+            for (int a = 0; a < 3; ++a)
+                for (int k = 1; k <= P.mono[3 * t + a]; ++k, ++deg) mag *= 6.283185307179586476925 * H[a] / k;
+            const double v = ((deg & 2) ? -mag : mag) * s[t];
+            if (deg & 1) ti += v;
+            else tr += v;
+        }
+        if (P.kind == 1 && !P.dwc) tr = 1.0;
+        const double gr = tr * wr - ti * wi, gi = tr * wi + ti * wr;
+        for (int c = 0; c < 3; ++c) {
+            const double M = P.kind == 1 ? gptr(P.sums)[3 * mu + c] : c == 0 ? 1.0 : 0.0;
+            if (P.kind == 1 || c == 0) {
+                fr[c] += M * gr;
+                fi[c] += M * gi;
+            }
+        }
+    }
+    if (P.kind == 1) {
+        const double pr = e[0] * fr[0] + e[1] * fr[1] + e[2] * fr[2], pi = e[0] * fi[0] + e[1] * fi[1] + e[2] * fi[2];
+        for (int c = 0; c < 3; ++c) { fr[c] -= e[c] * pr; fi[c] -= e[c] * pi; }
+    }
+    double sq = 0.0, mm = 0.0;
+    for (int c = 0; c < 3; ++c) sq += fr[c] * fr[c] + fi[c] * fi[c];
+    for (int c = 0; c < 3; ++c) mm += fr[c] * fr[c] + fi[c] * fi[c];
+    return (float)((sq - mm) * P.scale);
+}
+
 // One configuration: |F|^2 - |<F>|^2 is exactly 0 at every unit-cell Bragg point (the two squares
-// are the same number), or NaN where the lattice sums (or Debye-Waller means) are not finite;
-// I(0) = 0 on magnetic models.  One lane per H, the wave looks through the sums.  The float64
-// forms above took 9.8 us for 17^3 points of the order-8 model and 19 us for 1024 x 64 points,
-// this one 6.8 and 7.8 us.
+// are the same number) unless |F| is not finite or its square overflows.  With plain weights and
+// sums below kBraggPlainSum neither can be, and 0 is written; else the value is computed, one H a
+// lane.  The wave looks through the sums.  The float64 forms above took 9.8 us for 17^3 points of
+// the order-8 model and 19 us for 1024 x 64 points, this one 6.8 and 7.8 us.
 template <class PT>
 __device__ __forceinline__ void bragg_single_body(PT P, const int bx)
 {
     const int lane = threadIdx.x, idx = bx * 64 + lane;
-    double z = 0.0;                                // stays 0, or becomes NaN
-    for (int i = lane; i < P.S * P.T; i += 64) z += 0.0 * gptr(P.sums)[i];
+    bool plain = P.plain != 0;
+    for (int i = lane; i < P.S * P.T; i += 64) plain &= fabs(gptr(P.sums)[i]) <= kBraggPlainSum;     // (not NaN)
     if (P.dwc)
-        for (int i = lane; i < P.S * P.dwT; i += 64) z += 0.0 * gptr(P.dwc)[i];
-    const float v = __ballot(!(z == 0.0)) ? __builtin_nanf("") : 0.f;
+        for (int i = lane; i < P.S * P.dwT; i += 64) plain &= fabs(gptr(P.dwc)[i]) <= kBraggPlainSum;
+    const bool zero = __ballot(!plain) == 0;
     if (idx >= P.nH[0] * P.nH[1] * P.nH[2]) return;
     const int j3 = idx % P.nH[2], j2 = (idx / P.nH[2]) % P.nH[1], j1 = idx / (P.nH[2] * P.nH[1]);
     const int H[3] = {P.Hlo[0] + j1, P.Hlo[1] + j2, P.Hlo[2] + j3};
-    const bool origin = P.kind == 1 && H[0] == 0 && H[1] == 0 && H[2] == 0;
     gptr(P.out)[((size_t)(P.n[0] * H[0] - P.g0[0]) * P.cnt[1] + (P.n[1] * H[1] - P.g0[1])) * P.opitch + (P.n[2] * H[2] - P.g0[2]) + P.ooff] =
-        origin ? 0.f : v;
+        zero ? 0.f : bragg_one(P, H);
 }
 
 __global__ __launch_bounds__(64) void k_bragg_single(BraggParams P) { bragg_single_body<BraggParams>(P, blockIdx.x); }

@@ -304,3 +304,48 @@ def test_sites_form_writes_every_row(n, rows, c3, S, M, order, r3):
     G = O.grid_points(m.g0, m.count)
     pick = np.random.default_rng(1).choice(len(G), min(len(G), 4000), replace=False)
     assert_parity(got.reshape(-1)[pick], O.intensity(m, G[pick], order if order else None))
+
+
+@pytest.mark.parametrize("kind,order", [(synth.NUCLEAR, 0), (synth.NUCLEAR, 5), (synth.MAGNETIC, 0), (synth.MAGNETIC, 2)])
+@pytest.mark.parametrize("bad", ["b inf", "b nan", "b 1e160", "b 1e30", "ff inf", "ff grows", "disp 1e38"])
+def test_bragg_points_of_one_configuration_with_extreme_weights(kind, order, bad):
+    """Not a number where a weight is not finite or the squared structure factor overflows float64
+    (there the subtraction of its two squares is inf - inf), exactly 0 everywhere else."""
+    m = synth.random_model(3400 + order, n=(3, 4, 5), S=3, M=1, order=order, kind=kind, with_disp=order > 0, mag_order=order, sigma=0.03,
+                           cell=[1.0, 1.1, 0.9, 90.0, 95.0, 90.0] if kind == synth.NUCLEAR else [6.0, 7.0, 8.0, 90.0, 90.0, 90.0])
+    m.g0, m.count = (-6, -8, -10), (13, 17, 21)
+    H = O.grid_points((-2, -2, -2), (5, 5, 5))
+    want = np.zeros(len(H), bool)
+    if bad.startswith("b "):
+        m.b[1] = float(bad[2:])
+        want[:] = bad != "b 1e30"
+    elif bad == "disp 1e38":
+        if order != 5:
+            pytest.skip("needs a Taylor order whose powers pass 1e154 in the lattice sums")
+        m.disp[0, 1, 0, 0, 0] = 1e38
+        m.occ[0, 1, 0, 0, 0] = 1.0
+        want[:] = np.any(H != 0, axis=1)     # (every power has the factor 0 at the origin)
+    else:
+        if m.ff is None:
+            m.ff = np.tile(synth.MAG_FF, (3, 1))
+        if bad == "ff inf":
+            m.ff[1, 6] = np.inf
+            want[:] = True
+        else:
+            # 0.4 exp(+B s^2): the first factor past 1e160 (none of them near) at the larger |H|
+            cell = np.asarray(m.cell)
+            scale = 1.0 if kind == synth.NUCLEAR else 50.0
+            m.ff[1, 1] = -800.0 * scale
+            a = np.diag(cell[:3])
+            a[2] = cell[2] * np.array([np.cos(np.radians(cell[4])), 0.0, np.sin(np.radians(cell[4]))])
+            s2 = (np.linalg.norm(H @ np.linalg.inv(a).T, axis=1) / 2) ** 2
+            e = 800.0 * scale * s2 / np.log(10.0)       # the factor's decimal exponent
+            assert not np.any((e > 125) & (e < 156))
+            want = e > 140
+            assert 0 < want.sum() < len(H)
+    if kind == synth.MAGNETIC:
+        want[np.all(H == 0, axis=1)] = False
+    say(f"Bragg points of one configuration kind={kind} order={order} {bad}")
+    I = gpu_intensity(m).reshape(m.count)[::3, ::4, ::5].reshape(-1)
+    assert np.array_equal(np.isnan(I), want)
+    assert not np.any(I[~want])
