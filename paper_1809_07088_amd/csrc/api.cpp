@@ -1049,6 +1049,13 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
     }
     const double C = mag ? 0.07265 : 1.0;
     p.scale = (float)(C / (m->normN * m->M));
+    {
+        int eb = 0, es = 0;
+        const double mb = std::frexp(m->b[0], &eb), ms = std::frexp(C / (m->normN * m->M), &es);
+        const int k = std::max(-120, std::min(120, eb + (es + (es & 1)) / 2));
+        p.one_pre = (float)std::ldexp(1.0, k);
+        p.one_w = (float)std::ldexp(mb * mb * ms, 2 * (eb - k) + es);
+    }
     for (int i = 0; i < 9; ++i) p.recip[i] = (float)m->recip[i];
     p.ff_uniform = 1;
     for (int i = 0; i < m->S; ++i) {

@@ -159,6 +159,8 @@ struct RecombParams {
     int32_t class_of[kMaxSites];       // sorted position -> class index
     double tw[3];           // 2 pi / n_a
     float scale;            // 1/(N M)  (magnetic: C/(N M))
+    float one_pre, one_w;   // one site of order 0: b^2 scale = one_pre^2 one_w, one_pre a power of two
+                            // with one_w in [1/16, 1), so that no product leaves the range of I itself
     // magnetic only
     float recip[9];         // rows a*, b*, c* (inverse Angstrom)
     int32_t ff_uniform;     // 1 when every site has the same form factor

@@ -1928,8 +1928,7 @@ __device__ __forceinline__ void recombine_tiles_body(PT P, const int bx)
         colm[threadIdx.x] = (uint32_t)((k1 ? n1 - k1 : 0) * n2 + (k2 ? n2 - k2 : 0));
     }
     __syncthreads();
-    const float2 t0 = ldg2(P.tab1, 0);
-    const float b2s = (t0.x * t0.x + t0.y * t0.y) * P.scale;
+    const float pre = P.one_pre, w = P.one_w;
     auto place = [&](int r, int k3, float v) {
         for (int j = k3; j < np; j += n3) tile[r * np + j] = v;
     };
@@ -1942,10 +1941,11 @@ __device__ __forceinline__ void recombine_tiles_body(PT P, const int bx)
 #pragma unroll 8
         for (int m = ms; m < P.M; m += parts) {
             const float2 x = ldg2(X, (size_t)m * cstride);
-            v += x.x * x.x + x.y * x.y;
+            const float xr = pre * x.x, xi = pre * x.y;
+            v += xr * xr + xi * xi;
         }
-        if (parts == 1) place(r, k3, v * b2s);
-        else part[t] = v * b2s;
+        if (parts == 1) place(r, k3, v * w);
+        else part[t] = v * w;
     }
     __syncthreads();
     if (parts > 1) {

@@ -349,3 +349,17 @@ def test_bragg_points_of_one_configuration_with_extreme_weights(kind, order, bad
     I = gpu_intensity(m).reshape(m.count)[::3, ::4, ::5].reshape(-1)
     assert np.array_equal(np.isnan(I), want)
     assert not np.any(I[~want])
+
+
+@pytest.mark.parametrize("M", [1, 3, 9])
+@pytest.mark.parametrize("b,amp,norm", [(1e-18, 1e3, 1e4), (1e-25, 1e10, 1.0), (3e17, 0.5, 1e10), (1e22, 1e-5, 1e25), (0.0, 1.0, 1.0)])
+def test_one_site_tiles_with_small_and_large_weights(M, b, amp, norm):
+    """A site weight whose square, or its product with the norm or an amplitude, leaves the normal
+    float32 range though the intensities do not."""
+    m = synth.random_model(3500 + M, n=(20, 24, 40), S=1, M=M, order=0, with_disp=False)
+    m.b[:] = b
+    m.norm_N = norm
+    m.occ = (m.occ - 0.5) * np.float32(amp)
+    m.g0, m.count = (-5, -6, -45), (9, 11, 83)
+    say(f"one site b={b} M={M}")
+    sampled_parity(m, most=1500)
