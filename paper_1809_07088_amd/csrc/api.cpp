@@ -380,8 +380,8 @@ struct dsx_model_s {
     // plan
     int F = 0, T = 0, first_mono = 0, nh = 0, SF = 0, ncell = 0, nclass = 0;
     std::vector<int> site_of, class_of;     // class-sorted site order
-    std::vector<int> sc_start;              // site chunks for the recombination LDS budget
-    size_t chunk_lds = 0;
+    std::vector<int> sc_start;              // magnetic: site chunks of the class form
+    size_t chunk_lds = 0;                   // and their LDS; nuclear: nuclear_box_bytes
     int bs_elems = 0, xs_elems = 0;
     AxisPlan plan[3];
     // device state
@@ -1032,7 +1032,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         const char* v = std::getenv("DSX_RECOMBINE_VARIANT");
         p.variant = (v && *v) ? std::atoi(v) : m->tune_recomb_variant;
     }
-    p.nsc = (int)m->sc_start.size() - 1;
+    p.nsc = std::max(0, (int)m->sc_start.size() - 1);
     for (size_t i = 0; i < m->sc_start.size(); ++i) p.sc_start[i] = m->sc_start[i];
     for (int i = 0; i < m->S; ++i) { p.site_of[i] = m->site_of[i]; p.class_of[i] = m->class_of[i]; }
     p.bs_elems = m->bs_elems;
@@ -1081,7 +1081,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
     lp.hc = tb->hc;
     lp.block = tb->block;
     lp.lds = m->chunk_lds + sizeof(float2) * ((size_t)m->nclass * tb->nH3span + p.dw_elems);
-    size_t staged_lds = lp.lds;     // (the limit on sites, order and box, whatever the form)
+    size_t limit = lp.lds;          // (nuclear_box_bytes, or the class form of magnetic models)
     {
         int c = 0;
         for (int i = 0; i < m->S; ++i)
@@ -1112,7 +1112,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         const int staged = tb->qmod2_mr > 0 ? std::min(tb->rows_mr, tb->qmod2_mr) : tb->rows_mr;
         lp.lds = sizeof(float2) * magnetic_rows_lds_elems(p.mg, staged, tb->csites_mr, m->S, m->nclass, n3, tb->nH3span,
                                                           m->M > p.mg ? p.rows * bx.cnt[2] : 0);
-        staged_lds = lp.lds;
+        limit = lp.lds;
     }
     if (!mag) {
         // the sites form
@@ -1137,7 +1137,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         lp.lds = 0;
         p.planes = stored_planes(bx);   // a half-stored box: its planes G1 <= 0 only
     }
-    if (!lp.direct && std::max(lp.lds, staged_lds) > 160 * 1024) return fail(DSX_ERR_UNSUPPORTED, "recombination does not fit the LDS for this box");
+    if (!lp.direct && std::max(lp.lds, limit) > 160 * 1024) return fail(DSX_ERR_UNSUPPORTED, "recombination does not fit the LDS for this box");
     // folded form, where the class buffers fit the LDS
     if (!lp.direct && p.variant != 3 && fold_applies(m)) {
         bool whole = true;
@@ -1586,6 +1586,18 @@ dsx_status create_model_impl(const dsx_model_desc* d, bool transient, dsx_model*
     return st;
 }
 
+// The limit on the order, n3 and sites of a nuclear model (but for the direct form), part of the
+// interface whatever LDS the form that runs takes: the half spectra of one site's fields along axis
+// 3 and the pair coefficients of as many sites as 72 KB hold beside them (150 KB where those do not
+// hold one) must, with a box's class phases, stay within 160 KB.
+size_t nuclear_box_bytes(dsx_model m)
+{
+    const size_t fields = sizeof(float2) * (size_t)m->F * m->nh, site = sizeof(float2) * (size_t)n_pairs(m->order) * m->n[2];
+    const size_t budget = (fields + site > 72 * 1024 ? 150 : 72) * 1024;
+    const size_t sites = budget > fields ? std::max<size_t>(1, (budget - fields) / site) : 1;
+    return fields + site * std::min<size_t>(sites, m->S);
+}
+
 // The model's description, plan and device state; on failure create_model_impl
 // releases whatever it allocated.
 dsx_status create_model_body(const dsx_model_desc* d, bool transient, dsx_model m, dsx_model* out)
@@ -1621,23 +1633,21 @@ dsx_status create_model_body(const dsx_model_desc* d, bool transient, dsx_model 
     m->SF = m->S * m->F;
     m->normN = d->norm_N > 0 ? d->norm_N : (double)m->ncell * npos;
     m->nclass = count_classes(d, &m->site_of, &m->class_of);
-    // site chunks for the recombination's LDS budget: level-A buffer of the chunk's
-    // sites plus the staging area of one site (nuclear) or of the chunk (magnetic);
-    // 72 KB keeps two 512-thread blocks per CU, larger plans take up to 150 KB.
-    const bool mag = m->kind == DSX_MAGNETIC;
-    const size_t per_site = sizeof(float2) * (size_t)(mag ? 3 : n_pairs(m->order)) * m->n[2];
-    const size_t stage_fixed = mag ? 0 : sizeof(float2) * (size_t)m->F * m->nh;
-    const size_t stage_site = mag ? sizeof(float2) * 6 * (size_t)m->nh : 0;
-    size_t budget = 72 * 1024;
-    if (stage_fixed + per_site + stage_site > budget) budget = 150 * 1024;
-    const int per_chunk = (int)std::max<size_t>(1, (budget - stage_fixed) / (per_site + stage_site));
-    m->sc_start.clear();
-    for (int i = 0; i < m->S; i += per_chunk) m->sc_start.push_back(i);
-    m->sc_start.push_back(m->S);
-    const int chunk_sites = std::min(per_chunk, m->S);
-    m->bs_elems = (int)(per_site / sizeof(float2)) * chunk_sites;
-    m->xs_elems = (int)((stage_fixed + stage_site * chunk_sites) / sizeof(float2));
-    m->chunk_lds = per_site * chunk_sites + stage_fixed + stage_site * chunk_sites;
+    if (m->kind == DSX_MAGNETIC) {
+        // site chunks of the class form: level-A buffer and staging area of the chunk's sites within
+        // 72 KB, which keeps two 512-thread blocks per CU (one site may take up to 150 KB)
+        const size_t per_site = sizeof(float2) * 3 * (size_t)m->n[2], stage_site = sizeof(float2) * 6 * (size_t)m->nh;
+        const size_t budget = (per_site + stage_site > 72 * 1024 ? 150 : 72) * 1024;
+        const int chunk = (int)std::min<size_t>(m->S, std::max<size_t>(1, budget / (per_site + stage_site)));
+        m->sc_start.clear();
+        for (int i = 0; i < m->S; i += chunk) m->sc_start.push_back(i);
+        m->sc_start.push_back(m->S);
+        m->bs_elems = (int)(per_site / sizeof(float2)) * chunk;
+        m->xs_elems = (int)(stage_site / sizeof(float2)) * chunk;
+        m->chunk_lds = (per_site + stage_site) * chunk;
+    } else {
+        m->chunk_lds = nuclear_box_bytes(m);
+    }
     for (int a = 0; a < 3; ++a) m->plan[a] = make_plan(m->n[a]);
     m->set.assign(m->M, 0);
     (void)hipGetDevice(&m->device);

@@ -1,0 +1,74 @@
+// Host-only checks of C-ABI calls on models, with the runtime and the launchers of
+// fake_runtime.cpp.  Usage: calls_driver CHECK; exit status 0 on success.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "dsx.h"
+#include "fake_runtime.h"
+
+#define CHECK(c)                                                              \
+    do {                                                                      \
+        if (!(c)) {                                                           \
+            std::fprintf(stderr, "check failed at line %d: %s (%s)\n", __LINE__, #c, dsx_last_error()); \
+            std::exit(1);                                                     \
+        }                                                                     \
+    } while (0)
+
+// A nuclear model with S sites in general positions, its sites uploaded, its box |G| <= r n.
+static dsx_model make(int n1, int n2, int n3, int S, int order, int r, bool grid = true)
+{
+    std::vector<double> frac, b;
+    for (int i = 0; i < S; ++i) {
+        for (int a = 0; a < 3; ++a) frac.push_back(0.1 + 0.07 * i + 0.2 * a);
+        b.push_back(1.0);
+    }
+    dsx_model_desc d;
+    std::memset(&d, 0, sizeof(d));
+    for (int a = 0; a < 3; ++a) { d.cell[a] = 1.0; d.cell[3 + a] = 90.0; }
+    d.n[0] = n1; d.n[1] = n2; d.n[2] = n3;
+    d.n_sites = S; d.frac = frac.data(); d.b = b.data();
+    d.kind = DSX_NUCLEAR; d.has_occ = 1; d.taylor_order = order; d.n_configs = 1;
+    dsx_model m = nullptr;
+    CHECK(dsx_create_model(&d, &m) == DSX_OK);
+    std::vector<float> occ((size_t)S * n1 * n2 * n3, 1.f), disp(3 * occ.size(), 0.01f);
+    CHECK(dsx_set_sites(m, 0, occ.data(), order > 0 ? disp.data() : nullptr, nullptr, DSX_HOST) == DSX_OK);
+    if (grid) {
+        const int g0[3] = {-r * n1, -r * n2, -r * n3}, cnt[3] = {2 * r * n1 + 1, 2 * r * n2 + 1, 2 * r * n3 + 1};
+        CHECK(dsx_set_grid(m, g0, cnt) == DSX_OK);
+    }
+    return m;
+}
+
+// Orders and edges whose fields of one site pass the limit on them: models are made, their boxes
+// refused; the largest below it is taken.
+static void large_orders()
+{
+    std::vector<float> out((size_t)5 * 5 * 515);
+    for (int n3 : {231, 232, 233, 240, 250, 256})
+        for (int S : {1, 3, 64}) {
+            dsx_model m = make(1, 1, n3, S, 8, 1);
+            CHECK(dsx_compute_intensity(m, out.data(), DSX_HOST, nullptr) == DSX_ERR_UNSUPPORTED);
+            CHECK(dsx_destroy_model(m) == DSX_OK);
+        }
+    for (int n3 : {40, 90}) {
+        dsx_model m = make(1, 1, n3, 3, 8, 1);
+        CHECK(dsx_compute_intensity(m, out.data(), DSX_HOST, nullptr) == DSX_OK);
+        CHECK(dsx_destroy_model(m) == DSX_OK);
+    }
+    dsx_model m = make(1, 1, 40, 2, 16, 1);
+    CHECK(dsx_compute_intensity(m, out.data(), DSX_HOST, nullptr) == DSX_ERR_UNSUPPORTED);
+    CHECK(dsx_destroy_model(m) == DSX_OK);
+}
+
+int main(int argc, char** argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "large_orders") large_orders();
+    else return 2;
+    fake::reset();
+    std::printf("passed\n");
+    return 0;
+}
