@@ -1384,6 +1384,14 @@ dsx_status ensure_spectra(dsx_model m, hipStream_t st, bool force = false)
     return DSX_OK;
 }
 
+// Waits for a stream however its scope is left, so that host arrays which copies on the stream
+// still read (or write) outlive them.
+struct DrainStream {
+    hipStream_t st;
+    bool on = true;
+    ~DrainStream() { if (on) (void)hipStreamSynchronize(st); }
+};
+
 // Cut the plan's work list down to the rows of `mask` and put it in the model's own list
 // (uploaded on st; `list` holds it until the caller has waited for the stream).
 dsx_status prune_plan(dsx_model m, const Box& bx, const RowMask& mask, LaunchPlan& lp, hipStream_t st, std::vector<int4>& list)
@@ -2347,14 +2355,9 @@ dsx_status dsx_filter_points(dsx_model m, int32_t lanczos_m, int32_t mprime, int
         // (the copy of the point list, staged by the host, comes after the launches: it then runs
         // while the device computes)
         std::vector<int4> cut;
-        auto wait = [&](dsx_status r) {             // `cut` and q stay alive until the copies have run
-            const std::string msg = g_err;
-            (void)hipStreamSynchronize(st);
-            g_err = msg;
-            return r;
-        };
-        if ((s = ensure_spectra(m, st, false)) != DSX_OK) return wait(s);
-        if ((s = run_box(m, bx, m->d_pts, dense_layout(bx), st, use_mask ? &mask : nullptr, &cut)) != DSX_OK) return wait(s);
+        DrainStream drain{st};                      // `cut` and q stay alive until their copies have run
+        if ((s = ensure_spectra(m, st, false)) != DSX_OK) return s;
+        if ((s = run_box(m, bx, m->d_pts, dense_layout(bx), st, use_mask ? &mask : nullptr, &cut)) != DSX_OK) return s;
         HIPCHK(m, hipMemcpyAsync(m->d_q, q, (size_t)npts * 3 * sizeof(double), hipMemcpyHostToDevice, st));
         PointsParams pp{};
         pp.in = m->d_pts; pp.q = m->d_q; pp.out = dout; pp.npts = npts;
@@ -2362,13 +2365,10 @@ dsx_status dsx_filter_points(dsx_model m, int32_t lanczos_m, int32_t mprime, int
         pp.w = w;
         pp.rcut = (float)((1.0 - 1.0 / lanczos_m) / mprime);
         HIPCHK(m, timed("lanczos_points", st, [&] { return launch_lanczos_points(pp, st); }));
-        if (where == DSX_HOST) {
-            HIPCHK(m, hipMemcpyAsync(out, dout, (size_t)npts * sizeof(float), hipMemcpyDeviceToHost, st));
-            HIPCHK(m, hipStreamSynchronize(st));
-        } else {
-            // the point list is a host array read by the copy above: wait before returning
-            HIPCHK(m, hipStreamSynchronize(st));
-        }
+        if (where == DSX_HOST) HIPCHK(m, hipMemcpyAsync(out, dout, (size_t)npts * sizeof(float), hipMemcpyDeviceToHost, st));
+        // the point list is a host array read by the copy above: wait before returning
+        drain.on = false;
+        HIPCHK(m, hipStreamSynchronize(st));
         return DSX_OK;
     });
 }

@@ -63,10 +63,40 @@ static void large_orders()
     CHECK(dsx_destroy_model(m) == DSX_OK);
 }
 
+// A points call that fails after it has put copies on the stream returns only when they have run:
+// they read the caller's points and the call's own work list.
+static void points_errors()
+{
+    const int64_t np = 61;
+    const size_t bytes = np * 3 * sizeof(double);
+    for (int fault = 0; fault < 5; ++fault) {
+        dsx_model m = make(6, 5, 8, 3, 2, 1);
+        std::vector<double>* q = new std::vector<double>();
+        for (int i = 0; i < np; ++i)
+            for (double v : {0.2 * i - 6.0, 1.5, 0.25 * i - 7.0}) q->push_back(v);
+        std::vector<float> out(np);
+        CHECK(dsx_filter_points(m, 2, 2, np, q->data(), out.data(), DSX_HOST, nullptr) == DSX_OK);
+        CHECK(fake::pending == 0);
+        fake::launches.clear();
+        if (fault == 0) fake::fail_copy_bytes = bytes;
+        if (fault == 1) fake::fail_launch = "points";
+        if (fault == 2) fake::fail_copy_bytes = np * sizeof(float);
+        if (fault == 3) fake::fail_launch = "nuclear";
+        if (fault == 4) fake::fail_launch = "bragg";
+        CHECK(dsx_filter_points(m, 2, 2, np, q->data(), out.data(), DSX_HOST, nullptr) == DSX_ERR_DEVICE);
+        CHECK(std::string(dsx_last_error()).size() > 0);
+        CHECK(fake::pending == 0);
+        delete q;
+        fake::reset();
+        CHECK(dsx_destroy_model(m) == DSX_OK);
+    }
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "large_orders") large_orders();
+    else if (what == "points_errors") points_errors();
     else return 2;
     fake::reset();
     std::printf("passed\n");
