@@ -344,12 +344,16 @@ dsx_status dsx_tune_query(dsx_model m, int32_t choice[3], int32_t* tuned);
  * Stockham passes and the number of columns per block of the axis-1 transform in LDS.
  * The autotuner times every order of every grouping of the edge's factor 2^a into 4s
  * and 2s with its odd factors (at most 12 sequences per axis, the default first) on the
- * axes that take Stockham passes -- edges that are a product of two factors <= 16 take
- * register kernels of a fixed order, which a sequence leaves as they are -- and the tiles
- * 16, 32 and 64; the choices join the tune cache line.
+ * axes that take Stockham passes, and the tiles 0, 16, 32 and 64 where the model has an
+ * axis-1 launch of a tile; the choices join the tune cache line.  Edges that are a
+ * product of two factors <= 16, or of one such and a prime from 17 to 61 (to 47 on axes
+ * 2 and 3, which go together), take register kernels of a fixed order, which a sequence
+ * leaves as they are; a box with every edge <= 16 has no axis-1 launch, and n1 = 8, 16
+ * or 32 one without a tile.
  *   radices   [3][16] int32, per axis the radices in pass order, 0-terminated; each
  *             2, 4 or odd (>= 3), product the edge n of the axis; NULL keeps the plans
- *   col_tile  0 (by edge: 64 up to n1 = 64, else 32), 16, 32 or 64
+ *   col_tile  0 (by edge: 256 where one pass in registers takes a line, n1 <= 16 or a prime
+ *             to 61, else 64 up to n1 = 64 and 32 above), 16, 32 or 64
  * dsx_tune_set_fft marks the model tuned and its spectra stale.  DSX_ERR_ARG for an
  * invalid sequence or a tile whose LDS (8 n1 (1 + 2 tile) bytes) exceeds 160 KiB.
  * dsx_tune_query_fft writes the current sequences (0-padded) and tile.

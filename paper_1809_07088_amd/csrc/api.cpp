@@ -2429,6 +2429,13 @@ void tune_store(const std::string& key, int v, int fc, int t1, const FftChoice& 
       << " " << fft.plan[2] << "\n";
 }
 
+// The limit on tiles of dsx_tune_set_fft: both LDS buffers of the Stockham passes (the register
+// transforms take one, but a tile the tuner picks must be one that can be set).
+bool axis1_tile_fits(dsx_model m, int tile)
+{
+    return tile == 0 || sizeof(float2) * (size_t)m->n[0] * (1 + 2 * (size_t)tile) <= 160 * 1024;
+}
+
 // Minimum over `reps` timed runs of fn() on stream st (milliseconds), or < 0 on error.
 template <typename Fn>
 float time_min(hipStream_t st, int reps, Fn fn)
@@ -2494,9 +2501,8 @@ dsx_status dsx_autotune(dsx_model m, int32_t lanczos_m, void* hip_stream)
             if (t >= 0.f && (best < 0.f || t < best)) { best = t; best_fc = cand; }
         }
         m->tune_fchunk = best_fc;
-        // FFT radix orders of the axes the LDS kernels transform (the register kernels of
-        // edges 8, 16, 32 have a fixed order), one axis at a time
-        // (the register transforms have one order: only the Stockham passes are tuned)
+        // FFT radix orders of the axes that take Stockham passes (the register transforms have one
+        // order), one axis at a time
         const auto reg = [](int n, int prime) { int a, b; return split_length(n, &a, &b, prime); };
         for (int a : {2, 1, 0}) {
             const bool used = a == 0 ? !reg(m->n[0], kMaxRegPrime)
@@ -2513,12 +2519,13 @@ dsx_status dsx_autotune(dsx_model m, int32_t lanczos_m, void* hip_stream)
             }
             m->plan[a] = bestp;
         }
-        // columns per block of the LDS axis-1 FFT
-        if (!fft_reg_supported(m->n[0])) {
+        // columns per block of the axis-1 FFT: the default first (256 where one pass holds a line in
+        // registers, else a tile in LDS), then the tiles dsx_tune_set_fft takes
+        if (!fft_reg_supported(m->n[0]) && !whole_box(m)) {
             best = -1.f;
             int best_tc = 0;
-            for (int cand : {16, 32, 64}) {
-                if (sizeof(float2) * (size_t)m->n[0] * (1 + 2 * (size_t)cand) > 160 * 1024) continue;
+            for (int cand : {0, 16, 32, 64}) {
+                if (!axis1_tile_fits(m, cand)) continue;
                 m->tune_tc = cand;
                 const float t = time_min(st, 3, [&] { return ensure_spectra(m, st, true); });
                 if (t >= 0.f && (best < 0.f || t < best)) { best = t; best_tc = cand; }
@@ -2600,7 +2607,7 @@ dsx_status dsx_tune_set_fft(dsx_model m, const int32_t* radices, int32_t col_til
         if (s != DSX_OK) return s;
         if (!(col_tile == 0 || col_tile == 16 || col_tile == 32 || col_tile == 64))
             return fail(DSX_ERR_ARG, "the axis-1 column tile must be 0, 16, 32 or 64");
-        if (col_tile && sizeof(float2) * (size_t)m->n[0] * (1 + 2 * (size_t)col_tile) > 160 * 1024)
+        if (!axis1_tile_fits(m, col_tile))
             return fail(DSX_ERR_ARG, "the axis-1 column tile does not fit the LDS at this edge");
         AxisPlan np[3] = {m->plan[0], m->plan[1], m->plan[2]};
         if (radices) {

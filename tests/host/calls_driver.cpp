@@ -92,11 +92,54 @@ static void points_errors()
     }
 }
 
+// The tuner's choice of columns per axis-1 block: the default (0) is among the candidates, and
+// nothing is timed that the model does not launch or dsx_tune_set_fft would refuse.
+static int g_best_tc = 0;
+static double tile_cost(const fake::Launch& l)
+{
+    return l.name == "fft_axis1" && l.tc != g_best_tc ? 2.0 : 1.0;
+}
+
+static int tuned_tile(int n1, int n2, int n3, int best_tc)
+{
+    dsx_model m = make(n1, n2, n3, 2, 0, 1);
+    fake::launches.clear();
+    fake::cost = tile_cost;
+    g_best_tc = best_tc;
+    CHECK(dsx_autotune(m, 0, nullptr) == DSX_OK);
+    int32_t radices[48], tile = -1, choice[3], tuned = 0;
+    CHECK(dsx_tune_query_fft(m, radices, &tile) == DSX_OK && dsx_tune_query(m, choice, &tuned) == DSX_OK && tuned == 1);
+    CHECK(dsx_tune_set_fft(m, nullptr, tile) == DSX_OK);
+    CHECK(dsx_destroy_model(m) == DSX_OK);
+    fake::cost = nullptr;
+    return tile;
+}
+
+static void tuned_tiles()
+{
+    unsetenv("DSX_TUNE_CACHE");
+    CHECK(tuned_tile(12, 40, 40, 256) == 0);       // one pass: the default of 256 columns
+    CHECK(tuned_tile(47, 4, 4, 256) == 0);
+    CHECK(tuned_tile(12, 40, 40, 32) == 32);
+    CHECK(tuned_tile(47, 4, 4, 64) == 64);
+    CHECK(tuned_tile(40, 4, 4, 64) == 0);          // two passes: 64 is the default
+    CHECK(tuned_tile(40, 4, 4, 16) == 16);
+    CHECK(tuned_tile(67, 4, 4, 32) == 0);          // Stockham passes
+    CHECK(tuned_tile(67, 4, 4, 16) == 16);
+    CHECK(tuned_tile(40, 4, 4, -1) == 0);          // none better: the default stays
+    CHECK(tuned_tile(240, 2, 2, 64) == 0);         // 64 columns of 240 are past the limit
+    for (const fake::Launch& l : fake::launches) CHECK(l.name != "fft_axis1" || l.tc < 64);
+    CHECK(tuned_tile(12, 12, 12, 32) == 0);        // transformed whole: no axis-1 launch to tune
+    for (const fake::Launch& l : fake::launches) CHECK(l.name != "fft_axis1");
+    CHECK(tuned_tile(32, 20, 20, 16) == 0);        // a fixed kernel
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "large_orders") large_orders();
     else if (what == "points_errors") points_errors();
+    else if (what == "tuned_tiles") tuned_tiles();
     else return 2;
     fake::reset();
     std::printf("passed\n");
