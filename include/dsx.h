@@ -321,10 +321,12 @@ dsx_status dsx_batch_destroy(dsx_batch b);
 
 /*
  * Autotuner: times the kernel variants of a ready model for its key (kind, n,
- * sites, order, configurations, box, filter) -- the recombination form, the number
+ * sites, order, configurations, box, filter, and the site positions and factors as far
+ * as they choose its kernels) -- the recombination form, the number
  * of fields per FFT plane block and the filter's plane segment -- and keeps the
  * fastest.  With DSX_TUNE_CACHE naming a file, choices are read from / appended to
- * it (one line per key), so a key is tuned once and then always gets the same plan.
+ * it (one line per key), so a key is tuned once and then always gets the same plan;
+ * lines timed with an earlier build's kernels have other keys.
  * Runs kernels on hip_stream and waits for them.
  */
 dsx_status dsx_autotune(dsx_model m, int32_t lanczos_m, void* hip_stream);

@@ -569,6 +569,18 @@ bool fold_applies(dsx_model m)
     return true;
 }
 
+// The parity form: every r_mu3 a multiple of 1/2 (exactly, as given); a |Q|-dependent nuclear
+// scattering factor needs the classes apart at level C (class form).
+bool parity_applies(dsx_model m)
+{
+    if (m->kind != DSX_NUCLEAR || m->has_ff || m->order > kMaxOrderFast) return false;
+    for (int i = 0; i < m->S; ++i) {
+        const double t2 = 2.0 * m->frac[3 * i + 2];
+        if (t2 != std::floor(t2)) return false;
+    }
+    return true;
+}
+
 // Configurations a block of the sites form takes side by side: what 512 threads and 64 KB of
 // level-A buffers hold (bs float2 elements a plane and configuration).
 int sites_configs(int M, int npl, int gthreads, int bs)
@@ -1037,14 +1049,10 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
     for (int i = 0; i < m->S; ++i) { p.site_of[i] = m->site_of[i]; p.class_of[i] = m->class_of[i]; }
     p.bs_elems = m->bs_elems;
     p.xs_elems = m->xs_elems;
-    // parity form: every r_mu3 a multiple of 1/2 (exactly, as given); a |Q|-dependent
-    // nuclear scattering factor needs the classes apart at level C (class form)
     p.nuc_ff = (m->kind == DSX_NUCLEAR && m->has_ff) ? 1 : 0;
-    p.parity = (m->kind == DSX_NUCLEAR && !p.nuc_ff && m->order <= kMaxOrderFast) ? 1 : 0;
+    p.parity = parity_applies(m) ? 1 : 0;
     for (int i = 0; i < m->S; ++i) {
-        const double t2 = 2.0 * m->frac[3 * m->site_of[i] + 2];
-        if (t2 != std::floor(t2)) p.parity = 0;
-        const long a2 = (long)std::floor(t2);
+        const long a2 = (long)std::floor(2.0 * m->frac[3 * m->site_of[i] + 2]);
         p.class_sign[m->class_of[i]] = (a2 % 2 == 0) ? 1 : -1;
     }
     const double C = mag ? 0.07265 : 1.0;
@@ -2378,11 +2386,18 @@ dsx_status dsx_filter_points(dsx_model m, int32_t lanczos_m, int32_t mprime, int
 // ---------------------------------------------------------------------------- autotuner
 namespace {
 
+// The key of a cache line: the sizes, what chooses the kernel forms (scattering factors, the
+// Debye-Waller order, the r3 classes, folding and parity), and the set of kernels the times were
+// taken with, which is counted up when kernels that the choices steer are replaced (lines of other
+// sets stay in the file and are passed by).
+constexpr int kTuneKernels = 2;
+
 std::string tune_key(dsx_model m, int lm)
 {
     std::ostringstream k;
-    k << "gfx950|" << m->kind << "|" << m->n[0] << "," << m->n[1] << "," << m->n[2] << "|S" << m->S
-      << "|N" << m->order << "|M" << m->M << "|occ" << m->has_occ << "|box" << m->box.g0[0] << ","
+    k << "gfx950|k" << kTuneKernels << "|" << m->kind << "|" << m->n[0] << "," << m->n[1] << "," << m->n[2] << "|S" << m->S
+      << "|N" << m->order << "|ff" << m->has_ff << "|dw" << m->dw_order << "|c" << m->nclass << "|f" << fold_applies(m)
+      << "|p" << parity_applies(m) << "|M" << m->M << "|occ" << m->has_occ << "|box" << m->box.g0[0] << ","
       << m->box.g0[1] << "," << m->box.g0[2] << "," << m->box.cnt[0] << "," << m->box.cnt[1] << ","
       << m->box.cnt[2] << "|m" << lm;
     return k.str();

@@ -17,28 +17,29 @@
         }                                                                     \
     } while (0)
 
-// A nuclear model with S sites in general positions, its sites uploaded, its box |G| <= r n.
-static dsx_model make(int n1, int n2, int n3, int S, int order, int r, bool grid = true)
+// A nuclear model with S sites in general positions (or, with grid > 0, on multiples of 1/grid along
+// axes 2 and 3), its sites uploaded, its box |G| <= r n.
+static dsx_model make(int n1, int n2, int n3, int S, int order, int r, int grid = 0, bool ff = false)
 {
-    std::vector<double> frac, b;
+    std::vector<double> frac, b, f;
     for (int i = 0; i < S; ++i) {
-        for (int a = 0; a < 3; ++a) frac.push_back(0.1 + 0.07 * i + 0.2 * a);
+        for (int a = 0; a < 3; ++a) frac.push_back(grid > 0 && a > 0 ? (double)(i % grid) / grid : 0.1 + 0.07 * i + 0.2 * a);
         b.push_back(1.0);
+        for (double v : {0.4, 20.0, 0.5, 7.0, 0.1, 2.0, 0.0}) f.push_back(v);
     }
     dsx_model_desc d;
     std::memset(&d, 0, sizeof(d));
     for (int a = 0; a < 3; ++a) { d.cell[a] = 1.0; d.cell[3 + a] = 90.0; }
     d.n[0] = n1; d.n[1] = n2; d.n[2] = n3;
     d.n_sites = S; d.frac = frac.data(); d.b = b.data();
+    d.ff = ff ? f.data() : nullptr;
     d.kind = DSX_NUCLEAR; d.has_occ = 1; d.taylor_order = order; d.n_configs = 1;
     dsx_model m = nullptr;
     CHECK(dsx_create_model(&d, &m) == DSX_OK);
     std::vector<float> occ((size_t)S * n1 * n2 * n3, 1.f), disp(3 * occ.size(), 0.01f);
     CHECK(dsx_set_sites(m, 0, occ.data(), order > 0 ? disp.data() : nullptr, nullptr, DSX_HOST) == DSX_OK);
-    if (grid) {
-        const int g0[3] = {-r * n1, -r * n2, -r * n3}, cnt[3] = {2 * r * n1 + 1, 2 * r * n2 + 1, 2 * r * n3 + 1};
-        CHECK(dsx_set_grid(m, g0, cnt) == DSX_OK);
-    }
+    const int g0[3] = {-r * n1, -r * n2, -r * n3}, cnt[3] = {2 * r * n1 + 1, 2 * r * n2 + 1, 2 * r * n3 + 1};
+    CHECK(dsx_set_grid(m, g0, cnt) == DSX_OK);
     return m;
 }
 
@@ -134,12 +135,43 @@ static void tuned_tiles()
     CHECK(tuned_tile(32, 20, 20, 16) == 0);        // a fixed kernel
 }
 
+// The tune cache: a line serves the models that take the same kernels, and lines written for other
+// kernels of the same sizes (an earlier build's among them) are passed by.
+static bool tune_times(dsx_model m)
+{
+    fake::launches.clear();
+    CHECK(dsx_autotune(m, 0, nullptr) == DSX_OK);
+    const bool timed = !fake::launches.empty();
+    CHECK(dsx_destroy_model(m) == DSX_OK);
+    return timed;
+}
+
+static void tune_keys()
+{
+    const char* path = getenv("DSX_TUNE_CACHE");
+    CHECK(path);
+    FILE* f = std::fopen(path, "w");
+    CHECK(f);
+    std::fputs("gfx950|0|12,40,40|S4|N2|M1|occ1|box-12,-40,-40,25,81,81|m0\t2 4 4 16 4x3 4x2x5 4x2x5\n", f);
+    std::fclose(f);
+    CHECK(tune_times(make(12, 40, 40, 4, 2, 1)));                // not the line above
+    CHECK(!tune_times(make(12, 40, 40, 4, 2, 1)));               // its own
+    CHECK(tune_times(make(12, 40, 40, 4, 2, 1, 0, true)));       // factors that depend on |Q|: class form
+    CHECK(!tune_times(make(12, 40, 40, 4, 2, 1, 0, true)));
+    CHECK(tune_times(make(12, 40, 40, 4, 2, 1, 2)));             // halves: folded, parity sets
+    CHECK(!tune_times(make(12, 40, 40, 4, 2, 1, 4)));            // quarters: four classes, as in general positions
+    CHECK(tune_times(make(12, 40, 40, 4, 2, 1, 1)));             // all sites in one class
+    CHECK(!tune_times(make(12, 40, 40, 4, 2, 1, 2)));
+    CHECK(!tune_times(make(12, 40, 40, 4, 2, 1)));
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "large_orders") large_orders();
     else if (what == "points_errors") points_errors();
     else if (what == "tuned_tiles") tuned_tiles();
+    else if (what == "tune_keys") tune_keys();
     else return 2;
     fake::reset();
     std::printf("passed\n");

@@ -28,7 +28,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["large_orders", "points_errors", "tuned_tiles"])
+@pytest.mark.parametrize("check", ["large_orders", "points_errors", "tuned_tiles", "tune_keys"])
 def test_host_calls(driver, check, tmp_path):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1", UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1",
                DSX_TUNE_CACHE=str(tmp_path / "tune.txt"))
