@@ -363,3 +363,16 @@ def test_one_site_tiles_with_small_and_large_weights(M, b, amp, norm):
     m.g0, m.count = (-5, -6, -45), (9, 11, 83)
     say(f"one site b={b} M={M}")
     sampled_parity(m, most=1500)
+
+
+# ------------------------------------------------------------------ rows of a prime length, planes past the LDS
+@pytest.mark.parametrize("n,kind,order,M", [((2, 188, 205), synth.NUCLEAR, 1, 1), ((1, 141, 246), synth.NUCLEAR, 0, 2), ((2, 185, 188), synth.MAGNETIC, 0, 1),
+                                            ((1, 235, 235), synth.NUCLEAR, 1, 1), ((3, 244, 208), synth.NUCLEAR, 0, 1), ((1, 240, 253), synth.MAGNETIC, 0, 2)])
+def test_plane_rows_route_of_prime_edges(n, kind, order, M):
+    """Rows along axis 3 per block, then axis 2 in place, where one of those edges or both have a
+    prime factor from 17 to 47, odd and even numbers of rows (244 = 61 x 4: Stockham rows)."""
+    m = synth.random_model(3600 + n[1] + n[2], n=n, S=1, M=M, order=order, kind=kind, with_disp=order > 0, sigma=0.03,
+                           cell=None if kind == synth.NUCLEAR else [6.0, 7.0, 8.0, 90.0, 90.0, 90.0])
+    m.g0, m.count = (-2, -9, -9), (5, 19, 19)
+    say(f"row route of prime edges n={n} kind={kind}")
+    sampled_parity(m, order if order and kind == synth.NUCLEAR else None, 1500)
