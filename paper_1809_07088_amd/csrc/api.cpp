@@ -755,10 +755,12 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
         // in 47 KB 176), so larger passes are for small n3; one configuration takes up to 48 KB.
         // Rows that are staged one by one (q2 = 0) are bound by the sums over their classes, where a
         // pass of four costs more than two of two (3 sites, 20^3 cells, five configurations: 69 us
-        // at four a pass, 45 at two, 49 at one), and one with an idle half more than two of one
-        // (6 sites, 12^3 cells, three configurations: 68 and 59 us)
+        // at four a pass, 45 at two, 49 at one), and passes of two that leave a quarter of their
+        // places idle more than passes of one (6 sites, 12^3 cells, three configurations: 68 us at
+        // two a pass, 59 at one; with five, a sixth of the places idle, two a pass are faster)
         for (int mc : {4, 2, 1}) {
-            if (mc > 1 && (mc / 2 >= m->M || (q2 == 0 && (mc > 2 || m->M == 3)))) continue;
+            const int places = (m->M + mc - 1) / mc * mc;
+            if (mc > 1 && (mc / 2 >= m->M || (q2 == 0 && (mc > 2 || 4 * (places - m->M) >= places)))) continue;
             const bool passes = m->M > mc;
             const size_t budget = (mc > 1 ? 32 : passes ? 64 : 48) * 1024 / sizeof(float2);
             int cs = S;
