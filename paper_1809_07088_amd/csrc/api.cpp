@@ -21,6 +21,7 @@
 #include <sstream>
 #include <array>
 #include <climits>
+#include <limits>
 #include <map>
 #include <tuple>
 #include <mutex>
@@ -1065,6 +1066,9 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         const int k = std::max(-120, std::min(120, eb + (es + (es & 1)) / 2));
         p.one_pre = (float)std::ldexp(1.0, k);
         p.one_w = (float)std::ldexp(mb * mb * ms, 2 * (eb - k) + es);
+        // a weight past float32: infinite, or in ensembles no value, as the form that multiplies
+        // the amplitudes by it has it there
+        if (m->M > 2 && !std::isfinite((float)m->b[0])) p.one_w = std::numeric_limits<float>::quiet_NaN();
     }
     for (int i = 0; i < 9; ++i) p.recip[i] = (float)m->recip[i];
     p.ff_uniform = 1;

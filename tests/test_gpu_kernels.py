@@ -376,3 +376,15 @@ def test_plane_rows_route_of_prime_edges(n, kind, order, M):
     m.g0, m.count = (-2, -9, -9), (5, 19, 19)
     say(f"row route of prime edges n={n} kind={kind}")
     sampled_parity(m, order if order and kind == synth.NUCLEAR else None, 1500)
+
+
+@pytest.mark.parametrize("M", [1, 2, 3, 20])
+@pytest.mark.parametrize("b", [np.inf, np.nan, 1e160])
+def test_one_site_tiles_with_a_weight_past_float32(M, b):
+    """No finite value anywhere, in ensembles none at all."""
+    m = synth.random_model(3700 + M, n=(6, 5, 18), S=1, M=M, order=0, with_disp=False)
+    m.b[:] = b
+    m.g0, m.count = (-5, -6, -20), (9, 11, 41)
+    say(f"one site b={b} M={M}")
+    I = gpu_intensity(m)
+    assert not np.any(np.isfinite(I)) and (M < 3 or np.all(np.isnan(I)))
