@@ -1780,7 +1780,7 @@ hipError_t launch_recombine_magnetic_rows(const RecombParams& p, int block, size
 // stepped from row to row), so a voxel costs its loads, |F|^2 and one store, and every
 // load and store of a wave is one contiguous run.  For one or two sites x configurations
 // this beats the levelled forms, whose blocks serve one column of the grid each.
-constexpr int kDirectThreads = 256, kDirectRows = 16;
+constexpr int kDirectThreads = 256, kDirectRows = 16, kDirectGroup = 16;
 constexpr int kDirectWaves = kDirectThreads / 64;
 
 // a / b for a < 2^32 through the float64 reciprocal rb of b (relative error well below
@@ -1846,6 +1846,49 @@ __device__ __forceinline__ void recombine_direct_body(PT P, const int bx)
     const int k20 = __builtin_amdgcn_readfirstlane(P.g0[1] - n2 * floordiv_exact(P.g0[1], n2, __builtin_amdgcn_rcpf((float)n2)));
     auto* op = gptr(P.out) + P.ooff + (size_t)r0 * P.opitch + i3;
     const float cj = half ? -1.f : 1.f;
+    if (P.S == 1) {
+        // one site: the phase has modulus b, so |F_m|^2 = b^2 |X_m(k)|^2 exactly.  Rows go
+        // in groups: the group's spectra offsets first (a direct-form spectrum has fewer than
+        // 2^32 elements), then all its loads of a configuration in flight at once
+        const float2* __restrict__ X0 = P.X;
+        const float pre = P.one_pre, w = P.one_w;
+        for (int g = 0; g < nr; g += kDirectGroup) {
+            uint32_t colr[kDirectGroup];
+#pragma unroll
+            for (int r = 0; r < kDirectGroup; ++r) {
+                const uint32_t colp = (uint32_t)((k1 * n2 + k2) * SFnh);
+                const uint32_t colm = (uint32_t)(((k1 ? n1 - k1 : 0) * n2 + (k2 ? n2 - k2 : 0)) * SFnh);
+                colr[r] = (half ? colm : colp) + (uint32_t)koff;
+                if (++i2 == (int)c1) {
+                    i2 = 0;
+                    k2 = k20;
+                    k1 = (k1 + 1 == n1) ? 0 : k1 + 1;
+                } else {
+                    k2 = (k2 + 1 == n2) ? 0 : k2 + 1;
+                }
+            }
+            const int ng = min(kDirectGroup, nr - g);
+            float I[kDirectGroup];
+#pragma unroll
+            for (int r = 0; r < kDirectGroup; ++r) I[r] = 0.f;
+            for (int m = 0; m < P.M; ++m) {
+                const float2* __restrict__ Xm = X0 + (size_t)m * cstride;
+                float2 xv[kDirectGroup];
+#pragma unroll
+                for (int r = 0; r < kDirectGroup; ++r) xv[r] = r < ng ? ldg2(Xm, colr[r]) : make_float2(0.f, 0.f);
+#pragma unroll
+                for (int r = 0; r < kDirectGroup; ++r) {
+                    const float xr = pre * xv[r].x, xi = pre * xv[r].y;
+                    I[r] += xr * xr + xi * xi;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < kDirectGroup; ++r)
+                if (r < ng) op[(size_t)r * P.opitch] = I[r] * w;
+            op += (size_t)kDirectGroup * P.opitch;
+        }
+        return;
+    }
     for (int r = 0; r < nr; ++r) {
         const size_t colp = ((size_t)k1 * n2 + k2) * SFnh;                                   // X(k)
         const size_t colm = ((size_t)(k1 ? n1 - k1 : 0) * n2 + (k2 ? n2 - k2 : 0)) * SFnh;   // X(-k), conjugated
@@ -2026,13 +2069,34 @@ static hipError_t launch_recombine_tiles(const RecombParams& p, hipStream_t st)
     return dispatch(k_recombine_tiles, k_recombine_tiles_merged, (unsigned)((rows + r - 1) / r), kTileThreads, lds, st, q);
 }
 
+// One site, one or two configurations: tiles against the direct form (more configurations always
+// take tiles).  A tile forms n3 values a row and writes c2 of them, so it pays by the repeats
+// c2 / n3, and more where rows start on 16 bytes.  Measured, direct and tiles, one configuration:
+//   2 repeats    32^3 cells 7.0 and 12.0 us, 64^3 8.4 and 14.1, 100^3 15.9 and 18.5; only rows
+//                under 16 values, which leave most lanes of the direct form idle, gain (100 x 100 x 2
+//                at 4 repeats 14.7 and 6.9)
+//   4 repeats    rows on 16 bytes: 1024 boxes of 48^3 188 and 110, 24^3 two configurations 8.8 and
+//                10.4, 48^3 13.8 and 13.2, 64^3 21.8 and 20.1; others: 490 boxes of 53 x 37 x 49
+//                67 and 128, 24^3 7.7 and 10.0, 48^3 16.1 and 15.8, 64^3 25.9 and 24.6
+//   6 repeats    rows on 16 bytes: 24^3 10.1 and 8.7, 48^3 29.2 and 21.8; others: 20^3 8.2 and 9.2,
+//                31^3 13.9 and 13.3, 48^3 30.4 and 28.2
+//   8 and more   others: 16^3 9.7 and 9.5, 20^3 11.6 and 10.4, 16^3 at 16 repeats 25.9 and 20.4
+static bool tiles_pay(const RecombParams& p)
+{
+    const int n3 = p.n3, c2 = p.cnt[2];
+    if (p.M > 2 || c2 < 16) return true;
+    const long long vox = (long long)p.planes * p.cnt[1] * c2;
+    if (p.opitch % 4 == 0) return c2 >= 6 * n3 || (c2 >= 4 * n3 && (n3 <= 16 || vox >= (4 << 20)));
+    return (c2 >= 8 * n3 && vox >= (1 << 20)) || (c2 >= 4 * n3 && vox >= (6 << 20));
+}
+
 hipError_t launch_recombine_direct(const RecombParams& p, hipStream_t st)
 {
     if (p.planes < 0 || p.planes > p.cnt[0]) return hipErrorInvalidValue;
     const unsigned long long rows = (unsigned long long)p.planes * p.cnt[1];
     if (rows == 0 || p.cnt[2] == 0) return hipSuccess;
     if (rows * (unsigned long long)p.cnt[2] >= (1ULL << 32)) return hipErrorInvalidValue;
-    if (p.S == 1 && rows < (1ULL << 31)) return launch_recombine_tiles(p, st);
+    if (p.S == 1 && rows < (1ULL << 31) && tiles_pay(p)) return launch_recombine_tiles(p, st);
     const unsigned long long waves = (rows + kDirectRows - 1) / kDirectRows * ((p.cnt[2] + 63) / 64);
     return dispatch(k_recombine_direct, k_recombine_direct_merged, (unsigned)((waves + kDirectWaves - 1) / kDirectWaves),
                     kDirectThreads, 0, st, p);

@@ -388,3 +388,17 @@ def test_one_site_tiles_with_a_weight_past_float32(M, b):
     say(f"one site b={b} M={M}")
     I = gpu_intensity(m)
     assert not np.any(np.isfinite(I)) and (M < 3 or np.all(np.isnan(I)))
+
+
+@pytest.mark.parametrize("n,g0,count", [((6, 7, 12), (-12, -14, -24), (24, 28, 48)), ((6, 7, 12), (-12, -14, -24), (25, 29, 49)),
+                                        ((5, 6, 20), (-10, -12, -60), (21, 25, 120)), ((5, 6, 20), (-10, -12, -40), (21, 25, 81)),
+                                        ((8, 7, 9), (-60, -60, -72), (121, 121, 145)), ((31, 30, 31), (-93, -93, -93), (187, 187, 187)),
+                                        ((40, 41, 6), (-41, -42, 1), (83, 85, 7)), ((9, 9, 24), (-72, -72, -48), (145, 145, 96))])
+@pytest.mark.parametrize("M", [1, 2])
+def test_one_site_tiles_or_voxels(n, g0, count, M):
+    """Both sides of the rule between the tiled rows and the direct form: few and many repeats along
+    axis 3, rows on 16 bytes and not, small and large boxes, rows of few values."""
+    m = synth.random_model(3800 + sum(n) + M, n=n, S=1, M=M, order=0, with_disp=False)
+    m.g0, m.count = g0, count
+    say(f"one site n={n} M={M} box={g0}+{count}")
+    sampled_parity(m)
