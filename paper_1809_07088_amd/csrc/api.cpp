@@ -750,42 +750,59 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
         };
         const int q2 = grid_of(1);
         const int q1 = grid_of(0);
-        // configurations a pass: four, two or one, the first that holds the row residues (or four
-        // rows staged one by one) in 32 KB.  Blocks in flight count for more than what a pass of
-        // several saves (16 sites, 40^3 cells, two configurations: one a pass in 30 KB 130 us, two
-        // in 47 KB 176), so larger passes are for small n3; one configuration takes up to 48 KB.
-        // Rows that are staged one by one (q2 = 0) are bound by the sums over their classes, where a
-        // pass of four costs more than two of two (3 sites, 20^3 cells, five configurations: 69 us
-        // at four a pass, 45 at two, 49 at one), and passes of two that leave a quarter of their
-        // places idle more than passes of one (6 sites, 12^3 cells, three configurations: 68 us at
-        // two a pass, 59 at one; with five, a sixth of the places idle, two a pass are faster)
+        // Configurations a pass: four, two or one.  What several share is level C (a voxel's |Q|, form
+        // factor and projection), what they cost is LDS, that is blocks in flight, so they pay while
+        // a block stays small, or (to 32 KB) while a row has several supercells along axis 3 and its
+        // level C is not small beside the site spectra of level A.  Measured, one and two a pass
+        // (M = 17): 4 sites 12^3 in 13 KB 142 and 106 us, 24^3 in 20 KB 136 and 112, 40^3 (two
+        // supercells) in 25 KB 137 and 198; 2 sites 62^3 in 13 KB 187 and 173, 25 KB 203 and 261;
+        // 16 sites 12^3 in 22 KB 131 and 122, 18^3 in 21 KB 166 and 194, 40^3 in 31 KB 373 and 711.
+        // Two and four: 4 sites 8^3 in 15 KB 92 and 80, 18^3 in 29 KB 87 and 78; 2 sites 62^3 in
+        // 25 KB 173 and 222; 16 sites 12^3 in 31 KB 122 and 132.  Places that idle in the last pass,
+        // and columns cut into parts, undo the gain (6 sites 12^3, M = 3: one a pass 45 us, two 47; 5
+        // sites 27^3, M = 2: 31 and 43), as do residue rows that no longer fit (12 sites on thirds,
+        // 16^3, M = 10: one a pass 205, four 446).
+        const int most = std::min(kMagRowsMaxRows, std::max(1, maxH2));
         for (int mc : {4, 2, 1}) {
-            const int places = (m->M + mc - 1) / mc * mc;
-            if (mc > 1 && (mc / 2 >= m->M || (q2 == 0 && (mc > 2 || 4 * (places - m->M) >= places)))) continue;
+            const int idle = (m->M + mc - 1) / mc * mc - m->M, places = m->M + idle;
+            if (mc > 1 && (mc / 2 >= m->M || 8 * idle > 3 * places)) continue;
             const bool passes = m->M > mc;
-            const size_t budget = (mc > 1 ? 32 : passes ? 64 : 48) * 1024 / sizeof(float2);
+            // (one configuration: three blocks a CU)
+            const size_t budget = (mc > 1 ? 32 : passes ? 44 : 48) * 1024 / sizeof(float2);
             int cs = S;
             while (cs > 1 && (size_t)mc * cs * 3 * n3 * sizeof(float2) > 12 * 1024) cs = (cs + 1) / 2;
             // (every row takes its sums over the passes, staged or not)
             const size_t fixed = magnetic_rows_lds_elems(mc, 0, cs, S, NC, n3, t.nH3span, 0);
             const size_t per_row = magnetic_rows_lds_elems(mc, 1, 0, S, NC, n3, 0, 0);
-            const size_t per_sum = passes ? (size_t)(bx.cnt[2] + 1) / 2 : 0;
-            const int most = std::min(kMagRowsMaxRows, std::max(1, maxH2));
+            const size_t per_sum = magnetic_rows_lds_sums(m->M, mc) ? (size_t)(bx.cnt[2] + 1) / 2 : 0;
             // residue rows: every row of a column in one block when q2 staged rows fit; else the
-            // rows are staged one by one, as many as fit
+            // rows are staged one by one, as many as fit, in even parts
             int qm2 = 0, rows = 0;
             if (q2 > 0 && fixed + std::min(q2, most) * per_row + most * per_sum <= budget) {
                 qm2 = q2;
                 rows = most;
             } else if (fixed < budget) {
                 rows = std::min(most, (int)((budget - fixed) / (per_row + per_sum)));
-                // (three blocks a CU: 10 sites, 62^3 cells, three configurations ran at 947 us with
-                // as many rows as 64 KB hold, two blocks, and at 541 with 48 KB)
-                while (rows > 1 && fixed + rows * (per_row + per_sum) > 48 * 1024 / sizeof(float2)) --rows;
+            } else if (mc == 1 && fixed + per_row <= 48 * 1024 / sizeof(float2)) {
+                rows = 1;
             }
-            if (rows < 1 || (mc > 1 && rows < std::min(most, 4))) continue;
+            if (rows < 1 || (mc > 1 && (rows < std::min(most, 4) || (q2 > 0 && qm2 == 0)))) continue;
+            if (mc > 1) {
+                const size_t lds = sizeof(float2) * (fixed + (qm2 ? std::min(rows, qm2) : rows) * per_row + rows * per_sum);
+                const double level_c = (double)most * bx.cnt[2] / (3.0 * S * n3);
+                const bool idles = 4 * idle >= places;
+                const bool several = bx.cnt[2] >= 3 * n3 && level_c >= (idles ? 1.6 : 1.0) && !(idles && passes) &&
+                                     (rows == most || (!idles && (bx.cnt[2] >= 8 * n3 || n3 < 20)));
+                if (lds > 18 * 1024 && !(several && (mc == 2 || lds <= 30 * 1024 || level_c >= 2.0))) continue;
+            }
+            if (qm2 == 0) rows = (most + (most + rows - 1) / rows - 1) / ((most + rows - 1) / rows);
+            // planes share a block where one pass takes all configurations, and for several of them
+            // only where that leaves blocks enough (4 sites 8^3, M = 2, 320 blocks before: 23 us
+            // shared, 16 not; 2 sites 32^3, 3072 blocks: 16 and 20)
+            const long long blocks = (long long)(friedel ? (bx.cnt[0] + 1) / 2 : bx.cnt[0]) * std::min(n2, bx.cnt[1]) *
+                                     ((std::max(1, maxH2) + rows - 1) / rows);
             t.qmod2_mr = qm2;
-            t.qmod1_mr = passes ? 0 : q1;
+            t.qmod1_mr = passes || (mc > 1 && blocks < 2048) ? 0 : q1;
             t.rows_mr = rows; t.csites_mr = cs; t.mc_mr = mc;
             break;
         }
@@ -1125,7 +1142,7 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         lp.block = std::max(64, (bx.cnt[2] + 63) / 64 * 64);
         const int staged = tb->qmod2_mr > 0 ? std::min(tb->rows_mr, tb->qmod2_mr) : tb->rows_mr;
         lp.lds = sizeof(float2) * magnetic_rows_lds_elems(p.mg, staged, tb->csites_mr, m->S, m->nclass, n3, tb->nH3span,
-                                                          m->M > p.mg ? p.rows * bx.cnt[2] : 0);
+                                                          magnetic_rows_lds_sums(m->M, p.mg) ? p.rows * bx.cnt[2] : 0);
         limit = lp.lds;
     }
     if (!mag) {

@@ -349,6 +349,8 @@ constexpr int kMagRowsMaxThreads = 512;
 constexpr int kMagRowsMaxRows = 16;
 constexpr int kMagRowsMaxClasses = 8;   // the per-residue class sums need q <= nclass <= this
 hipError_t launch_recombine_magnetic_rows(const RecombParams& p, int block, size_t lds, hipStream_t st);
+// whether its sums over several passes are in LDS (those of one configuration each: in registers)
+inline bool magnetic_rows_lds_sums(int M, int mc) { return M > mc && mc > 1; }
 // float2 elements of its LDS for mc configurations a pass, `rows` staged rows (a block's rows, or
 // min(rows, qmod2)), site chunks of csites, S sites, nclass classes, `sums` floats for the sums of
 // several passes

@@ -1322,9 +1322,11 @@ __device__ __forceinline__ void cmac(float2& acc, float2 a, float2 b) {
 // NCT: the number of r3 classes when the classes are summed per residue of H3 mod q
 // (then at most kMagRowsMaxClasses, and the residue sums unroll over it), else 0.
 // MC: configurations a pass takes (their sums side by side in LDS, a voxel's |Q|, form factor and
-// projection worked out once for them); more than MC are added up over the passes in LDS, and
-// only then do planes not share a block.
-template <int MC, int NCT, class PT>
+// projection worked out once for them).  Several passes add up in LDS, or, REGS, those of one
+// configuration in the thread's registers, one sum per row, picked by its number (17 configurations,
+// 24^3: 16 sites on quarters 213 us in registers and 227 in LDS, 8 sites in general positions, 7 rows,
+// 448 and 585).  Planes share a block only where one pass takes all configurations.
+template <int MC, int NCT, bool REGS, class PT>
 __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
 {
     extern __shared__ float2 smem[];
@@ -1386,9 +1388,12 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
     }
     const size_t plane = (size_t)P.cnt[1] * P.opitch;
     const size_t cstride = (size_t)n1 * n2 * SFnh;
+    float I[REGS ? kMagRowsMaxRows : 1];
+#pragma unroll
+    for (int r = 0; r < (REGS ? kMagRowsMaxRows : 1); ++r) I[r] = 0.f;
     for (int m0 = 0; m0 < P.M; m0 += MC) {
         const int mc = MC == 1 ? 1 : min(MC, P.M - m0);
-        const bool last = MC == 1 ? m0 + 1 >= P.M : m0 + MC >= P.M;
+        const bool last = m0 + MC >= P.M;
         __syncthreads();
         for (int idx = threadIdx.x; idx < MC * Dm; idx += blockDim.x) D[idx] = make_float2(0.f, 0.f);
         for (int s0 = 0; s0 < S; s0 += P.csites) {
@@ -1546,6 +1551,12 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
                 }
                 val = q2 > 0.f ? val : 0.f;
                 // (several passes: one plane per block, the sums so far in the thread's own places)
+                if constexpr (REGS) {
+#pragma unroll
+                    for (int rr = 0; rr < kMagRowsMaxRows; ++rr)
+                        if (rr == r) I[rr] += val;
+                    continue;
+                }
                 if (m0 > 0) val += Iacc[r * cnt3 + i3];
                 if (!last) { Iacc[r * cnt3 + i3] = val; continue; }
                 const int i2 = G2 - P.g0[1];
@@ -1555,15 +1566,30 @@ __device__ __forceinline__ void recombine_magnetic_rows_body(PT P, const int bx)
             }
         }
     }
+    if constexpr (REGS) {
+        float* const orow0 = P.out + P.ooff + (size_t)w.i1 * plane + i3;
+        float* const mrow0 = P.out + P.ooff + (size_t)(P.cnt[0] - 1 - w.i1) * plane + (P.cnt[2] - 1 - i3);
+        if (active) {
+#pragma unroll
+            for (int r = 0; r < kMagRowsMaxRows; ++r) {
+                if (r < rows) {
+                    const int i2 = w.k2 + n2 * (w.H2lo + w.h2a + r) - P.g0[1];
+                    const float o = I[r] * P.scale;
+                    orow0[(size_t)i2 * P.opitch] = o;
+                    if (w.mirror) mrow0[(size_t)(P.cnt[1] - 1 - i2) * P.opitch] = o;
+                }
+            }
+        }
+    }
 }
 
-template <int MC, int NCT>
-__global__ __launch_bounds__(kMagRowsMaxThreads) void k_recombine_magnetic_rows(RecombParams P) { recombine_magnetic_rows_body<MC, NCT, RecombParams>(P, blockIdx.x); }
-template <int MC, int NCT>
+template <int MC, int NCT, bool REGS>
+__global__ __launch_bounds__(kMagRowsMaxThreads) void k_recombine_magnetic_rows(RecombParams P) { recombine_magnetic_rows_body<MC, NCT, REGS, RecombParams>(P, blockIdx.x); }
+template <int MC, int NCT, bool REGS>
 __global__ __launch_bounds__(kMagRowsMaxThreads) void k_recombine_magnetic_rows_merged(const RecombParams* __restrict__ tab, const Slot* __restrict__ slots)
 {
     int d, bx;
-    if (slot_of(slots, d, bx)) recombine_magnetic_rows_body<MC, NCT, const RecombParams&>(tab[d], bx);
+    if (slot_of(slots, d, bx)) recombine_magnetic_rows_body<MC, NCT, REGS, const RecombParams&>(tab[d], bx);
 }
 
 // Magnetic sites with Debye-Waller factors, rows form: blocks and threads as above (one plane), but
@@ -1725,27 +1751,27 @@ static hipError_t launch_mag_dw_rows(const RecombParams& p, int block, size_t ld
     return dispatch(k_recombine_magnetic_dw_rows<MC>, k_recombine_magnetic_dw_rows_merged<MC>, p.nwork, block, lds, st, p);
 }
 
-template <int MC, int NCT>
+template <int MC, int NCT, bool REGS>
 static hipError_t launch_mag_rows_v(const RecombParams& p, int block, size_t lds, hipStream_t st)
 {
-    hipError_t e = set_lds(k_recombine_magnetic_rows<MC, NCT>, lds);
+    hipError_t e = set_lds(k_recombine_magnetic_rows<MC, NCT, REGS>, lds);
     if (e != hipSuccess) return e;
-    return dispatch(k_recombine_magnetic_rows<MC, NCT>, k_recombine_magnetic_rows_merged<MC, NCT>, p.nwork, block,
+    return dispatch(k_recombine_magnetic_rows<MC, NCT, REGS>, k_recombine_magnetic_rows_merged<MC, NCT, REGS>, p.nwork, block,
                     lds, st, p);
 }
 
-template <int MC>
+template <int MC, bool REGS>
 static hipError_t launch_mag_rows(const RecombParams& p, int block, size_t lds, hipStream_t st)
 {
     // residue sums for up to four classes (the unrolled sums keep the block's q x NC
     // phases in registers); more classes, or no residue grid, take level C per class,
     // which is exact for any q
-    if (p.qmod <= 0 || p.nclass > 4) return launch_mag_rows_v<MC, 0>(p, block, lds, st);
+    if (p.qmod <= 0 || p.nclass > 4) return launch_mag_rows_v<MC, 0, REGS>(p, block, lds, st);
     switch (p.nclass) {
-        case 1: return launch_mag_rows_v<MC, 1>(p, block, lds, st);
-        case 2: return launch_mag_rows_v<MC, 2>(p, block, lds, st);
-        case 3: return launch_mag_rows_v<MC, 3>(p, block, lds, st);
-        default: return launch_mag_rows_v<MC, 4>(p, block, lds, st);
+        case 1: return launch_mag_rows_v<MC, 1, REGS>(p, block, lds, st);
+        case 2: return launch_mag_rows_v<MC, 2, REGS>(p, block, lds, st);
+        case 3: return launch_mag_rows_v<MC, 3, REGS>(p, block, lds, st);
+        default: return launch_mag_rows_v<MC, 4, REGS>(p, block, lds, st);
     }
 }
 
@@ -1764,9 +1790,9 @@ hipError_t launch_recombine_magnetic_rows(const RecombParams& p, int block, size
     if (p.qmod > 0 && (p.qmod > p.nclass || p.nclass > kMagRowsMaxClasses)) return hipErrorInvalidValue;
     if (p.M > p.mg && p.qmod1 > 0) return hipErrorInvalidValue;   // grouped planes: one pass
     switch (p.mg) {
-        case 1: return launch_mag_rows<1>(p, block, lds, st);
-        case 2: return launch_mag_rows<2>(p, block, lds, st);
-        case 4: return launch_mag_rows<4>(p, block, lds, st);
+        case 1: return p.M > 1 ? launch_mag_rows<1, true>(p, block, lds, st) : launch_mag_rows<1, false>(p, block, lds, st);
+        case 2: return launch_mag_rows<2, false>(p, block, lds, st);
+        case 4: return launch_mag_rows<4, false>(p, block, lds, st);
         default: return hipErrorInvalidValue;
     }
 }
