@@ -1839,7 +1839,7 @@ __device__ __forceinline__ int floordiv_exact(int a, int b, float rb)
     return q;
 }
 
-template <class PT>
+template <bool ONE, class PT>
 __device__ __forceinline__ void recombine_direct_body(PT P, const int bx)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1872,7 +1872,7 @@ __device__ __forceinline__ void recombine_direct_body(PT P, const int bx)
     const int k20 = __builtin_amdgcn_readfirstlane(P.g0[1] - n2 * floordiv_exact(P.g0[1], n2, __builtin_amdgcn_rcpf((float)n2)));
     auto* op = gptr(P.out) + P.ooff + (size_t)r0 * P.opitch + i3;
     const float cj = half ? -1.f : 1.f;
-    if (P.S == 1) {
+    if constexpr (ONE) {
         // one site: the phase has modulus b, so |F_m|^2 = b^2 |X_m(k)|^2 exactly.  Rows go
         // in groups: the group's spectra offsets first (a direct-form spectrum has fewer than
         // 2^32 elements), then all its loads of a configuration in flight at once
@@ -1950,14 +1950,13 @@ __device__ __forceinline__ void recombine_direct_body(PT P, const int bx)
     }
 }
 
-__global__ __launch_bounds__(kDirectThreads) void k_recombine_direct(RecombParams P)
-{
-    recombine_direct_body<RecombParams>(P, blockIdx.x);
-}
+template <bool ONE>
+__global__ __launch_bounds__(kDirectThreads) void k_recombine_direct(RecombParams P) { recombine_direct_body<ONE, RecombParams>(P, blockIdx.x); }
+template <bool ONE>
 __global__ __launch_bounds__(kDirectThreads) void k_recombine_direct_merged(const RecombParams* __restrict__ tab, const Slot* __restrict__ slots)
 {
     int d, bx;
-    if (slot_of(slots, d, bx)) recombine_direct_body<const RecombParams&>(tab[d], bx);
+    if (slot_of(slots, d, bx)) recombine_direct_body<ONE, const RecombParams&>(tab[d], bx);
 }
 
 // One site (Taylor order 0): the site phase has modulus b, so I(G) = scale b^2 sum_m |X_m(k)|^2
@@ -2124,8 +2123,9 @@ hipError_t launch_recombine_direct(const RecombParams& p, hipStream_t st)
     if (rows * (unsigned long long)p.cnt[2] >= (1ULL << 32)) return hipErrorInvalidValue;
     if (p.S == 1 && rows < (1ULL << 31) && tiles_pay(p)) return launch_recombine_tiles(p, st);
     const unsigned long long waves = (rows + kDirectRows - 1) / kDirectRows * ((p.cnt[2] + 63) / 64);
-    return dispatch(k_recombine_direct, k_recombine_direct_merged, (unsigned)((waves + kDirectWaves - 1) / kDirectWaves),
-                    kDirectThreads, 0, st, p);
+    const unsigned grid = (unsigned)((waves + kDirectWaves - 1) / kDirectWaves);
+    return p.S == 1 ? dispatch(k_recombine_direct<true>, k_recombine_direct_merged<true>, grid, kDirectThreads, 0, st, p)
+                    : dispatch(k_recombine_direct<false>, k_recombine_direct_merged<false>, grid, kDirectThreads, 0, st, p);
 }
 
 // instantiated in recombine_o*.hip
