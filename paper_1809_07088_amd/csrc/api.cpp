@@ -583,47 +583,89 @@ bool parity_applies(dsx_model m)
 }
 
 // Configurations a block of the sites form takes side by side: what 512 threads and 64 KB of
-// level-A buffers hold (bs float2 elements a plane and configuration).
-int sites_configs(int M, int npl, int gthreads, int bs)
+// level-A buffers hold (bs float2 elements a plane and configuration), and no more than fill the
+// chip: once the launch of `blocks` blocks has as many waves as fit at once, the groups of a block
+// only wait for each other.  Side by side against one at a time over orders 0 to 5 and 1 to 16
+// sites: 0.5 to 0.8 of the time on grids of 10^3 cells (30 000 threads), 0.85 at 130 000, 0.95 to 1.1
+// at 170 000 to 390 000, 1.2 to 1.3 above.  Blocks whose waves leave over a sixth of a SIMD's empty
+// are passed by (groups of three waves, twice: 14^3, |h| <= 5, one site of order 2, two
+// configurations 27 us, one at a time 18).
+int sites_configs(int M, int order, int hc, int npl, int gthreads, int bs, long long blocks)
 {
-    int mg = std::max(1, std::min(M, 512 / (npl * gthreads)));
-    while (mg > 1 && (size_t)mg * npl * bs * sizeof(float2) > 64 * 1024) --mg;
-    return mg;
+    // waves per SIMD of the kernel, by its registers
+    const int occ = hc <= 4 ? (order <= 2 ? 7 : 6) : hc <= 8 ? (order == 0 ? 6 : order <= 5 ? 5 : 4) : 4;
+    const long long waves = blocks * npl * gthreads / 64, fill = 1024LL * occ * (hc <= 8 ? 3 : 2) / 2;
+    const int most = std::max(1, std::min(M, 512 / (npl * gthreads)));
+    for (int mg = (int)std::min<long long>(most, std::max<long long>(1, (fill + waves - 1) / std::max<long long>(1, waves))); mg > 1; --mg) {
+        const int w = npl * mg * gthreads / 64;
+        if (waves * mg > fill && 6 * (4 * occ / w * w) < 5 * 4 * occ) continue;
+        if ((size_t)mg * npl * bs * sizeof(float2) <= 64 * 1024) return mg;
+    }
+    return 1;
 }
 
-// Block shape of the sites form on a box (t.hc, t.nchunk3, t.nact3 are set): two planes per
-// block where a column has more than one, halves of the k3 range when they still are 8 or more
-// long, the sites of a chunk within 48 KB of LDS (three blocks per CU; a smaller slice where one
-// site alone exceeds 96 KB), rows for at most 320 items a group, and, with the threads that
-// leaves over, several configurations at a time.
+// Block shape of the sites form on a box (t.hc, t.nchunk3, t.nact3 are set): halves of the k3 range
+// when they still are 8 or more long, the sites of a chunk within 48 KB of LDS (three blocks per CU;
+// a smaller slice where one site alone exceeds 96 KB), rows for at most 320 items a group, and,
+// with the threads that leaves over, several configurations at a time.
+// Two planes per block share level A.  One plane a block where odd numbers of planes leave a fifth
+// of the second ones out and level A is short (20^3 cells, |h| <= 3, two sites of order 2, 16
+// configurations 85 us with two planes, 59 with one; six of order 5, two configurations of 27^3 107
+// and 114) or two fifths whatever it is (47^3, |h| <= 1, order 1, 9 configurations 63 and 42), but
+// for blocks that would be single waves; and where two groups of three waves would leave a quarter of the
+// chip's waves empty while the sites fit 24 KB (27^3, |h| <= 5, two sites of order 2 585 and 367; 14^3
+// six sites of order 8, 30 KB, 133 and 161).
 void plan_sites_form(dsx_model m, const Box& bx, int maxH2, DeviceTables& t)
 {
     const int S = m->S, qp = n_pairs(m->order) | 1;
-    int maxH1 = 0;
-    for (int k = 0; k < m->n[0]; ++k) maxH1 = std::max(maxH1, hcount(k, m->n[0], bx.g0[0], bx.cnt[0]));
-    t.npl_s = maxH1 > 1 ? 2 : 1;
-    t.slices_s = t.nact3 >= 16 ? 2 : 1;
-    auto per_site = [&](int npl, int n3s) { return sizeof(float2) * (size_t)npl * n3s * qp; };
-    for (;;) {
-        t.n3s_s = (t.nact3 + t.slices_s - 1) / t.slices_s;
-        const bool fits = per_site(t.npl_s, t.n3s_s) <= 96 * 1024 && t.n3s_s * t.nchunk3 <= 512 / t.npl_s;
-        if (fits || (t.slices_s == 8 && t.npl_s == 1)) break;
-        if (t.slices_s < 8) t.slices_s *= 2;
-        else t.npl_s = 1;
+    std::vector<int> planes(m->n[0], 0);             // computed planes of each k1
+    const bool friedel = symmetric_box(bx);
+    int total = 0, maxH1 = 0;
+    for (int i = 0; i < bx.cnt[0]; ++i) {
+        const long G1 = bx.g0[0] + i;
+        if (friedel && G1 > 0) continue;
+        const int k1 = (int)(G1 - (long)m->n[0] * floordiv_l(G1, m->n[0]));
+        maxH1 = std::max(maxH1, ++planes[k1]);
+        ++total;
     }
-    t.slices_s = (t.nact3 + t.n3s_s - 1) / t.n3s_s;
-    t.csites_s = (int)std::max<size_t>(1, std::min<size_t>(S, 48 * 1024 / per_site(t.npl_s, t.n3s_s)));
-    // even chunks
-    const int nch = (S + t.csites_s - 1) / t.csites_s;
-    t.csites_s = (S + nch - 1) / nch;
-    // (a group has a thread for every item: 256 threads of each of two planes, 512 of one)
-    const int per_row = t.n3s_s * t.nchunk3, maxg = 512 / t.npl_s / 64 * 64;
-    int rows = std::max(1, std::min(std::min(320, maxg) / per_row, 2048 / S));
-    rows = std::min(rows, std::max(1, maxH2));
-    const int parts = (std::max(1, maxH2) + rows - 1) / rows;
-    t.rows_s = (std::max(1, maxH2) + parts - 1) / parts;
-    t.gthreads_s = std::min(maxg, (t.rows_s * per_row + 63) / 64 * 64);
-    t.mg_s = m->M > 1 ? sites_configs(m->M, t.npl_s, t.gthreads_s, t.csites_s * t.n3s_s * qp) : 1;
+    int pairs = 0;
+    for (int c : planes) pairs += (c + 1) / 2;
+    long long blocks = 0;
+    auto shape = [&](int npl) {
+        t.npl_s = npl;
+        t.slices_s = t.nact3 >= 16 ? 2 : 1;
+        auto per_site = [&](int np, int n3s) { return sizeof(float2) * (size_t)np * n3s * qp; };
+        for (;;) {
+            t.n3s_s = (t.nact3 + t.slices_s - 1) / t.slices_s;
+            const bool fits = per_site(t.npl_s, t.n3s_s) <= 96 * 1024 && t.n3s_s * t.nchunk3 <= 512 / t.npl_s;
+            if (fits || (t.slices_s == 8 && t.npl_s == 1)) break;
+            if (t.slices_s < 8) t.slices_s *= 2;
+            else t.npl_s = 1;
+        }
+        t.slices_s = (t.nact3 + t.n3s_s - 1) / t.n3s_s;
+        t.csites_s = (int)std::max<size_t>(1, std::min<size_t>(S, 48 * 1024 / per_site(t.npl_s, t.n3s_s)));
+        // even chunks
+        const int nch = (S + t.csites_s - 1) / t.csites_s;
+        t.csites_s = (S + nch - 1) / nch;
+        // (a group has a thread for every item: 256 threads of each of two planes, 512 of one)
+        const int per_row = t.n3s_s * t.nchunk3, maxg = 512 / t.npl_s / 64 * 64;
+        int rows = std::max(1, std::min(std::min(320, maxg) / per_row, 2048 / S));
+        rows = std::min(rows, std::max(1, maxH2));
+        const int parts = (std::max(1, maxH2) + rows - 1) / rows;
+        t.rows_s = (std::max(1, maxH2) + parts - 1) / parts;
+        t.gthreads_s = std::min(maxg, (t.rows_s * per_row + 63) / 64 * 64);
+        blocks = 0;
+        for (int c : planes) blocks += (c + t.npl_s - 1) / t.npl_s;
+        blocks *= (long long)std::min(m->n[1], bx.cnt[1]) * parts * t.slices_s;
+    };
+    shape(maxH1 > 1 ? 2 : 1);
+    if (t.npl_s == 2) {
+        const double idle = 1.0 - 0.5 * total / std::max(1, pairs);
+        const bool odd = t.gthreads_s > 64 && (idle >= 0.4 || (idle >= 0.2 && S * n_pairs(m->order) <= 100));
+        const bool thirds = t.gthreads_s == 192 && blocks >= 500 && sizeof(float2) * (size_t)S * t.n3s_s * qp <= 24 * 1024;
+        if (odd || thirds) shape(1);
+    }
+    t.mg_s = m->M > 1 ? sites_configs(m->M, m->order, t.hc, t.npl_s, t.gthreads_s, t.csites_s * t.n3s_s * qp, blocks) : 1;
 }
 
 dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
@@ -1453,7 +1495,7 @@ dsx_status prune_plan(dsx_model m, const Box& bx, const RowMask& mask, LaunchPla
         // fewer rows a block: narrower groups, and more configurations side by side
         p.rows = rows;
         p.gthreads = std::min(p.gthreads, (rows * p.n3s * p.nchunk3 + 63) / 64 * 64);
-        p.mg = m->M > 1 ? sites_configs(m->M, p.npl, p.gthreads, p.bs_elems) : 1;
+        p.mg = m->M > 1 ? sites_configs(m->M, m->order, lp.hc, p.npl, p.gthreads, p.bs_elems, (long long)list.size()) : 1;
         lp.block = p.npl * p.mg * p.gthreads;
         lp.lds = sites_lds(m, p, lp.hc);
     }
