@@ -587,7 +587,8 @@ bool parity_applies(dsx_model m)
 // chip: once the launch of `blocks` blocks has as many waves as fit at once, the groups of a block
 // only wait for each other.  Side by side against one at a time over orders 0 to 5 and 1 to 16
 // sites: 0.5 to 0.8 of the time on grids of 10^3 cells (30 000 threads), 0.85 at 130 000, 0.95 to 1.1
-// at 170 000 to 390 000, 1.2 to 1.3 above.  Blocks whose waves leave over a sixth of a SIMD's empty
+// at 170 000 to 390 000, 1.2 to 1.3 above; half as much again where a row has eight repeats or
+// fewer (27^3, |h| <= 1, 16 configurations 0.69).  Blocks whose waves leave over a sixth of a SIMD's empty
 // are passed by (groups of three waves, twice: 14^3, |h| <= 5, one site of order 2, two
 // configurations 27 us, one at a time 18).
 int sites_configs(int M, int order, int hc, int npl, int gthreads, int bs, long long blocks)
