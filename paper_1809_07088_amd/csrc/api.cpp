@@ -304,11 +304,51 @@ void free_tables(DeviceTables& t)
 // Rows (G1, G2) of a box that are needed.
 struct RowMask {
     int lo[2], cnt[2];
-    std::vector<unsigned char> need;   // [cnt0][cnt1]
-    bool at(long G1, long G2) const
+    std::vector<unsigned char> need, any;   // [cnt0][cnt1]; [cnt0]: whether a G1 has one
+    // the row flags of a G1, null where it has none
+    const unsigned char* of(long G1) const
     {
-        const long a = G1 - lo[0], b = G2 - lo[1];
-        return a >= 0 && b >= 0 && a < cnt[0] && b < cnt[1] && need[(size_t)a * cnt[1] + b] != 0;
+        const long a = G1 - lo[0];
+        return a >= 0 && a < cnt[0] && any[a] ? &need[(size_t)a * cnt[1]] : nullptr;
+    }
+    bool at(const unsigned char* r, long G2) const
+    {
+        const long b = G2 - lo[1];
+        return r && b >= 0 && b < cnt[1] && r[b] != 0;
+    }
+    // every flag set also sets the w - 1 after it along both axes (in doubling steps); returns how
+    // many are set then
+    long long widen(int w)
+    {
+        const int c0 = cnt[0], c1 = cnt[1];
+        std::vector<unsigned char> r0(c1);
+        for (int i = 0; i < c0; ++i) {
+            unsigned char* r = &need[(size_t)i * c1];
+            for (int k = 1; k < w; ) {
+                const int d = std::min(k, w - k);
+                std::copy(r, r + c1, r0.begin());
+                for (int j = d; j < c1; ++j) r[j] |= r0[j - d];
+                k += d;
+            }
+        }
+        for (int k = 1; k < w; ) {
+            const int d = std::min(k, w - k);
+            for (int i = c0 - 1; i >= d; --i) {
+                unsigned char *r = &need[(size_t)i * c1], *e = &need[(size_t)(i - d) * c1];
+                for (int j = 0; j < c1; ++j) r[j] |= e[j];
+            }
+            k += d;
+        }
+        any.assign(c0, 0);
+        long long rows = 0;
+        for (int i = 0; i < c0; ++i) {
+            const unsigned char* r = &need[(size_t)i * c1];
+            int n = 0;
+            for (int j = 0; j < c1; ++j) n += r[j];
+            any[i] = n > 0;
+            rows += n;
+        }
+        return rows;
     }
 };
 
@@ -342,13 +382,18 @@ std::vector<int4> prune_work(const std::vector<int4>& its, const Box& bx, int n2
         for (int p = 0; p < np; ++p) {
             const long G1 = it.z + (long)p * step;
             const bool mir = (it.w >> (planes == 2 ? 24 + 2 * p : 24 + p)) & 1;
-            for (int h = h2a; h < h2b; ++h) {
+            const unsigned char *r = mask.of(G1), *rm = mir ? mask.of(-G1) : nullptr;
+            if (!r && !rm) continue;
+            auto needed = [&](int h) {
                 const long G2 = it.y + (long)n2 * (H2lo + h);
-                if (mask.at(G1, G2) || (mir && mask.at(-G1, -G2))) {
-                    a = std::min(a, h);
-                    b = std::max(b, h + 1);
-                }
-            }
+                return mask.at(r, G2) || mask.at(rm, -G2);
+            };
+            // (only what lies outside the span so far)
+            int f = h2a, l = h2b;
+            while (f < a && !needed(f)) ++f;
+            a = std::min(a, f);
+            while (l > b && !needed(l - 1)) --l;
+            b = std::max(b, l);
         }
         if (a >= b) continue;
         it.w = (it.w & ~0xffffff) | a | (b << 12);
@@ -2363,31 +2408,9 @@ dsx_status dsx_filter_points(dsx_model m, int32_t lanczos_m, int32_t mprime, int
         if (!fine) return fail(DSX_ERR_ARG, "points must be finite, |Q| <= 1e6");
         long lo[3], hi[3];
         for (int a = 0; a < 3; ++a) { lo[a] = floor_l(vmin[a]) - w + 1; hi[a] = floor_l(vmax[a]) + w; }
-        // the rows (G1, G2) the windows reach; on a plane or a line they are few of the box's
+        // (what the windows reach, before the box is made symmetric)
         RowMask mask;
         for (int a = 0; a < 2; ++a) { mask.lo[a] = (int)lo[a]; mask.cnt[a] = (int)(hi[a] - lo[a] + 1); }
-        bool use_mask = (long long)mask.cnt[0] * mask.cnt[1] <= (1LL << 22);
-        if (use_mask) {
-            const int c0 = mask.cnt[0], c1 = mask.cnt[1];
-            mask.need.assign((size_t)c0 * c1, 0);
-            for (int64_t i = 0; i < npts; ++i)      // the windows' first rows ...
-                mask.need[(size_t)(floor_l(q[3 * i]) - w + 1 - lo[0]) * c1 + (floor_l(q[3 * i + 1]) - w + 1 - lo[1])] = 1;
-            // ... then the 2 w of each, along axis 2 and along axis 1 (backwards: in place)
-            long long rows = 0;
-            for (int i = c0 - 1; i >= 0; --i) {
-                unsigned char* r = &mask.need[(size_t)i * c1];
-                for (int j = c1 - 1; j >= 0; --j)
-                    for (int d = 1; d < 2 * w && d <= j && !r[j]; ++d) r[j] = r[j - d];
-            }
-            for (int i = c0 - 1; i >= 0; --i)
-                for (int j = 0; j < c1; ++j) {
-                    unsigned char* r = &mask.need[(size_t)i * c1 + j];
-                    for (int d = 1; d < 2 * w && d <= i && !*r; ++d) *r = *(r - (size_t)d * c1);
-                    rows += *r;
-                }
-            // (a list of most rows is not worth the upload)
-            use_mask = rows * 4 < 3LL * c0 * c1;
-        }
         // a box nearly symmetric about G = 0 is made symmetric (at most ~10 % more volume):
         // the recombination then evaluates half of it (I(-G) = I(G))
         bool near_sym = true;
@@ -2431,6 +2454,25 @@ dsx_status dsx_filter_points(dsx_model m, int32_t lanczos_m, int32_t mprime, int
         std::vector<int4> cut;
         DrainStream drain{st};                      // `cut` and q stay alive until their copies have run
         if ((s = ensure_spectra(m, st, false)) != DSX_OK) return s;
+        // The rows (G1, G2) the windows reach, found while the device transforms: on a plane or a line
+        // they are few of the box's.  Finding them and cutting the work list takes the host about
+        // 1 ns a row and 10 us, evaluating them all takes the device a time as the terms of a row.  The
+        // line lies between both, from lines and planes in boxes of 900 to 270 000 rows, all rows
+        // against the windows': 24 x 24 x 16 cells, |h| <= 2.4, rows of 124 points, three sites of
+        // order 3, 5 configurations 128 and 100 us, six sites of one configuration 57 and 89;
+        // 128 x 128 x 4 cells, |h| <= 2, rows of four points of six sites 93 and 364; the (h h l) plane
+        // of 32 sites, 100 configurations over 10^3 cells, |h| <= 6, 1526 and 1230.
+        const double nrows = (double)mask.cnt[0] * mask.cnt[1];
+        const double terms = (double)bx.cnt[2] * m->M * m->S * (m->kind == DSX_MAGNETIC ? 3 : m->order + 1);
+        bool use_mask = nrows <= (double)(1 << 22) && nrows * (terms - 1600.0) >= 3e7;
+        if (use_mask) {
+            const int c0 = mask.cnt[0], c1 = mask.cnt[1];
+            mask.need.assign((size_t)c0 * c1, 0);
+            for (int64_t i = 0; i < npts; ++i)      // the windows' first rows, then the 2 w of each
+                mask.need[(size_t)(floor_l(q[3 * i]) - w + 1 - mask.lo[0]) * c1 + (floor_l(q[3 * i + 1]) - w + 1 - mask.lo[1])] = 1;
+            // (a list of most rows is not worth the upload)
+            use_mask = mask.widen(2 * w) * 4 < 3LL * c0 * c1;
+        }
         if ((s = run_box(m, bx, m->d_pts, dense_layout(bx), st, use_mask ? &mask : nullptr, &cut)) != DSX_OK) return s;
         HIPCHK(m, hipMemcpyAsync(m->d_q, q, (size_t)npts * 3 * sizeof(double), hipMemcpyHostToDevice, st));
         PointsParams pp{};

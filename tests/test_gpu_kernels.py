@@ -120,6 +120,38 @@ def test_points_cut_work_lists(shape, kind, S, M, order, basis):
     assert_parity(got, O.filtered_points(m, 2, Q, order if order and not magnetic else None))
 
 
+@pytest.mark.parametrize("shape", ["hhl", "line", "off"])
+@pytest.mark.parametrize("kind,S,M,order,basis", [("occ", 6, 20, 0, None), ("disp", 4, 4, 3, "fcc"), ("disp", 3, 6, 2, None),
+                                                  ("mag", 4, 6, 0, "fcc"), ("mag", 2, 10, 0, None), ("mag", 2, 10, 2, None)])
+def test_points_cut_work_lists_of_wide_boxes(shape, kind, S, M, order, basis):
+    """The same over boxes of 17 000 rows, which hold enough terms that the lists are worth cutting,
+    against the call whose points reach every row of the box."""
+    import torch
+    from tests.helpers import to_dsx
+    magnetic = kind == "mag"
+    m = synth.random_model(2350 + S + M + order, n=(6, 5, 8), S=S, M=M, order=order, kind=synth.MAGNETIC if magnetic else synth.NUCLEAR,
+                           with_occ=kind == "occ", with_disp=order > 0, mag_order=order if magnetic else 0, sigma=0.03,
+                           cell=[6.0, 6.0, 6.0, 90.0, 90.0, 90.0] if magnetic else None)
+    if basis == "fcc":
+        m.frac = synth.FCC_BASIS[:S].copy()
+    t = np.linspace(-12.1, 12.1, 9)
+    h, l = (v.ravel() for v in np.meshgrid(t, t / 3, indexing="ij"))
+    Q = {"hhl": np.stack([6 * h, 5 * h, 8 * l], -1), "line": np.stack([6 * t, 5 * t + 0.5, 8 * t / 3], -1),
+         "off": np.stack([6 * h + 131.25, -5 * h - 20.5, 8 * l], -1)}[shape]
+    say(f"points over a wide box {shape} {kind} S={S} M={M} order={order}")
+    d = to_dsx(m)
+    step = [np.arange(*np.floor(Q[:, a])[[0, -1]][np.argsort(Q[[0, -1], a])], 3) + 0.5 for a in (0, 1)]
+    cover = np.stack([v.ravel() for v in np.meshgrid(*step, Q[:1, 2], indexing="ij")], -1)
+    got = []
+    for q in (Q, np.concatenate([Q, cover])):
+        out = torch.full((len(q),), float("nan"), dtype=torch.float32, device="cuda")
+        d.filter_points(2, q, out)
+        got.append(out.cpu().numpy())
+    d.close()
+    assert np.isfinite(got[1]).all()
+    assert_parity(got[0], got[1][:len(Q)])
+
+
 # ------------------------------------------------------------------ Bragg points of ensembles
 @pytest.mark.parametrize("S,M,order", [(20, 64, 0), (3, 65, 0), (17, 130, 0), (2, 40, 2)])
 def test_bragg_points_of_ensembles(S, M, order):
