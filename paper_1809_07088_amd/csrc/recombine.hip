@@ -2094,9 +2094,12 @@ static hipError_t launch_recombine_tiles(const RecombParams& p, hipStream_t st)
     return dispatch(k_recombine_tiles, k_recombine_tiles_merged, (unsigned)((rows + r - 1) / r), kTileThreads, lds, st, q);
 }
 
-// One site, one or two configurations: tiles against the direct form (more configurations always
-// take tiles).  A tile forms n3 values a row and writes c2 of them, so it pays by the repeats
-// c2 / n3, and more where rows start on 16 bytes.  Measured, direct and tiles, one configuration:
+// One site: tiles against the direct form.  A tile forms n3 values a row and writes c2 of them, so
+// it pays by the repeats c2 / n3, more where rows start on 16 bytes and with more configurations,
+// which it adds up before any value is written.  Measured, direct and tiles, one configuration:
+//   under 2      all values of a row for few of them, unless rows are so few or short that either
+//                form waits for memory: 20 x 26 x 14 cells, rows of 17 points, 15 600 values formed
+//                1.1, 60 000 1.9 times the direct form's time; 24^2 x 2 cells 0.8; 48 x 48 x 24 2.1
 //   2 repeats    32^3 cells 7.0 and 12.0 us, 64^3 8.4 and 14.1, 100^3 15.9 and 18.5; only rows
 //                under 16 values, which leave most lanes of the direct form idle, gain (100 x 100 x 2
 //                at 4 repeats 14.7 and 6.9)
@@ -2106,11 +2109,19 @@ static hipError_t launch_recombine_tiles(const RecombParams& p, hipStream_t st)
 //   6 repeats    rows on 16 bytes: 24^3 10.1 and 8.7, 48^3 29.2 and 21.8; others: 20^3 8.2 and 9.2,
 //                31^3 13.9 and 13.3, 48^3 30.4 and 28.2
 //   8 and more   others: 16^3 9.7 and 9.5, 20^3 11.6 and 10.4, 16^3 at 16 repeats 25.9 and 20.4
+// Three to seven configurations, five of them: 2 repeats 12^3 10.0 and 6.9, 24^3 10.3 and 18.1,
+// 48^3 11.7 and 27.3, 100^3 34.4 and 33.5; 4 repeats 24^3 12.1 and 15.6, 48^3 32.4 and 19.1; 6 repeats
+// 24^3 18.4 and 12.8.  Eight: 2 repeats 24^3 13.0 and 11.9, 48^3 14.5 and 16.3, 64^3 22.5 and 17.8.
+// Twelve: 24^3 16.6 and 7.6, 64^3 30.4 and 25.2.
 static bool tiles_pay(const RecombParams& p)
 {
     const int n3 = p.n3, c2 = p.cnt[2];
-    if (p.M > 2 || c2 < 16) return true;
-    const long long vox = (long long)p.planes * p.cnt[1] * c2;
+    const long long rows = (long long)p.planes * p.cnt[1], vox = rows * c2;
+    if (p.M >= 12) return true;
+    if (p.M >= 8) return c2 >= 3 * n3 || n3 <= 3 * p.M || vox >= (1 << 20);
+    if (c2 < (p.M > 2 ? 3 : 2) * n3) return n3 <= 6 || rows * n3 <= 24000;
+    if (p.M > 2) return c2 >= 6 * n3 || n3 <= 8 || vox >= (1 << 20);
+    if (c2 < 16) return true;
     if (p.opitch % 4 == 0) return c2 >= 6 * n3 || (c2 >= 4 * n3 && (n3 <= 16 || vox >= (4 << 20)));
     return (c2 >= 8 * n3 && vox >= (1 << 20)) || (c2 >= 4 * n3 && vox >= (6 << 20));
 }

@@ -434,3 +434,23 @@ def test_one_site_tiles_or_voxels(n, g0, count, M):
     m.g0, m.count = g0, count
     say(f"one site n={n} M={M} box={g0}+{count}")
     sampled_parity(m)
+
+
+@pytest.mark.parametrize("n,g0,count", [((20, 26, 14), (-40, -52, -2), (81, 105, 5)), ((20, 26, 14), (-40, -52, 3), (80, 105, 17)),
+                                        ((12, 13, 40), (-12, -13, -40), (25, 27, 81)), ((25, 24, 24), (-25, -24, -48), (51, 49, 97)),
+                                        ((9, 11, 24), (-9, -22, -72), (19, 45, 145)), ((30, 31, 7), (-30, -62, -2), (61, 125, 5))])
+@pytest.mark.parametrize("M,b", [(1, 1.0), (2, 1.0), (3, 1.0), (5, 1e22), (8, 1.0), (12, 1.0), (3, np.inf), (8, 1e160)])
+def test_one_site_ensembles_tiles_or_voxels(n, g0, count, M, b):
+    """The same for ensembles and for boxes thinner than the supercell, with a weight whose square
+    leaves float32, and with weights past it (which leave no value)."""
+    m = synth.random_model(3900 + sum(n) + M, n=n, S=1, M=M, order=0, with_disp=False)
+    m.b[:] = b
+    m.g0, m.count = g0, count
+    if b == 1e22:
+        m.norm_N = 1e25
+        m.occ = (m.occ - 0.5) * np.float32(1e-5)
+    say(f"one site n={n} M={M} b={b} box={g0}+{count}")
+    if b in (np.inf, 1e160):
+        assert np.all(np.isnan(gpu_intensity(m)))
+    else:
+        sampled_parity(m, most=1500)
