@@ -2692,9 +2692,12 @@ hipError_t launch_bragg(const BraggParams& p, int order, hipStream_t st)
     if (p.kind == 1) {
         return dispatch(k_bragg_magnetic, k_bragg_magnetic_merged, (total + 3) / 4, 256, 0, st, p);
     }
-    // (one lane per H walks every configuration and site in turn, and needs some 16k points of
-    // H to fill the chip with waves)
-    if (order == 0 && p.S <= kBraggLaneSites && (total >= 16384 || !bragg_by_configs(p)))
+    // (one lane per H walks every configuration and site in turn, 0.04 us a term and 0.08 a
+    // configuration, and needs some 16k points of H to fill the chip with waves; the ensemble form
+    // takes 1.6 us per 1000 points.  17^3 points, lanes and ensemble: one site, 16 configurations 7.2
+    // and 14.6 us, 64 13.1 and 14.5, 100 17.6 and 15.1; eight sites, 16 11.6 and 14.6, 30 15.6 and 14.4)
+    if (order == 0 && p.S <= kBraggLaneSites &&
+        (total >= 16384 || !bragg_by_configs(p) || 25LL * p.M * (p.S + 2) < total + 500))
         return dispatch(k_bragg_lanes, k_bragg_lanes_merged, (total + 63) / 64, 64, 0, st, p);
     if (bragg_by_configs(p)) return dispatch(k_bragg_ensemble, k_bragg_ensemble_merged, total, 64, 0, st, p);
     switch (order) {

@@ -164,6 +164,17 @@ def test_bragg_points_of_ensembles(S, M, order):
     assert_parity(I.reshape(-1), O.intensity(m, G, order if order else None))
 
 
+@pytest.mark.parametrize("S,M", [(1, 16), (2, 17), (1, 70), (5, 16)])
+def test_many_bragg_points_of_ensembles(S, M):
+    """Boxes of 1331 Bragg points: lanes over the points for few terms, else over the configurations."""
+    m = synth.random_model(2450 + S + M, n=(2, 3, 2), S=S, M=M, order=0, with_occ=True, with_disp=False)
+    m.g0, m.count = (-10, -15, -10), (21, 31, 21)
+    say(f"many Bragg points of an ensemble S={S} M={M}")
+    I = gpu_intensity(m).reshape(m.count)[::2, ::3, ::2]
+    G = O.grid_points(m.g0, m.count).reshape(m.count + (3,))[::2, ::3, ::2].reshape(-1, 3)
+    assert_parity(I.reshape(-1), O.intensity(m, G, None))
+
+
 # ------------------------------------------------------------------ one site: tiled rows
 @pytest.mark.parametrize("n,M", [((3, 4, 5), 1), ((12, 5, 7), 3), ((2, 3, 31), 70), ((9, 8, 64), 2), ((1, 2, 200), 1)])
 @pytest.mark.parametrize("box", ["symmetric", "offset", "short"])
