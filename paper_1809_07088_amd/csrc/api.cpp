@@ -289,6 +289,7 @@ struct DeviceTables {
     int ks3 = 0, nact3 = 0;    // the k3 with points in the box: nact3 of them, cyclically from ks3
     int4* work_mr = nullptr;   // magnetic models: blocks of the row-staged form (null: not used)
     int nwork_mr = 0, rows_mr = 0, csites_mr = 0, qmod_mr = 0, qmod2_mr = 0, qmod1_mr = 0, mc_mr = 1;
+    bool sums_mr = false;
     // the lists in column order (before they are dealt to the XCDs), to cut them down to the
     // rows a point list needs
     std::vector<int4> h_work, h_work2, h_work3, h_work_s, h_work_mr;
@@ -849,8 +850,11 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
         // 25 KB 173 and 222; 16 sites 12^3 in 31 KB 122 and 132.  Places that idle in the last pass,
         // and columns cut into parts, undo the gain (6 sites 12^3, M = 3: one a pass 45 us, two 47; 5
         // sites 27^3, M = 2: 31 and 43), as do residue rows that no longer fit (12 sites on thirds,
-        // 16^3, M = 10: one a pass 205, four 446).
+        // 16^3, M = 10: one a pass 205, four 446).  All in one pass, one and all: 16 sites on quarters,
+        // M = 2, |h| <= 2, 8^3 in one site chunk 30 and 27, 24^3 in two 34 and 39; on halves, whose planes
+        // share the block, 32^3, |h| <= 3, 76 and 48, M = 4 131 and 80.
         const int most = std::min(kMagRowsMaxRows, std::max(1, maxH2));
+        const long long columns = (long long)(friedel ? (bx.cnt[0] + 1) / 2 : bx.cnt[0]) * std::min(n2, bx.cnt[1]);
         for (int mc : {4, 2, 1}) {
             const int idle = (m->M + mc - 1) / mc * mc - m->M, places = m->M + idle;
             if (mc > 1 && (mc / 2 >= m->M || 8 * idle > 3 * places)) continue;
@@ -862,7 +866,14 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
             // (every row takes its sums over the passes, staged or not)
             const size_t fixed = magnetic_rows_lds_elems(mc, 0, cs, S, NC, n3, t.nH3span, 0);
             const size_t per_row = magnetic_rows_lds_elems(mc, 1, 0, S, NC, n3, 0, 0);
-            const size_t per_sum = magnetic_rows_lds_sums(m->M, mc) ? (size_t)(bx.cnt[2] + 1) / 2 : 0;
+            const size_t sums = (size_t)(bx.cnt[2] + 1) / 2;
+            // the sums over several passes of one configuration: in registers, but in LDS for large
+            // launches of residue rows (two passes over 40^3, 16 sites on quarters, |h| <= 3, 4840 blocks
+            // 151 us in registers and 136 in LDS, three passes on halves, |h| <= 2, 3240 blocks
+            // 126 and 98; 28^3, |h| <= 3, 2380 blocks, nine passes 212 and 226)
+            const bool lds_sums = passes && (mc > 1 || (q2 > 0 && columns >= 3000 &&
+                                                        fixed + std::min(q2, most) * per_row + most * sums <= budget));
+            const size_t per_sum = lds_sums ? sums : 0;
             // residue rows: every row of a column in one block when q2 staged rows fit; else the
             // rows are staged one by one, as many as fit, in even parts
             int qm2 = 0, rows = 0;
@@ -875,11 +886,15 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
                 rows = 1;
             }
             if (rows < 1 || (mc > 1 && (rows < std::min(most, 4) || (q2 > 0 && qm2 == 0)))) continue;
+            const long long blocks = columns * ((std::max(1, maxH2) + rows - 1) / rows);
             if (mc > 1) {
                 const size_t lds = sizeof(float2) * (fixed + (qm2 ? std::min(rows, qm2) : rows) * per_row + rows * per_sum);
                 const double level_c = (double)most * bx.cnt[2] / (3.0 * S * n3);
                 const bool idles = 4 * idle >= places;
-                const bool several = bx.cnt[2] >= 3 * n3 && level_c >= (idles ? 1.6 : 1.0) && !(idles && passes) &&
+                // (all of them in one pass: level A's sites too, where no more site chunks come of it, or
+                // where planes share the block, see below)
+                const bool whole = !passes && q1 > 0 && (cs == S || blocks >= 2048);
+                const bool several = bx.cnt[2] >= 3 * n3 && level_c >= (idles ? 1.6 : whole ? 0.0 : 1.0) && !(idles && passes) &&
                                      (rows == most || (!idles && (bx.cnt[2] >= 8 * n3 || n3 < 20)));
                 if (lds > 18 * 1024 && !(several && (mc == 2 || lds <= 30 * 1024 || level_c >= 2.0))) continue;
             }
@@ -887,11 +902,9 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
             // planes share a block where one pass takes all configurations, and for several of them
             // only where that leaves blocks enough (4 sites 8^3, M = 2, 320 blocks before: 23 us
             // shared, 16 not; 2 sites 32^3, 3072 blocks: 16 and 20)
-            const long long blocks = (long long)(friedel ? (bx.cnt[0] + 1) / 2 : bx.cnt[0]) * std::min(n2, bx.cnt[1]) *
-                                     ((std::max(1, maxH2) + rows - 1) / rows);
             t.qmod2_mr = qm2;
             t.qmod1_mr = passes || (mc > 1 && blocks < 2048) ? 0 : q1;
-            t.rows_mr = rows; t.csites_mr = cs; t.mc_mr = mc;
+            t.rows_mr = rows; t.csites_mr = cs; t.mc_mr = mc; t.sums_mr = lds_sums;
             break;
         }
     }
@@ -1227,10 +1240,11 @@ dsx_status plan_recombine(dsx_model m, const Box& bx, float* out, const Layout& 
         p.qmod = tb->qmod_mr;
         p.qmod2 = tb->qmod2_mr;
         p.qmod1 = tb->qmod1_mr;
+        p.lds_sums = tb->sums_mr;
         lp.block = std::max(64, (bx.cnt[2] + 63) / 64 * 64);
         const int staged = tb->qmod2_mr > 0 ? std::min(tb->rows_mr, tb->qmod2_mr) : tb->rows_mr;
         lp.lds = sizeof(float2) * magnetic_rows_lds_elems(p.mg, staged, tb->csites_mr, m->S, m->nclass, n3, tb->nH3span,
-                                                          magnetic_rows_lds_sums(m->M, p.mg) ? p.rows * bx.cnt[2] : 0);
+                                                          tb->sums_mr ? p.rows * bx.cnt[2] : 0);
         limit = lp.lds;
     }
     if (!mag) {

@@ -184,6 +184,7 @@ struct RecombParams {
     int32_t qmod2;          // > 0: every r_mu2 a multiple of 1/qmod2: rows whose H2 agree mod
                             // qmod2 have the same site phases, so levels B and the residue sums
                             // run on the first min(rows, qmod2) rows of a block only
+    int32_t lds_sums;       // magnetic rows: the sums over several passes in LDS, not in registers
     int32_t qmod1;          // > 0: every r_mu1 a multiple of 1/qmod1: G1 planes of one column whose
                             // H1 agree mod qmod1 have the same site phases; a work item then
                             // covers 1 + ((w >> 28) & 3) planes G1 + p qmod1 n1, plane p mirrored
@@ -349,8 +350,6 @@ constexpr int kMagRowsMaxThreads = 512;
 constexpr int kMagRowsMaxRows = 16;
 constexpr int kMagRowsMaxClasses = 8;   // the per-residue class sums need q <= nclass <= this
 hipError_t launch_recombine_magnetic_rows(const RecombParams& p, int block, size_t lds, hipStream_t st);
-// whether its sums over several passes are in LDS (those of one configuration each: in registers)
-inline bool magnetic_rows_lds_sums(int M, int mc) { return M > mc && mc > 1; }
 // float2 elements of its LDS for mc configurations a pass, `rows` staged rows (a block's rows, or
 // min(rows, qmod2)), site chunks of csites, S sites, nclass classes, `sums` floats for the sums of
 // several passes

@@ -10,13 +10,14 @@
 //                transforms them along axes 3 (real-to-complex, two real rows packed
 //                in one complex line) and 2, entirely in LDS.
 //  k_axis1_regs  transforms along axis 1 in place.
-// Both take edges n = A B with A, B <= 16: A (then B) points per thread in registers.
+// Both take edges n = A B with A, B <= 16, or A a prime up to 61 on axis 1 and up to 47 in
+// the planes (both edges of a plane then): A (then B) points per thread in registers.
 // Edges 8, 16 and 32 have kernels with the length fixed at compile time
-// (k_fft_planes_reg, k_fft_axis1_reg).  The remaining edges (a prime factor above 16,
-// or no such split) take k_fft_planes and k_fft_axis1: Stockham auto-sort passes in LDS
-// of radix 2, 3, 4, 5 and a direct DFT, one output per thread, for any other prime
-// (planned first, where it needs no twiddles); twiddles come from a float64-generated
-// table.
+// (k_fft_planes_reg, k_fft_axis1_reg).  The remaining edges (a larger prime factor, or no
+// such split, as 250 = 25 x 10) take k_fft_planes and k_fft_axis1: Stockham auto-sort
+// passes in LDS of radix 2, 3, 4, 5 and a direct DFT, one output per thread, for any other
+// prime (planned first, where it needs no twiddles); twiddles come from a
+// float64-generated table.
 #include <algorithm>
 #include <type_traits>
 

@@ -270,7 +270,7 @@ __global__ __launch_bounds__(512, 2) void k_lanczos_ring_merged(const LanczosPar
 // weights are fixed (in registers); along axis 2 it takes four consecutive output rows, whose
 // phases are the same for its whole wave; the values join a register ring of the last M2 planes,
 // from which the s output planes between two input planes are emitted.  The next plane is in
-// flight in registers meanwhile.  Bound by latency (three barriers per input plane) on small
+// flight in registers meanwhile.  Bound by latency (two barriers per input plane) on small
 // outputs and by the writes on large ones: 146 x 162 x 218 outputs at s = 2 took 100 us with the
 // generic kernel's divisions, LDS ring and four barriers, 19 us here.
 template <int M2, bool S1, class PT>

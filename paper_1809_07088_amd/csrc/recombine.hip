@@ -1788,9 +1788,10 @@ hipError_t launch_recombine_magnetic_rows(const RecombParams& p, int block, size
         }
     }
     if (p.qmod > 0 && (p.qmod > p.nclass || p.nclass > kMagRowsMaxClasses)) return hipErrorInvalidValue;
-    if (p.M > p.mg && p.qmod1 > 0) return hipErrorInvalidValue;   // grouped planes: one pass
+    if (p.M > p.mg && (p.qmod1 > 0 || (p.mg > 1 && !p.lds_sums))) return hipErrorInvalidValue;   // grouped planes: one pass
     switch (p.mg) {
-        case 1: return p.M > 1 ? launch_mag_rows<1, true>(p, block, lds, st) : launch_mag_rows<1, false>(p, block, lds, st);
+        case 1: return p.M > 1 && !p.lds_sums ? launch_mag_rows<1, true>(p, block, lds, st)
+                                              : launch_mag_rows<1, false>(p, block, lds, st);
         case 2: return launch_mag_rows<2, false>(p, block, lds, st);
         case 4: return launch_mag_rows<4, false>(p, block, lds, st);
         default: return hipErrorInvalidValue;

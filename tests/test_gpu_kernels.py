@@ -258,6 +258,19 @@ def test_magnetic_rows_staged_one_by_one(S, M, n):
     sampled_parity(m, None, 1500)
 
 
+@pytest.mark.parametrize("r,S,M", [(4, 16, 2), (4, 16, 3), (4, 16, 5), (2, 16, 3), (4, 8, 3), (2, 12, 2)])
+@pytest.mark.parametrize("box", ["symmetric", "offset"])
+def test_magnetic_rows_of_many_columns(r, S, M, box):
+    """Passes of one configuration over 3240 columns and more, whose sums are in LDS, and passes of
+    all configurations whose planes share a block; sites on quarters and halves."""
+    m = synth.random_model(4000 + S + M + r, n=(10, 40, 40), S=S, M=M, order=0, kind=synth.MAGNETIC, with_disp=False,
+                           cell=[6.0, 6.0, 6.0, 90.0, 90.0, 90.0])
+    m.frac = np.random.default_rng(S + r).integers(0, r, m.frac.shape) / r
+    m.g0, m.count = ((-80, -60, -120), (161, 121, 241)) if box == "symmetric" else ((-77, -50, -110), (79, 100, 230))
+    say(f"magnetic rows of many columns r={r} S={S} M={M} box={m.g0}+{m.count}")
+    sampled_parity(m, most=200)
+
+
 # ------------------------------------------------------------------ lines of a prime length
 @pytest.mark.parametrize("p", [17, 19, 23, 29, 31, 37, 41, 43, 47, 53, 59, 61, 67])
 @pytest.mark.parametrize("axis", [0, 1, 2])
