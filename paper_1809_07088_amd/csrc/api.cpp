@@ -784,7 +784,6 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
     const int h2per = std::max(1, maxT / per_h2);
     const bool friedel = symmetric_box(bx);
     if (bx.half && !friedel) return fail(DSX_ERR_STATE, "half storage needs a symmetric box");
-    std::vector<std::pair<long long, int4>> items, items2, items3, items_mr, items_s;
     int maxrows = 1;
     // the row-staged magnetic form: one thread per G3 of the box (at most
     // kMagRowsMaxThreads), rows per block from the LDS budget (about four blocks per CU),
@@ -916,118 +915,94 @@ dsx_status tables_for(dsx_model m, const Box& bx, DeviceTables** out)
     // that a slice still writes 64-byte runs of an output row
     const int nsl = (t.nact3 >= 16) ? 2 : 1;
     t.n3s = (t.nact3 + nsl - 1) / nsl;
-    for (int k1 = 0; k1 < n1; ++k1) {
+    // the columns in the order of the lists: one and its mirror adjacent
+    std::vector<std::pair<int, int>> cols;           // (2 (lower of c and its mirror) + (c is the upper), c)
+    cols.reserve((size_t)n1 * n2);
+    for (int k1 = 0; k1 < n1; ++k1)
+        for (int k2 = 0; k2 < n2; ++k2) {
+            const int c0 = k1 * n2 + k2, c1 = ((n1 - k1) % n1) * n2 + (n2 - k2) % n2;
+            cols.push_back({std::min(c0, c1) * 2 + (c0 > c1 ? 1 : 0), c0});
+        }
+    std::sort(cols.begin(), cols.end());
+    std::vector<std::pair<int, int>> planes;         // (j1, mirror) of the G1 planes computed
+    std::vector<std::vector<std::pair<int, int>>> groups;
+    for (const auto& col : cols) {
+        const int k1 = col.second / n2, k2 = col.second % n2, km2 = (n2 - k2) % n2;
         const int nH1 = hcount(k1, n1, bx.g0[0], bx.cnt[0]);
         const int H1lo = (int)ceildiv_l((long)bx.g0[0] - k1, n1);
-        for (int k2 = 0; k2 < n2; ++k2) {
-            const int nH2 = hcount(k2, n2, bx.g0[1], bx.cnt[1]);
-            if (nH2 == 0) continue;
-            const int km1 = (n1 - k1) % n1, km2 = (n2 - k2) % n2;
-            // order key: a column and its mirror are adjacent
-            const long long c0 = (long long)k1 * n2 + k2, c1 = (long long)km1 * n2 + km2;
-            const long long key = std::min(c0, c1) * 2 + (c0 > c1 ? 1 : 0);
-            const int np = (nH2 + h2per - 1) / h2per;
-            const int rpp = (nH2 + np - 1) / np;
-            std::vector<std::pair<int, int>> planes;   // (j1, mirror) of the G1 planes computed
-            for (int j1 = 0; j1 < nH1; ++j1) {
-                const int G1 = k1 + n1 * (H1lo + j1);
-                int mirror = 0;
-                if (friedel) {
-                    if (G1 > 0) continue;
-                    if (G1 == 0) {
-                        if (k2 > km2) continue;
-                        mirror = k2 < km2 ? 1 : 0;
-                    } else {
-                        mirror = bx.half ? 0 : 1;   // half storage keeps the planes G1 <= 0 only
-                    }
-                }
-                planes.push_back({j1, mirror});
-            }
-            if (t.rows_mr > 0) {
-                const int npm = (nH2 + t.rows_mr - 1) / t.rows_mr;
-                const int rpm = (nH2 + npm - 1) / npm;
-                // planes grouped by the residue of H1 mod q1, at most four a group, in H1 order
-                std::vector<std::vector<std::pair<int, int>>> groups;
-                if (t.qmod1_mr > 0) {
-                    const int q1 = t.qmod1_mr;
-                    for (int res = 0; res < q1; ++res) {
-                        std::vector<std::pair<int, int>> g;
-                        for (const auto& pl : planes)
-                            if (pl.first % q1 == res) {
-                                // a group's planes are j1, j1 + q1, ... (the kernel steps G1 by q1 n1)
-                                if (g.size() == 4 || (!g.empty() && pl.first != g.back().first + q1)) {
-                                    groups.push_back(g);
-                                    g.clear();
-                                }
-                                g.push_back(pl);
-                            }
-                        if (!g.empty()) groups.push_back(g);
-                    }
+        const int nH2 = hcount(k2, n2, bx.g0[1], bx.cnt[1]);
+        if (nH2 == 0) continue;
+        planes.clear();
+        for (int j1 = 0; j1 < nH1; ++j1) {
+            const int G1 = k1 + n1 * (H1lo + j1);
+            int mirror = 0;
+            if (friedel) {
+                if (G1 > 0) continue;
+                if (G1 == 0) {
+                    if (k2 > km2) continue;
+                    mirror = k2 < km2 ? 1 : 0;
                 } else {
-                    for (const auto& pl : planes) groups.push_back({pl});
-                }
-                for (int part = 0; part < npm; ++part) {
-                    const int h2a = part * rpm, h2b = std::min(nH2, h2a + rpm);
-                    if (h2a >= h2b) continue;
-                    for (const auto& g : groups) {
-                        const int G1 = k1 + n1 * (H1lo + g[0].first);
-                        int wv = h2a | (h2b << 12) | ((int)(g.size() - 1) << 28);
-                        for (size_t p = 0; p < g.size(); ++p) wv |= g[p].second << (24 + p);
-                        items_mr.push_back({key * 4096 + g[0].first, make_int4(k1, k2, G1, wv)});
-                    }
+                    mirror = bx.half ? 0 : 1;   // half storage keeps the planes G1 <= 0 only
                 }
             }
-            if (!mag) {
-                const int nps = (nH2 + t.rows_s - 1) / t.rows_s;
-                const int rps = (nH2 + nps - 1) / nps;
-                for (int part = 0; part < nps; ++part) {
-                    const int h2a = part * rps, h2b = std::min(nH2, h2a + rps);
-                    if (h2a >= h2b) continue;
-                    for (size_t i = 0; i < planes.size(); i += t.npl_s) {
-                        const int j1 = planes[i].first;
-                        const int hasb = t.npl_s == 2 && i + 1 < planes.size() ? 1 : 0;
-                        const int mb = hasb ? planes[i + 1].second : 0;
-                        const int wv = h2a | (h2b << 12) | (planes[i].second << 24) | (hasb << 25) | (mb << 26);
-                        for (int sl = 0; sl < t.slices_s; ++sl)
-                            items_s.push_back({key * 4096 + j1, make_int4(k1, k2, k1 + n1 * (H1lo + j1), wv | (sl << 27))});
-                    }
+            planes.push_back({j1, mirror});
+        }
+        // a list's items of a column: by plane, then by part of the H2 range
+        auto parts = [&](int rows, auto put) {
+            const int np = (nH2 + rows - 1) / rows, per = (nH2 + np - 1) / np;
+            for (int a = 0; a < nH2; a += per) put(a | (std::min(nH2, a + per) << 12));
+        };
+        auto g1_of = [&](size_t i) { return k1 + n1 * (H1lo + planes[i].first); };
+        auto pair_bits = [&](size_t i) {
+            const int hasb = i + 1 < planes.size() ? 1 : 0;
+            return (planes[i].second << 24) | (hasb << 25) | ((hasb ? planes[i + 1].second : 0) << 26);
+        };
+        if (t.rows_mr > 0) {
+            // planes grouped by the residue of H1 mod q1, at most four a group, in H1 order
+            groups.clear();
+            const int q1 = t.qmod1_mr;
+            if (q1 > 0) {
+                for (int res = 0; res < q1; ++res) {
+                    std::vector<std::pair<int, int>> g;
+                    for (const auto& pl : planes)
+                        if (pl.first % q1 == res) {
+                            // a group's planes are j1, j1 + q1, ... (the kernel steps G1 by q1 n1)
+                            if (g.size() == 4 || (!g.empty() && pl.first != g.back().first + q1)) {
+                                groups.push_back(g);
+                                g.clear();
+                            }
+                            g.push_back(pl);
+                        }
+                    if (!g.empty()) groups.push_back(g);
                 }
+                std::sort(groups.begin(), groups.end());
+            } else {
+                for (const auto& pl : planes) groups.push_back({pl});
             }
-            for (int part = 0; part < np; ++part) {
-                const int h2a = part * rpp, h2b = std::min(nH2, h2a + rpp);
-                if (h2a >= h2b) continue;
-                maxrows = std::max(maxrows, h2b - h2a);
-                for (size_t i = 0; mag && t.rows_mr == 0 && i < planes.size(); ++i) {
-                    const int j1 = planes[i].first;
-                    const int G1 = k1 + n1 * (H1lo + j1);
-                    items.push_back({key * 4096 + j1, make_int4(k1, k2, G1, h2a | (h2b << 12) | (planes[i].second << 24))});
-                }
-                // planes are consecutive in H1 (the skipped ones are all at the end)
-                for (size_t i = 0; fold && i < planes.size(); i += 2) {
-                    const int j1 = planes[i].first;
-                    const int G1 = k1 + n1 * (H1lo + j1);
-                    const int hasb = i + 1 < planes.size() ? 1 : 0;
-                    const int mb = hasb ? planes[i + 1].second : 0;
-                    const int wv = h2a | (h2b << 12) | (planes[i].second << 24) | (hasb << 25) | (mb << 26);
-                    items2.push_back({key * 4096 + j1, make_int4(k1, k2, G1, wv)});
-                    // the slices of one block are adjacent: they share the column's spectra
-                    // and the cache lines of the output rows
-                    for (int sl = 0; sl < nsl && nsl > 1; ++sl)
-                        items3.push_back({key * 4096 + j1, make_int4(k1, k2, G1, wv | (sl << 27))});
-                }
+            for (const auto& g : groups) {
+                int wv = (int)(g.size() - 1) << 28;
+                for (size_t p = 0; p < g.size(); ++p) wv |= g[p].second << (24 + p);
+                parts(t.rows_mr, [&](int h2) { t.h_work_mr.push_back(make_int4(k1, k2, k1 + n1 * (H1lo + g[0].first), wv | h2)); });
             }
         }
+        // (planes are consecutive in H1: the skipped ones are all at the end; the slices of one
+        // block are adjacent: they share the column's spectra and the cache lines of the output rows)
+        for (size_t i = 0; !mag && i < planes.size(); i += t.npl_s) {
+            const int wv = t.npl_s == 2 ? pair_bits(i) : planes[i].second << 24;
+            parts(t.rows_s, [&](int h2) {
+                for (int sl = 0; sl < t.slices_s; ++sl) t.h_work_s.push_back(make_int4(k1, k2, g1_of(i), wv | h2 | (sl << 27)));
+            });
+        }
+        for (size_t i = 0; mag && t.rows_mr == 0 && i < planes.size(); ++i)
+            parts(h2per, [&](int h2) { t.h_work.push_back(make_int4(k1, k2, g1_of(i), (planes[i].second << 24) | h2)); });
+        for (size_t i = 0; fold && i < planes.size(); i += 2)
+            parts(h2per, [&](int h2) {
+                const int wv = pair_bits(i) | h2;
+                t.h_work2.push_back(make_int4(k1, k2, g1_of(i), wv));
+                for (int sl = 0; sl < nsl && nsl > 1; ++sl) t.h_work3.push_back(make_int4(k1, k2, g1_of(i), wv | (sl << 27)));
+            });
+        parts(h2per, [&](int h2) { maxrows = std::max(maxrows, (h2 >> 12) - (h2 & 0xfff)); });
     }
-    auto sorted = [](std::vector<std::pair<long long, int4>>& its) {
-        std::stable_sort(its.begin(), its.end(),
-                         [](const std::pair<long long, int4>& x, const std::pair<long long, int4>& y) { return x.first < y.first; });
-        std::vector<int4> v;
-        v.reserve(its.size());
-        for (const auto& x : its) v.push_back(x.second);
-        return v;
-    };
-    t.h_work = sorted(items); t.h_work2 = sorted(items2); t.h_work3 = sorted(items3);
-    t.h_work_mr = sorted(items_mr); t.h_work_s = sorted(items_s);
     const std::vector<int4> work = xcd_order(t.h_work), work2 = xcd_order(t.h_work2), work3 = xcd_order(t.h_work3);
     const std::vector<int4> work_mr = xcd_order(t.h_work_mr), work_s = xcd_order(t.h_work_s);
     t.nwork_s = (int)work_s.size();
