@@ -261,13 +261,13 @@ __device__ __forceinline__ float parity_eval(const float2 (&S)[N + 1], float t3)
 //            multiple of 1/2), the classes folded into the coefficient sets of even and odd H3.
 // A pass over the configurations costs two barriers per site chunk and one latency of loads
 // for all its sites, where staging the sites one by one paid both per site: 16 occupational
-// sites on a 261^3 box (half of it computed) ran at 377 us that way and 107 us here, six sites at
-// order 5 with three configurations on 77 x 85 x 113 at 103 and 61 us, 32 occupational sites with
+// sites on a 261^3 box (half of it computed) ran at 377 us that way and 84 us here, six sites at
+// order 5 with three configurations on 77 x 85 x 113 at 103 and 62 us, 32 occupational sites with
 // 100 configurations on 125^3 at 5.0 and 0.97 ms (the latter still with a read and a wait per
-// phase), five sites at order 4 with two on 389 x 389 x 5 at 282 and 46 us (there only the k3
+// phase), five sites at order 4 with two on 389 x 389 x 5 at 282 and 42 us (there only the k3
 // with points in the box are taken).  Bound by vector issue (levels B and C) and
 // by the latency of level A, which other blocks of the CU cover (LDS of a block <= 64 KB).
-// Several configurations share a block wherever its items leave threads over: each group keeps
+// Several configurations share a block until the launch fills the chip: each group keeps
 // its own |F|^2 sums, added through LDS in a fixed order at the end.
 template <int N>
 constexpr int kPairPitch = n_pairs(N) | 1;   // odd: the k3 of a wave's lanes start on different banks
@@ -1965,7 +1965,7 @@ __global__ __launch_bounds__(kDirectThreads) void k_recombine_direct_merged(cons
 // intensities of their n3 residues k3 once (in LDS; several configurations split over the threads
 // that leaves idle), then writes the rows, c2 / n3 times as many values, as 16-byte stores of one
 // contiguous run.  Bound by those writes: 1024 boxes of 48^3 (453 MB) took 188 us with a load, an
-// |X|^2 and a 4-byte store per voxel (lanes idle past 48), 125 us here, 110 with streaming stores
+// |X|^2 and a 4-byte store per voxel (lanes idle past 48), 125 us here, 110 to 116 with streaming stores
 // and blocks of half the length
 // (whole runs are written once: nothing is gained by keeping them in L2; a 513^3 box that the
 // filter reads next: 323 us for the call, 306 with them).
